@@ -4,14 +4,11 @@
 // here as IVF-Flat (exact scores inside the probed lists) and IVF-PQ
 // (asymmetric distance computation on product-quantised residuals).
 //
-// Build (datastore construction, not the per-step path):
-//   ivf_assign: every key's list = its most similar centroid (one thread per
-//     key, the key in registers, centroids streamed through LDS in tiles);
-//   pq_encode: code j of key i = nearest codebook entry of the residual
-//     slice (one thread per key, all codebooks in LDS);
-//   the index stores each list's rows contiguously (a counting sort by list:
-//     histogram, exclusive scan, scatter); the order inside a list does not
-//     enter any result, since candidates carry their original row id.
+// Build (datastore construction, not the per-step path): every key's list and
+// its PQ codes come from ivf_build.hip; the index stores each list's rows
+// contiguously (a counting sort by list: histogram, exclusive scan, scatter);
+// the order inside a list does not enter any result, since candidates carry
+// their original row id.
 // Search (per step), for Q queries:
 //   ivf_coarse: query-centroid similarities (probe ranking) and, for PQ, the
 //     inner product of the (normalised) query with each centroid;
@@ -32,117 +29,11 @@ namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kIvfThreads = 256;
-constexpr int kAssignTile = 64;   // centroids per LDS tile in ivf_assign
 
 __device__ __forceinline__ float wsum(float x) {
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) x += __shfl_xor(x, off, 64);
     return x;
-}
-
-__device__ __forceinline__ float key_elem(const uint16_t* row, int t, int dt) {
-    const uint16_t b = row[t];
-    if (dt == DT_F16) return (float)__builtin_bit_cast(_Float16, b);
-    return __builtin_bit_cast(float, (uint32_t)b << 16);
-}
-
-// out_list[i] = argmax_l sim(key i, centroid l); ties to the lower l.
-template <int KD>
-__global__ __launch_bounds__(kIvfThreads) void ivf_assign_kernel(
-    const uint16_t* __restrict__ keys, int key_dtype, int64_t n, int d, int64_t ld,
-    const float* __restrict__ centroids, int nlist, int cosine, int32_t* __restrict__ out_list) {
-    __shared__ float s_c[kAssignTile * KD];
-    __shared__ float s_inv[kAssignTile];
-    const int64_t i = (int64_t)blockIdx.x * kIvfThreads + threadIdx.x;
-    float x[KD];
-    float xn = 0.0f;
-#pragma unroll
-    for (int t = 0; t < KD; ++t) {
-        x[t] = (i < n && t < d) ? key_elem(keys + i * ld, t, key_dtype) : 0.0f;
-        xn = __builtin_fmaf(x[t], x[t], xn);
-    }
-    const float inv_x = (xn > 0.0f) ? 1.0f / __builtin_sqrtf(xn) : 0.0f;
-    float best = -__builtin_inff();
-    int arg = 0;
-    for (int l0 = 0; l0 < nlist; l0 += kAssignTile) {
-        const int nt = (nlist - l0 < kAssignTile) ? nlist - l0 : kAssignTile;
-        __syncthreads();
-        for (int e = threadIdx.x; e < nt * KD; e += kIvfThreads) {
-            const int l = e / KD, t = e - l * KD;
-            s_c[e] = t < d ? centroids[(int64_t)(l0 + l) * d + t] : 0.0f;
-        }
-        __syncthreads();
-        if (cosine) {
-            for (int l = threadIdx.x; l < nt; l += kIvfThreads) {
-                float cn = 0.0f;
-                for (int t = 0; t < d; ++t) cn = __builtin_fmaf(s_c[l * KD + t], s_c[l * KD + t], cn);
-                s_inv[l] = (cn > 0.0f) ? 1.0f / __builtin_sqrtf(cn) : 0.0f;
-            }
-            __syncthreads();
-        }
-        for (int l = 0; l < nt; ++l) {
-            float a0 = 0.0f, a1 = 0.0f;
-#pragma unroll
-            for (int t = 0; t < KD; t += 2) {
-                a0 = __builtin_fmaf(x[t], s_c[l * KD + t], a0);
-                a1 = __builtin_fmaf(x[t + 1], s_c[l * KD + t + 1], a1);
-            }
-            float s = a0 + a1;
-            if (cosine) s = (s * s_inv[l]) * inv_x;
-            if (s > best) {
-                best = s;
-                arg = l0 + l;
-            }
-        }
-    }
-    if (i < n) out_list[i] = arg;
-}
-
-// Codes of key i: nearest codebook entry (squared L2, ties to the lower
-// entry) to each slice of the residual key - centroid[list].  One thread per
-// key; the residual slice (dsub <= kMaxDsub values) is formed when needed.
-__global__ __launch_bounds__(kIvfThreads) void pq_encode_kernel(
-    const uint16_t* __restrict__ keys, int key_dtype, int64_t n, int d, int64_t ld,
-    const float* __restrict__ centroids, const int32_t* __restrict__ list_ids,
-    const float* __restrict__ codebooks, int m, int ksub, int nlist,
-    uint8_t* __restrict__ codes) {
-    extern __shared__ float s_cb[];   // m * ksub * dsub = ksub * d floats
-    for (int e = threadIdx.x; e < ksub * d; e += kIvfThreads) s_cb[e] = codebooks[e];
-    __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * kIvfThreads + threadIdx.x;
-    if (i >= n) return;
-    const int dsub = d / m;
-    const int32_t li = list_ids[i];
-    if (li < 0 || li >= nlist) {                 // no such list: code 0 throughout
-        for (int j = 0; j < m; ++j) codes[i * m + j] = 0;
-        return;
-    }
-    const float* c = centroids + (int64_t)li * d;
-    const uint16_t* row = keys + i * ld;
-    for (int j = 0; j < m; ++j) {
-        float rs[kMaxDsub];
-#pragma unroll
-        for (int t = 0; t < kMaxDsub; ++t)
-            rs[t] = t < dsub ? key_elem(row, j * dsub + t, key_dtype) - c[j * dsub + t] : 0.0f;
-        float bd = __builtin_inff();
-        int be = 0;
-        for (int e = 0; e < ksub; ++e) {
-            const float* cb = s_cb + ((int64_t)j * ksub + e) * dsub;
-            float dist = 0.0f;
-#pragma unroll
-            for (int t = 0; t < kMaxDsub; ++t) {
-                if (t < dsub) {
-                    const float df = rs[t] - cb[t];
-                    dist = __builtin_fmaf(df, df, dist);
-                }
-            }
-            if (dist < bd) {
-                bd = dist;
-                be = e;
-            }
-        }
-        codes[i * m + j] = (uint8_t)be;
-    }
 }
 
 // inv[l] = 1 / ||row l|| of an fp32 matrix (0 for a zero row), one wave per row.
@@ -657,33 +548,6 @@ unsigned grid_for(int64_t n, int threads) {
 }
 
 }  // namespace
-
-hipError_t launch_ivf_assign(const void* keys, int key_dtype, int64_t n, int d, int64_t ld,
-                             const float* centroids, int nlist, int cosine, int32_t* out_list,
-                             hipStream_t stream) {
-    const unsigned blocks = (unsigned)((n + kIvfThreads - 1) / kIvfThreads);
-    if (d <= 64)
-        hipLaunchKernelGGL(ivf_assign_kernel<64>, dim3(blocks), dim3(kIvfThreads), 0, stream,
-                           (const uint16_t*)keys, key_dtype, n, d, ld, centroids, nlist, cosine,
-                           out_list);
-    else
-        hipLaunchKernelGGL(ivf_assign_kernel<128>, dim3(blocks), dim3(kIvfThreads), 0, stream,
-                           (const uint16_t*)keys, key_dtype, n, d, ld, centroids, nlist, cosine,
-                           out_list);
-    return hipGetLastError();
-}
-
-hipError_t launch_pq_encode(const void* keys, int key_dtype, int64_t n, int d, int64_t ld,
-                            const float* centroids, int nlist, const int32_t* list_ids,
-                            const float* codebooks, int m, int ksub, uint8_t* codes,
-                            hipStream_t stream) {
-    const unsigned blocks = (unsigned)((n + kIvfThreads - 1) / kIvfThreads);
-    const size_t lds = (size_t)ksub * d * sizeof(float);
-    hipLaunchKernelGGL(pq_encode_kernel, dim3(blocks), dim3(kIvfThreads), lds, stream,
-                       (const uint16_t*)keys, key_dtype, n, d, ld, centroids, list_ids, codebooks,
-                       m, ksub, nlist, codes);
-    return hipGetLastError();
-}
 
 hipError_t launch_f32_inv_norms(const float* rows, int n, int d, float* inv, hipStream_t stream) {
     hipLaunchKernelGGL(f32_inv_norm_kernel,

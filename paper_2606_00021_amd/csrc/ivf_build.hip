@@ -1,0 +1,713 @@
+// Datastore construction for the inverted file (Sec. 3.2 Eq. 7; App.
+// implementation details: IVF-PQ, nlist 4096, pq_m 16 over 64-dim keys):
+//   ivf_assign: every key's list = its most similar centroid, a contraction
+//     of N keys with nlist centroids on the matrix cores;
+//   pq_encode: code j of key i = nearest codebook entry of the j-th slice of
+//     the residual key - centroid[list].
+#include "internal.h"
+
+namespace sense {
+namespace {
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+
+template <int KT>
+__device__ __forceinline__ float elem_f32(uint32_t bits) {
+    if constexpr (KT == DT_F16) return (float)__builtin_bit_cast(_Float16, (uint16_t)bits);
+    return __builtin_bit_cast(float, bits << 16);
+}
+
+// ------------------------------------------------------------- assignment
+// The shift that brings a value's leading bit to 2^14 (0 for zero, infinity
+// and NaN, which stay as they are).
+__device__ __forceinline__ int shift_to_14(float big) {
+    const int ex = (int)(__builtin_bit_cast(uint32_t, big) >> 23) - 127;
+    return (ex > -127 && ex < 128) ? 14 - ex : 0;
+}
+
+// The list of one key in plain fp32 (the definition, centroid by centroid):
+// for keys whose squared norm is not an ordinary number (zero, infinite, NaN
+// or out of fp32's normal range), which the matrix-core path leaves out.
+template <int KT>
+__device__ __attribute__((noinline)) int assign_one(const uint16_t* __restrict__ row, int d,
+                                                    const float* __restrict__ centroids,
+                                                    int nlist, int cosine) {
+    float xn = 0.0f;
+    for (int t = 0; t < d; ++t) {
+        const float x = elem_f32<KT>(row[t]);
+        xn = __builtin_fmaf(x, x, xn);
+    }
+    const float inv_x = (xn > 0.0f) ? 1.0f / __builtin_sqrtf(xn) : 0.0f;
+    float best = -__builtin_inff();
+    int arg = 0;
+    for (int l = 0; l < nlist; ++l) {
+        const float* c = centroids + (int64_t)l * d;
+        float a0 = 0.0f, a1 = 0.0f, cn = 0.0f;
+        for (int t = 0; t < d; t += 2) {
+            a0 = __builtin_fmaf(elem_f32<KT>(row[t]), c[t], a0);
+            a1 = __builtin_fmaf(elem_f32<KT>(row[t + 1]), c[t + 1], a1);
+            cn = __builtin_fmaf(c[t], c[t], cn);
+            cn = __builtin_fmaf(c[t + 1], c[t + 1], cn);
+        }
+        float s = a0 + a1;
+        if (cosine) s = (s * ((cn > 0.0f) ? 1.0f / __builtin_sqrtf(cn) : 0.0f)) * inv_x;
+        if (s > best) {
+            best = s;
+            arg = l;
+        }
+    }
+    return arg;
+}
+
+// out_list[i] = argmax_l sim(key i, centroid l); ties to the lower l.
+//
+// Bound: the matrix cores (n * nlist * d products, twice) and, beside them, the
+// vector ALUs that prepare the centroids, in fp16 for both key types.  A key
+// is scaled by a power of two that brings its largest element to [2^14, 2^15):
+// fp16 keys and the 8-bit mantissas of bf16 are then exact down to 2^-32 of
+// that element (and to 2^-40 of it below); a positive factor does not change
+// the key's best centroid.  An fp32 centroid (normalised first under cosine;
+// scaled likewise under inner product, whose scores are scaled back) is taken
+// in two rounded fp16 parts, which leave 2^-24 of each element: the rounding
+// of one fp32 operation.  Products are exact and summed in the fp32
+// accumulators, the small part first.  A lane keeps the best score of its own
+// four rows of every 16-centroid tile and the tile it came from (strictly
+// greater, in ascending order), five instructions per four scores; at the end
+// the lanes (and waves) merge per key, and four lanes settle which of the
+// winning four rows it was, one row each, in fp32.
+//
+// Two ways to share the centroids:
+//   assign_stage: a wave has its own T tiles of 16 keys; the block's waves
+//     prepare the centroids together, kTileC of them per stage, into LDS in
+//     A-fragment order (conflict-free 16-byte reads), double-buffered with one
+//     barrier a stage.  One half of the waves prepares the next stage before
+//     its products and the other half after them, so that on every SIMD one
+//     wave's preparation runs beside the other's products.
+//   assign_split: the waves of a block hold the same T tiles of keys, and deal
+//     out the centroids, 16 at a time, each preparing its tile in registers:
+//     more preparation per key, but no barrier, and 16 T keys fill a block.
+//
+// 4096 centroids, 64 dims, bf16: 262144 keys 2639 us with one thread per key
+// on the VALU, 291 us staged (0.95 PFLOP/s; a large torch matrix product
+// reaches 1.2), 652 split; 16384 keys 1617, 115 and 43 us.
+
+// The sum or maximum over the G consecutive lanes of a group (G 8, 16 or 32).
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x),
+                                                                 CTRL, 0xF, 0xF, false));
+}
+template <int G>
+__device__ __forceinline__ float group_sum(float x) {
+    x += dpp<0xB1>(x);                             // quad xor 1
+    x += dpp<0x4E>(x);                             // quad xor 2
+    x += dpp<0x141>(x);                            // half-row mirror
+    if constexpr (G >= 16) x += dpp<0x140>(x);     // row mirror
+    if constexpr (G >= 32) x += __shfl_xor(x, 16, 64);
+    return x;
+}
+template <int G>
+__device__ __forceinline__ float group_max(float x) {
+    x = __builtin_fmaxf(x, dpp<0xB1>(x));
+    x = __builtin_fmaxf(x, dpp<0x4E>(x));
+    x = __builtin_fmaxf(x, dpp<0x141>(x));
+    if constexpr (G >= 16) x = __builtin_fmaxf(x, dpp<0x140>(x));
+    if constexpr (G >= 32) x = __builtin_fmaxf(x, __shfl_xor(x, 16, 64));
+    return x;
+}
+
+// The two fp16 parts of x.  No contraction with the product x may come from:
+// the part and the rest must be those of the same rounded number.
+__device__ __forceinline__ void two_parts(float x, _Float16& hi, _Float16& lo) {
+#pragma clang fp contract(off)
+    asm volatile("" : "+v"(x));
+    hi = (_Float16)x;
+    lo = (_Float16)(__builtin_fabsf(x) == __builtin_inff() ? 0.0f : x - (float)hi);
+}
+
+// Keys base + 16 t + col as B fragments (k = 8 grp + 32 ks .. + 7), scaled;
+// rows past n re-read row n - 1.  unscale[t] undoes the scale; bit t of the
+// result: the key's squared norm is an ordinary number.
+template <int KT, int KS, int T>
+__device__ __forceinline__ uint32_t load_keys(const uint16_t* __restrict__ keys, int64_t base,
+                                              int64_t n, int d, int64_t ld, f16x8 (&kf)[T][KS],
+                                              float (&unscale)[T]) {
+    const int lane = threadIdx.x & 63, col = lane & 15, grp = lane >> 4;
+    uint32_t plain = 0;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const int64_t i = base + 16 * t + col;
+        const uint16_t* row = keys + (i < n ? i : n - 1) * ld;
+        u32x4 kw[KS];
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const int e = 8 * grp + 32 * ks;
+            kw[ks] = *(const u32x4*)(row + (e < d ? e : 0));
+        }
+        float xn = 0.0f, big = 0.0f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            if (8 * grp + 32 * ks >= d) kw[ks] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t w = kw[ks][j];
+                const float lo = elem_f32<KT>(w & 0xFFFFu), hi = elem_f32<KT>(w >> 16);
+                xn = __builtin_fmaf(lo, lo, xn);
+                xn = __builtin_fmaf(hi, hi, xn);
+                big = __builtin_fmaxf(big, __builtin_fmaxf(__builtin_fabsf(lo), __builtin_fabsf(hi)));
+            }
+        }
+        xn += __shfl_xor(xn, 16, 64);
+        xn += __shfl_xor(xn, 32, 64);
+        big = __builtin_fmaxf(big, __shfl_xor(big, 16, 64));
+        big = __builtin_fmaxf(big, __shfl_xor(big, 32, 64));
+        plain |= (xn > 0x1p-100f && xn < 0x1p100f) ? 1u << t : 0u;
+        const int sh = shift_to_14(big);
+        unscale[t] = __builtin_ldexpf(1.0f, -sh);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t w = kw[ks][j];
+                kf[t][ks][2 * j] = (_Float16)__builtin_ldexpf(elem_f32<KT>(w & 0xFFFFu), sh);
+                kf[t][ks][2 * j + 1] = (_Float16)__builtin_ldexpf(elem_f32<KT>(w >> 16), sh);
+            }
+        if (t % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // registers: four tiles' loads
+    }
+    return plain;
+}
+
+// The products of one centroid tile (first row l0, parts hi and lo, inner
+// product: f[i] undoes the scale of row 4 grp + i) with T key tiles.
+template <int KS, int T, bool COS>
+__device__ __forceinline__ void tile_products(int l0, const f16x8 (&hi)[KS], const f16x8 (&lo)[KS],
+                                              const float (&f)[4], const f16x8 (&kf)[T][KS],
+                                              const float (&unscale)[T], float (&best)[T],
+                                              int (&row0)[T]) {
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(lo[ks], kf[t][ks], acc, 0, 0, 0);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi[ks], kf[t][ks], acc, 0, 0, 0);
+        if constexpr (!COS)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i] = (acc[i] * unscale[t]) * f[i];
+        const float m = __builtin_fmaxf(__builtin_fmaxf(acc[0], acc[1]),
+                                        __builtin_fmaxf(acc[2], acc[3]));
+        const bool up = m > best[t];
+        best[t] = up ? m : best[t];
+        row0[t] = up ? l0 : row0[t];
+        // Taken here: put off, the comparisons' masks would be kept (and
+        // spilled) instead.
+        asm volatile("" : "+v"(row0[t]));
+        if (t % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // registers: four sums
+    }
+}
+
+// The better of (b, r) and (ob, orow): the larger score, the lower row on a tie.
+__device__ __forceinline__ void take_better(float& b, int& r, float ob, int orow) {
+    const bool up = ob > b || (ob == b && orow < r);
+    b = up ? ob : b;
+    r = up ? orow : r;
+}
+
+// The best group of four rows of each key over the four lanes that hold it.
+__device__ __forceinline__ void merge_lanes(float& b, int& r) {
+#pragma unroll
+    for (int off = 16; off < 64; off <<= 1)
+        take_better(b, r, __shfl_xor(b, off, 64), __shfl_xor(r, off, 64));
+}
+
+// Which of rows r .. r + 3 is the key's best: this lane's row l of them in
+// fp32, merged over the four lanes at distances step and 2 step.
+template <int KT, bool COS>
+__device__ __forceinline__ int settle(const uint16_t* __restrict__ row, int d,
+                                      const float* __restrict__ centroids, int nlist, int l,
+                                      int step) {
+    const float* c = centroids + (int64_t)(l < nlist ? l : 0) * d;
+    float a0 = 0.0f, a1 = 0.0f, c0 = 0.0f, c1 = 0.0f;
+    for (int e = 0; e < d; e += 8) {
+        const u32x4 w = *(const u32x4*)(row + e);
+        float cv[8];
+        __builtin_memcpy(cv, c + e, 32);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            a0 = __builtin_fmaf(elem_f32<KT>(w[j] & 0xFFFFu), cv[2 * j], a0);
+            a1 = __builtin_fmaf(elem_f32<KT>(w[j] >> 16), cv[2 * j + 1], a1);
+            c0 = __builtin_fmaf(cv[2 * j], cv[2 * j], c0);
+            c1 = __builtin_fmaf(cv[2 * j + 1], cv[2 * j + 1], c1);
+        }
+    }
+    float s = a0 + a1;
+    const float cn = c0 + c1;
+    if constexpr (COS) s = s * ((cn > 0.0f) ? 1.0f / __builtin_sqrtf(cn) : 0.0f);
+    // No number among the scores: the first list, as nothing beats it.
+    s = (l < nlist && s == s) ? s : -__builtin_inff();
+    take_better(s, l, __shfl_xor(s, step, 64), __shfl_xor(l, step, 64));
+    take_better(s, l, __shfl_xor(s, 2 * step, 64), __shfl_xor(l, 2 * step, 64));
+    return l;
+}
+
+template <int KT, int KD, int T, bool COS>
+__global__ __launch_bounds__(512) void assign_stage_kernel(
+    const uint16_t* __restrict__ keys, int64_t n, int d, int64_t ld,
+    const float* __restrict__ centroids, int nlist, int32_t* __restrict__ out_list) {
+    constexpr int W = 8;
+    constexpr int KS = KD / 32;                    // 32-dim steps
+    constexpr int kTileC = KD <= 64 ? 64 : 32;     // centroids per stage
+    constexpr int CT = kTileC / 16;                // centroid tiles per stage
+    constexpr int LPC = KD / 4;                    // threads per centroid (4 dims each)
+    constexpr int CPP = 64 * W / 2 / LPC;          // centroids per pass of half the waves
+    constexpr int NP = kTileC / 2 / CPP;           // passes over half a stage
+    static_assert(LPC <= 64 && 2 * NP * CPP == kTileC, "staging shape");
+    __shared__ f16x8 s_a[2][CT][KS][2][64];
+    __shared__ float s_f[2][kTileC];               // inner product: undoes the row's scale
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool early = wv < W / 2;                 // waves w and w + 4 share a SIMD
+    const int col = lane & 15, grp = lane >> 4;
+    const int64_t base = ((int64_t)blockIdx.x * W + wv) * (16 * T);
+
+    // Staging: this thread's 4 dims of rows sr + p * CPP of a stage (dims >= d
+    // are zero; loads on clamped addresses).
+    const int st = tid & (64 * W / 2 - 1);
+    const int sr = (early ? 0 : kTileC / 2) + st / LPC, sd = 4 * (st % LPC);
+    float4 raw[NP];
+    auto request = [&](int l0) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int l = l0 + sr + p * CPP;
+            const bool in = l < nlist && sd < d;
+            __builtin_memcpy(&raw[p], centroids + (in ? (int64_t)l * d + sd : 0), 16);
+        }
+    };
+    auto stage = [&](int l0, int buf) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int r = sr + p * CPP;
+            const bool in = sd < d;
+            float x[4] = {in ? raw[p].x : 0.0f, in ? raw[p].y : 0.0f, in ? raw[p].z : 0.0f,
+                          in ? raw[p].w : 0.0f};
+            if constexpr (COS) {
+                float cn = 0.0f;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) cn = __builtin_fmaf(x[t], x[t], cn);
+                cn = group_sum<LPC>(cn);
+                const float mul = (cn > 0.0f) ? 0x1p14f / __builtin_sqrtf(cn) : 0.0f;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) x[t] = x[t] * mul;
+            } else {
+                float big = 0.0f;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const float v = __builtin_fabsf(x[t]);
+                    big = __builtin_fmaxf(big, v < __builtin_inff() ? v : 0.0f);
+                }
+                const int sh = shift_to_14(group_max<LPC>(big));
+#pragma unroll
+                for (int t = 0; t < 4; ++t) x[t] = __builtin_ldexpf(x[t], sh);
+                if (sd == 0) s_f[buf][r] = __builtin_ldexpf(1.0f, -sh);
+            }
+            f16x4 hi, lo;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                // Rows past the last centroid score NaN: never the best.
+                _Float16 h, l;
+                two_parts(l0 + r < nlist ? x[t] : __builtin_nanf(""), h, l);
+                hi[t] = h;
+                lo[t] = l;
+            }
+            // A[row r % 16][k = sd % 32 ..]: lane 16 * ((sd % 32) / 8) + r % 16.
+            const int al = 16 * ((sd & 31) >> 3) + (r & 15);
+            const int half = (sd >> 2) & 1;
+            ((f16x4*)&s_a[buf][r >> 4][sd >> 5][0][al])[half] = hi;
+            ((f16x4*)&s_a[buf][r >> 4][sd >> 5][1][al])[half] = lo;
+        }
+    };
+
+    request(0);
+    f16x8 kf[T][KS];
+    float unscale[T], best[T];
+    int row0[T];                                   // first row of the best's 16-row tile
+    const uint32_t plain = load_keys<KT, KS, T>(keys, base, n, d, ld, kf, unscale);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        best[t] = -__builtin_inff();
+        row0[t] = 0;
+    }
+    stage(0, 0);
+    if (early) request(kTileC);
+    __syncthreads();
+    int buf = 0;
+    for (int l0 = 0; l0 < nlist; l0 += kTileC) {
+        const bool more = l0 + kTileC < nlist;
+        if (early) {
+            if (more) stage(l0 + kTileC, buf ^ 1);
+            request(l0 + 2 * kTileC);
+        } else {
+            request(l0 + kTileC);
+        }
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            f16x8 hi[KS], lo[KS];
+            float f[4] = {};
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                hi[ks] = s_a[buf][c][ks][0][lane];
+                lo[ks] = s_a[buf][c][ks][1][lane];
+            }
+            if constexpr (!COS)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) f[i] = s_f[buf][16 * c + 4 * grp + i];
+            tile_products<KS, T, COS>(l0 + 16 * c, hi, lo, f, kf, unscale, best, row0);
+        }
+        if (!early && more) stage(l0 + kTileC, buf ^ 1);
+        __syncthreads();
+        buf ^= 1;
+    }
+    for (int t = 0; t < T; ++t) {
+        float b = best[0];
+        int r = row0[0];
+#pragma unroll
+        for (int u = 1; u < T; ++u) {              // t is uniform: scalar selects
+            b = t == u ? best[u] : b;
+            r = t == u ? row0[u] : r;
+        }
+        r += 4 * grp;
+        merge_lanes(b, r);
+        const int64_t i = base + 16 * t + col;
+        const uint16_t* row = keys + (i < n ? i : n - 1) * ld;
+        const int l = settle<KT, COS>(row, d, centroids, nlist, r + grp, 16);
+        if (grp == 0 && i < n)
+            out_list[i] = (plain >> t) & 1u ? l : assign_one<KT>(row, d, centroids, nlist, COS);
+    }
+}
+
+template <int KT, int KD, int T, bool COS>
+__global__ __launch_bounds__(512) void assign_split_kernel(
+    const uint16_t* __restrict__ keys, int64_t n, int d, int64_t ld,
+    const float* __restrict__ centroids, int nlist, int32_t* __restrict__ out_list) {
+    constexpr int W = 8;
+    constexpr int KS = KD / 32;                    // 32-dim steps
+    __shared__ float s_best[W][16 * T];
+    __shared__ int s_row0[W][16 * T];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, grp = lane >> 4;
+    const int64_t base = (int64_t)blockIdx.x * (16 * T);
+    const int ntiles = (nlist + 15) / 16;
+
+    // This lane's part of a centroid tile: row tile * 16 + col, dims 8 grp + 32
+    // ks .. + 7 (rows past the last re-read it, dims >= d read dim 0).
+    float raw[KS][8];
+    auto request = [&](int tile) {
+        int l = tile * 16 + col;
+        l = l < nlist ? l : nlist - 1;
+        const float* c = centroids + (int64_t)l * d;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const int e = 8 * grp + 32 * ks;
+            __builtin_memcpy(raw[ks], c + (e < d ? e : 0), 32);
+        }
+    };
+    request(wv);
+    f16x8 kf[T][KS];
+    float unscale[T], best[T];
+    int row0[T];
+    const uint32_t plain = load_keys<KT, KS, T>(keys, base, n, d, ld, kf, unscale);
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        best[t] = -__builtin_inff();
+        row0[t] = 0;
+    }
+    for (int tile = wv; tile < ntiles; tile += W) {
+        // Normalise or scale, and split.  Rows past the last centroid become
+        // NaN: their scores are never the best.
+        f16x8 hi[KS], lo[KS];
+        float f[4] = {};
+        const bool real = tile * 16 + col < nlist;
+        float mul = 0.0f;                          // cosine: 2^14 / norm
+        int sh = 0;
+        if constexpr (COS) {
+            float cn = 0.0f;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                float a = 0.0f;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) a = __builtin_fmaf(raw[ks][j], raw[ks][j], a);
+                cn += 8 * grp + 32 * ks < d ? a : 0.0f;
+            }
+            cn += __shfl_xor(cn, 16, 64);
+            cn += __shfl_xor(cn, 32, 64);
+            mul = (cn > 0.0f) ? 0x1p14f / __builtin_sqrtf(cn) : 0.0f;
+        } else {
+            float big = 0.0f;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const float v = __builtin_fabsf(raw[ks][j]);
+                    big = __builtin_fmaxf(
+                        big, (v < __builtin_inff() && 8 * grp + 32 * ks < d) ? v : 0.0f);
+                }
+            big = __builtin_fmaxf(big, __shfl_xor(big, 16, 64));
+            big = __builtin_fmaxf(big, __shfl_xor(big, 32, 64));
+            sh = shift_to_14(big);
+            const float inv = __builtin_ldexpf(1.0f, -sh);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) f[i] = __shfl(inv, 4 * grp + i, 64);
+        }
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const bool in = 8 * grp + 32 * ks < d;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                float v = in ? raw[ks][j] : 0.0f;
+                v = COS ? v * mul : __builtin_ldexpf(v, sh);
+                _Float16 h, l;
+                two_parts(real ? v : __builtin_nanf(""), h, l);
+                hi[ks][j] = h;
+                lo[ks][j] = l;
+            }
+        }
+        if (tile + W < ntiles) request(tile + W);
+        tile_products<KS, T, COS>(tile * 16, hi, lo, f, kf, unscale, best, row0);
+    }
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        int r = row0[t] + 4 * grp;
+        merge_lanes(best[t], r);
+        if (grp == 0) {
+            s_best[wv][16 * t + col] = best[t];
+            // The sign marks a key that the products do not serve.
+            s_row0[wv][16 * t + col] = (plain >> t) & 1u ? r : -1;
+        }
+    }
+    __syncthreads();
+    // Four lanes per key: the best group of all waves, then one row each.
+    for (int u = tid; u < 64 * T; u += 64 * W) {
+        const int key = u >> 2;
+        const int64_t i = base + key;
+        float b = s_best[0][key];
+        int r = s_row0[0][key];
+        const bool served = r >= 0;
+#pragma unroll
+        for (int w = 1; w < W; ++w) take_better(b, r, s_best[w][key], s_row0[w][key]);
+        const uint16_t* row = keys + (i < n ? i : n - 1) * ld;
+        const int l = settle<KT, COS>(row, d, centroids, nlist, (served ? r : 0) + (u & 3), 1);
+        if ((u & 3) == 0 && i < n)
+            out_list[i] = served ? l : assign_one<KT>(row, d, centroids, nlist, COS);
+    }
+}
+
+// ---------------------------------------------------------------- encoding
+constexpr int kEncThreads = 256;
+constexpr int kEncGroup = 8;     // entries per comparison with the best so far
+
+// Squared distance of a residual slice to a codebook entry, in dimension
+// order; DS dims, or dsub <= kMaxDsub of them when DS = 0.
+template <int DS>
+__device__ __forceinline__ float slice_dist(const float* rs, const float* __restrict__ cb,
+                                            int dsub) {
+    float dist = 0.0f;
+#pragma unroll
+    for (int t = 0; t < (DS ? DS : kMaxDsub); ++t) {
+        if (DS || t < dsub) {
+            const float df = rs[t] - cb[t];
+            dist = __builtin_fmaf(df, df, dist);
+        }
+    }
+    return dist;
+}
+
+// Codes of key i: nearest codebook entry (squared L2, ties to the lower
+// entry) to each slice of the residual key - centroid[list]; codes j0 ..
+// j0 + jn - 1 of 256 keys per block, one thread per key.
+//
+// Bound: the vector ALUs, 2 DS instructions per (slice, entry) for the
+// distance itself.  Every lane compares with the same entry at the same time,
+// so the codebook comes through scalar loads and enters the subtractions as a
+// scalar operand: no LDS and no vector register for it.  Eight distances are
+// reduced to their minimum before one comparison with the best so far, and the
+// entry inside the winning group is found once per slice, from the same
+// arithmetic (10 instead of 24 selection instructions per eight entries).
+// The slice length is a template parameter (with a run-time length the loop
+// was 16 predicated steps for each entry, from LDS): 262144 keys of 64
+// dims, 16 slices, 256 entries: 2303 -> 240 us, 0.9 of the VALUs' issue rate.
+template <int KT, int DS>
+__global__ __launch_bounds__(kEncThreads) void pq_encode_kernel(
+    const uint16_t* __restrict__ keys, int64_t n, int d, int64_t ld,
+    const float* __restrict__ centroids, const int32_t* __restrict__ list_ids,
+    const float* __restrict__ codebooks, int m, int ksub, int nlist, int jn, int words,
+    uint8_t* __restrict__ codes) {
+    constexpr int R = DS ? DS : kMaxDsub;
+    const int64_t i = (int64_t)blockIdx.x * kEncThreads + threadIdx.x;
+    const int j0 = blockIdx.y * jn;
+    const int j1 = j0 + jn < m ? j0 + jn : m;
+    const int dsub = DS ? DS : d / m;
+    const int64_t ic = i < n ? i : n - 1;
+    const int32_t li = list_ids[ic];
+    const bool known = li >= 0 && li < nlist;      // no such list: code 0 throughout
+    const float* c = centroids + (int64_t)(known ? li : 0) * d;
+    const uint16_t* row = keys + ic * ld;
+    uint32_t word = 0;
+    for (int j = j0; j < j1; ++j) {
+        float rs[R];
+#pragma unroll
+        for (int t = 0; t < R; ++t)
+            rs[t] = (DS || t < dsub) ? elem_f32<KT>(row[j * dsub + t]) - c[j * dsub + t] : 0.0f;
+        const float* cb = codebooks + (int64_t)j * ksub * dsub;
+        float bd = __builtin_inff();
+        int be = 0;
+        int e = 0;
+        for (; e + kEncGroup <= ksub; e += kEncGroup) {
+            float g = slice_dist<DS>(rs, cb + (int64_t)e * dsub, dsub);
+#pragma unroll
+            for (int u = 1; u < kEncGroup; ++u)    // a NaN distance is no minimum
+                g = __builtin_fminf(g, slice_dist<DS>(rs, cb + (int64_t)(e + u) * dsub, dsub));
+            const bool up = g < bd;
+            bd = up ? g : bd;
+            be = up ? e : be;
+        }
+        for (; e < ksub; ++e) {
+            const float g = slice_dist<DS>(rs, cb + (int64_t)e * dsub, dsub);
+            const bool up = g < bd;
+            bd = up ? g : bd;
+            be = up ? e : be;
+        }
+        // The first entry from be on at that distance (the same bits).
+        int code = 0;
+        if (bd < __builtin_inff()) {
+            code = be;
+            while (code < ksub - 1 &&
+                   !(slice_dist<DS>(rs, cb + (int64_t)code * dsub, dsub) == bd))
+                ++code;
+        }
+        if (!known) code = 0;
+        if (words) {
+            word |= (uint32_t)code << (8 * (j & 3));
+            if ((j & 3) == 3) {
+                if (i < n) *(uint32_t*)(codes + i * m + (j & ~3)) = word;
+                word = 0;
+            }
+        } else if (i < n) {
+            codes[i * m + j] = (uint8_t)code;
+        }
+    }
+}
+
+template <int KT, int KD, int T, bool STAGE>
+hipError_t assign_shape(const void* keys, int64_t n, int d, int64_t ld, const float* centroids,
+                        int nlist, int cosine, int32_t* out_list, hipStream_t stream) {
+    const int64_t per = (int64_t)16 * T * (STAGE ? 8 : 1);
+    const dim3 grid((unsigned)((n + per - 1) / per)), block(512);
+    const uint16_t* k = (const uint16_t*)keys;
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, block, 0, stream, k, n, d, ld, centroids, nlist, out_list);
+        return hipGetLastError();
+    };
+    if constexpr (STAGE)
+        return cosine ? go(assign_stage_kernel<KT, KD, T, true>)
+                      : go(assign_stage_kernel<KT, KD, T, false>);
+    else
+        return cosine ? go(assign_split_kernel<KT, KD, T, true>)
+                      : go(assign_split_kernel<KT, KD, T, false>);
+}
+
+// The shape with the least time, from its blocks per compute unit.  Measured
+// at 64 dims and 4096 centroids (us): split with 4 tiles 43 at 16384 keys, 153
+// at 65536; staged with 2 tiles 115 at 16384, 122 at 65536, 186 at 131072;
+// staged with 4 tiles 169 at 131072, 291 at 262144.  Fewer centroids and other
+// dims scale all three alike (50000 x 64 x 512: 38, 29, 44; 100000 x 32 x
+// 1000: 51, 37, 38).  Eight tiles per wave are no faster than four (287 at
+// 262144): two waves a SIMD are then all that fit.
+template <int KT, int KD>
+hipError_t assign_dim(const void* keys, int64_t n, int d, int64_t ld, const float* centroids,
+                      int nlist, int cosine, int32_t* out_list, hipStream_t stream) {
+    const int64_t cus = device_cus();
+    auto rounds = [&](int64_t per) { return (n + per * cus - 1) / (per * cus); };
+    const int64_t split4 = 6 + 37 * rounds(64), stage2 = 30 + 90 * rounds(256),
+                  stage4 = 45 + 123 * rounds(512);
+    if (split4 <= stage2 && split4 <= stage4)
+        return assign_shape<KT, KD, 4, false>(keys, n, d, ld, centroids, nlist, cosine, out_list, stream);
+    if (stage2 < stage4)
+        return assign_shape<KT, KD, 2, true>(keys, n, d, ld, centroids, nlist, cosine, out_list, stream);
+    return assign_shape<KT, KD, 4, true>(keys, n, d, ld, centroids, nlist, cosine, out_list, stream);
+}
+
+template <int KT>
+hipError_t assign_type(const void* keys, int64_t n, int d, int64_t ld, const float* centroids,
+                       int nlist, int cosine, int32_t* out_list, hipStream_t stream) {
+    if (d <= 32) return assign_dim<KT, 32>(keys, n, d, ld, centroids, nlist, cosine, out_list, stream);
+    if (d <= 64) return assign_dim<KT, 64>(keys, n, d, ld, centroids, nlist, cosine, out_list, stream);
+    return assign_dim<KT, 128>(keys, n, d, ld, centroids, nlist, cosine, out_list, stream);
+}
+
+template <int KT, int DS>
+hipError_t encode_dsub(const void* keys, int64_t n, int d, int64_t ld, const float* centroids,
+                       int nlist, const int32_t* list_ids, const float* codebooks, int m, int ksub,
+                       uint8_t* codes, hipStream_t stream) {
+    // All slices of a key in one block once that gives every SIMD four waves;
+    // fewer keys spread their slices over more blocks.
+    const int64_t blocks = (n + kEncThreads - 1) / kEncThreads;
+    const int64_t want = (int64_t)device_cus() * 4;
+    int64_t parts = (want + blocks - 1) / blocks;
+    if (parts > m) parts = m;
+    int jn = (int)((m + parts - 1) / parts);
+    if (jn >= 3 && m % 4 == 0) jn = (jn + 3) / 4 * 4;
+    // Four codes a store where words are aligned and blocks hold whole words.
+    const int words = m % 4 == 0 && jn % 4 == 0 && ((uintptr_t)codes & 3) == 0;
+    hipLaunchKernelGGL((pq_encode_kernel<KT, DS>),
+                       dim3((unsigned)blocks, (unsigned)((m + jn - 1) / jn)), dim3(kEncThreads), 0,
+                       stream, (const uint16_t*)keys, n, d, ld, centroids, list_ids, codebooks, m,
+                       ksub, nlist, jn, words, codes);
+    return hipGetLastError();
+}
+
+template <int KT>
+hipError_t encode_type(const void* keys, int64_t n, int d, int64_t ld, const float* centroids,
+                       int nlist, const int32_t* list_ids, const float* codebooks, int m, int ksub,
+                       uint8_t* codes, hipStream_t stream) {
+    switch (d / m) {
+        case 2:
+            return encode_dsub<KT, 2>(keys, n, d, ld, centroids, nlist, list_ids, codebooks, m, ksub, codes, stream);
+        case 4:
+            return encode_dsub<KT, 4>(keys, n, d, ld, centroids, nlist, list_ids, codebooks, m, ksub, codes, stream);
+        case 8:
+            return encode_dsub<KT, 8>(keys, n, d, ld, centroids, nlist, list_ids, codebooks, m, ksub, codes, stream);
+        case 16:
+            return encode_dsub<KT, 16>(keys, n, d, ld, centroids, nlist, list_ids, codebooks, m, ksub, codes, stream);
+        default:
+            return encode_dsub<KT, 0>(keys, n, d, ld, centroids, nlist, list_ids, codebooks, m, ksub, codes, stream);
+    }
+}
+
+}  // namespace
+
+hipError_t launch_ivf_assign(const void* keys, int key_dtype, int64_t n, int d, int64_t ld,
+                             const float* centroids, int nlist, int cosine, int32_t* out_list,
+                             hipStream_t stream) {
+    return key_dtype == DT_BF16
+               ? assign_type<DT_BF16>(keys, n, d, ld, centroids, nlist, cosine, out_list, stream)
+               : assign_type<DT_F16>(keys, n, d, ld, centroids, nlist, cosine, out_list, stream);
+}
+
+hipError_t launch_pq_encode(const void* keys, int key_dtype, int64_t n, int d, int64_t ld,
+                            const float* centroids, int nlist, const int32_t* list_ids,
+                            const float* codebooks, int m, int ksub, uint8_t* codes,
+                            hipStream_t stream) {
+    return key_dtype == DT_BF16
+               ? encode_type<DT_BF16>(keys, n, d, ld, centroids, nlist, list_ids, codebooks, m,
+                                      ksub, codes, stream)
+               : encode_type<DT_F16>(keys, n, d, ld, centroids, nlist, list_ids, codebooks, m,
+                                     ksub, codes, stream);
+}
+
+}  // namespace sense

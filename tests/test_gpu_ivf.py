@@ -316,3 +316,87 @@ def test_ivf_skewed_lists_with_fewer_candidates_than_k():
                           .astype(np.float64), "cosine")
     check_topk(g_ids[:real], sc[0, :real].cpu().numpy(), cs, real)
     index.close()
+
+
+# Edges of the build kernels' tiles: one key, one under and over a 16-key tile
+# and a block, lists under and over a staged centroid tile, dims that leave a
+# 32-dim step ragged, sub-vectors of every length class, codebooks around the
+# eight entries compared at once.
+BUILD_CASES = [
+    # n, d, key dtype, nlist, metric, m, ksub, key stride, centroid scale
+    (1, 8, "bf16", 1, "cosine", 8, 1, 8, 1.0),
+    (127, 64, "f16", 31, "ip", 16, 7, 64, 1.0),
+    (129, 64, "bf16", 33, "cosine", 32, 8, 72, 1e-15),
+    (2049, 40, "f16", 65, "cosine", 8, 9, 48, 1e6),
+    (35_000, 128, "bf16", 130, "ip", 8, 128, 128, 1e10),
+    (70_001, 24, "f16", 64, "cosine", 8, 256, 24, 1.0),
+    (140_003, 64, "bf16", 97, "cosine", 16, 256, 64, 1.0),
+    (270_001, 32, "bf16", 63, "ip", 4, 200, 40, 1e-4),
+]
+
+
+@pytest.mark.parametrize("case", BUILD_CASES, ids=[str(i) for i in range(len(BUILD_CASES))])
+def test_build_kernel_edges(case):
+    n, d, kdt, nlist, metric, m, ksub, ld, scale = case
+    print(f"[ivf-build-edges] case={case}", flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n + d)
+    dt = {"bf16": torch.bfloat16, "f16": torch.float16}[kdt]
+    cen = torch.randn(nlist, d, generator=g, device=DEV)
+    if nlist > 40:
+        cen[40] = cen[7]                                   # a tie: the lower list wins
+    lab = torch.randint(0, nlist, (n,), generator=g, device=DEV)
+    keys = torch.full((n, ld), 7.0, dtype=dt, device=DEV)[:, :d]
+    keys.copy_(cen[lab] + 0.5 * torch.randn(n, d, generator=g, device=DEV))
+    odd = {}
+    if n > 100:
+        keys[3] = 0.0
+        keys[50, 1] = float("nan")
+        odd = {3: 0, 50: 0}                                # no centroid is better than the first
+    cen *= scale
+    got = sense.sense_ivf_assign(keys, cen, metric)
+    torch.cuda.synchronize()
+    x, c = keys.double(), cen.double()
+    s, weight = x @ c.T, x.norm(dim=1, keepdim=True) * c.norm(dim=1)
+    if metric == "cosine":
+        s = s / weight
+        weight = torch.ones_like(s)
+    gl = got.long()
+    assert int(gl.min()) >= 0 and int(gl.max()) < nlist
+    off = float((gl != s.nan_to_num(-1e300).argmax(dim=1)).float().mean())
+    print(f"[ivf-build-edges] {off:.2e} of the lists are not the 64-bit choice", flush=True)
+    # Two fp32 sums of d products each, and the norms' and scale's roundings.
+    bound = 2 * (d + 8) * 2.0 ** -23 * weight.max(dim=1).values
+    sel = s.gather(1, gl[:, None])[:, 0]
+    ok = sel >= s.max(dim=1).values - bound
+    for row, want in odd.items():
+        assert int(gl[row]) == want
+        ok[row] = True
+    assert bool(ok.all()), f"rows {torch.nonzero(~ok).flatten()[:5].tolist()}"
+    if nlist > 40:
+        assert not bool((gl == 40).any())
+
+    books = 0.5 * scale * torch.randn(m, ksub, d // m, generator=g, device=DEV)
+    if ksub > 8:
+        books[:, 8] = books[:, 2]
+    lists = got.clone()
+    if n > 100:
+        lists[10], lists[11] = -1, nlist                   # no such list: code 0 throughout
+    codes = sense.sense_pq_encode(keys, cen, lists, books).long()
+    torch.cuda.synchronize()
+    if n > 100:
+        assert not bool(codes[10:12].any()) and not bool(codes[50, 1 * m // d]), "code 0"
+    rows = torch.ones(n, dtype=torch.bool, device=DEV)
+    if n > 100:
+        rows[10] = rows[11] = rows[50] = False
+    r = (keys.float() - cen[lists.clamp(0, nlist - 1).long()]).double().view(n, m, d // m)
+    for j in range(m):
+        for i0 in range(0, n, 1 << 15):
+            rj = r[i0:i0 + (1 << 15), j]
+            dist = ((rj[:, None, :] - books[j].double()[None]) ** 2).sum(dim=2)
+            mine = dist.gather(1, codes[i0:i0 + (1 << 15), j:j + 1])[:, 0]
+            best = dist.min(dim=1).values
+            near = mine <= best * (1 + 2 * (d // m + 3) * 2.0 ** -23) + 1e-37
+            assert bool((near | ~rows[i0:i0 + (1 << 15)]).all()), f"slice {j} from row {i0}"
+        if ksub > 8:
+            assert not bool((codes[:, j] == 8).any())
