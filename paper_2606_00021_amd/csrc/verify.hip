@@ -5,24 +5,32 @@
 // row; everything else is per-row scalars.  Two kernels:
 //
 // verify_rows: one block of 256 threads per (row, vocabulary slice).  A
-//   slice is what the block holds in registers: every thread issues all of
-//   its eight 16-byte loads at once (no dependent chain; small blocks keep
-//   the register count low, so many blocks share a compute unit and one's
-//   arithmetic hides another's loads), then
-//     phase 1: m = max of the slice (wave max, then the four waves);
-//     phase 2: with t = (x - m) log2 e,
-//       S   = sum 2^t                 (= sum e^(x-m)),
-//       T2  = sum 2^t * t             (= log2 e * sum e^(x-m)(x-m)),
+//   thread takes four 16-byte words of the slice per step, the next step's
+//   words requested before this one's are used, so a block's loads stay in
+//   flight through its arithmetic, and no step waits for another wave.  Every
+//   lane keeps its own running maximum m2 (times log2 e), and with
+//   t = x log2 e - m2
+//       S   = sum 2^t,   T2 = sum 2^t * t;
+//   beside them the wave counts
 //       cnt = #{v : x_v > x_d} + #{v < d : x_v = x_d},  x_d the draft token's
-//             logit, counted as x_v >= x_d left of d and x_v >= next(x_d)
-//             from d on (one compare per element; in a full slice a wave
-//             ballot per element, counted on the scalar unit).
-//   and stores one 16-byte partial (m, S, T2, cnt) per (row, slice).  With
+//             logit, as x_v >= x_d left of d and x_v >= next(x_d) from d on.
+//   The lanes, then the waves, are brought to one maximum at the end, and the
+//   block stores one 16-byte partial (m2, S, T2, cnt) per (row, slice).  With
 //   p = softmax(x), E = -sum p ln p = ln S - ln2 * T2 / S.  The draft token
 //   is the first argmax exactly when cnt = 0 and is in the top-k set exactly
 //   when cnt < k, so neither an argmax nor a sort of the vocabulary is needed.
 //   Sums are formed in a fixed order (DPP butterflies, then the waves in
 //   order), so results are deterministic.
+//   Rows may start at any element: the elements before the first 16-byte word
+//   of memory and behind the last go to single lanes.
+//
+//   Bound: the read of the rows; per 16-bit logit 6.5 vector instructions
+//   (half of one for the maximum, unpack, fma, exp2 at half rate, add, fma),
+//   one more where a logit of the wave reaches the judged one.
+//   16 x 64 x 8 rows of 32000 fp32, ragged (half judged): 108 -> 77 us, 6.8
+//   TB/s, most of it from dealing the judged rows evenly to the XCDs.  64 x 8 of
+//   152064 bf16: 26 us before and after, 6.0 TB/s with launch and ramp; rows
+//   of 151937, which start anywhere: 50 us one element at a time, 26 so.
 //
 // verify_finalize: one block per candidate group.  Phase 1 gives every
 //   (candidate, position) row its own thread, which merges the row's slices
@@ -39,37 +47,18 @@ namespace {
 
 constexpr int kRowThreads = kVerifyRowThreads;
 constexpr int kRowWaves = kRowThreads / 64;
-constexpr int kNV = 8;             // 16-byte vectors per thread per slice
-constexpr int kScalarPer = 32;     // elements per thread per slice, unaligned rows
+constexpr int kNV = 4;             // 16-byte words per thread and step
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
 struct Partial {
-    float m;
+    float m2;
     float s;
     float t2;
     int cnt;
 };
 
-struct Stats {
-    float m, s, t2;
-};
-
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-
-// Merge of two (m, S, T2) states of disjoint element sets.
-__device__ __forceinline__ Stats merge(const Stats& a, const Stats& b) {
-    if (a.m == -__builtin_inff()) return b;
-    if (b.m == -__builtin_inff()) return a;
-    const float mm = a.m > b.m ? a.m : b.m;
-    const float da = (a.m - mm) * kLog2e, db = (b.m - mm) * kLog2e;
-    const float fa = fast_exp2(da), fb = fast_exp2(db);
-    Stats r;
-    r.m = mm;
-    r.s = fa * a.s + fb * b.s;
-    r.t2 = fa * __builtin_fmaf(da, a.s, a.t2) + fb * __builtin_fmaf(db, b.s, b.t2);
-    return r;
-}
 
 template <int CTRL>
 __device__ __forceinline__ int dpp_i(int x) {
@@ -109,14 +98,15 @@ __device__ __forceinline__ float wave_max_f(float x) {
 }
 
 template <int LT>
+__device__ __forceinline__ float bits_f32(uint32_t bits) {
+    if constexpr (LT == DT_BF16) return __builtin_bit_cast(float, bits << 16);
+    return (float)__builtin_bit_cast(_Float16, (uint16_t)bits);
+}
+
+template <int LT>
 __device__ __forceinline__ float load_one(const char* base, int64_t i) {
-    if constexpr (LT == DT_F32) {
-        return ((const float*)base)[i];
-    } else if constexpr (LT == DT_BF16) {
-        return __builtin_bit_cast(float, (uint32_t)((const uint16_t*)base)[i] << 16);
-    } else {
-        return (float)__builtin_bit_cast(_Float16, ((const uint16_t*)base)[i]);
-    }
+    if constexpr (LT == DT_F32) return ((const float*)base)[i];
+    else return bits_f32<LT>(((const uint16_t*)base)[i]);
 }
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -153,39 +143,172 @@ __device__ __forceinline__ float next_up(float x) {
     return __builtin_bit_cast(float, x > 0.0f ? u + 1u : u - 1u);
 }
 
-// Maximum and fixed-order pairwise sums over the block's per-wave values.
-__device__ __forceinline__ float waves_max(const float* s) {
-    float m = s[0];
-#pragma unroll
-    for (int w = 1; w < kRowWaves; ++w) m = __builtin_fmaxf(m, s[w]);
-    return m;
+// What a lane has seen of a row: m2 = log2 e times the largest logit, and with
+// t = x log2 e - m2 the sums S of 2^t and T2 of 2^t t.  Every change of the
+// maximum goes through the difference of two rounded m2, so that all of a
+// row's terms refer to the same numbers.
+struct State {
+    float m2 = -__builtin_inff(), s = 0.0f, t2 = 0.0f;
+};
+
+// The factor 2^(from - to) and its exponent, for from <= to.  The clamp (where
+// 2^d is 0) covers an empty state (-inf) and two of them (NaN).
+__device__ __forceinline__ float drop_to(float from, float to, float& d) {
+    d = __builtin_fmaxf(from - to, -256.0f);
+    return fast_exp2(d);
 }
-template <int N, typename T, typename Get>
-__device__ __forceinline__ T pair_sum(Get get, int off) {
-    if constexpr (N == 1) {
-        return get(off);
-    } else {
-        return pair_sum<N / 2, T>(get, off) + pair_sum<N / 2, T>(get, off + N / 2);
+
+__device__ __forceinline__ void raise_to(State& a, float m2) {
+    float d;
+    const float f = drop_to(a.m2, m2, d);
+    a.t2 = f * __builtin_fmaf(d, a.s, a.t2);
+    a.s = f * a.s;
+    a.m2 = m2;
+}
+
+// Merges N partials into (a, c): to the largest maximum at once, so that no
+// factor waits for another.
+template <int N>
+__device__ __forceinline__ void merge_all(State& a, int& c, const Partial (&q)[N]) {
+    float m2 = a.m2;
+#pragma unroll
+    for (int u = 0; u < N; ++u) m2 = __builtin_fmaxf(m2, q[u].m2);
+    raise_to(a, m2);
+#pragma unroll
+    for (int u = 0; u < N; ++u) {
+        State b{q[u].m2, q[u].s, q[u].t2};
+        raise_to(b, m2);
+        a.s += b.s;
+        a.t2 += b.t2;
+        c += q[u].cnt;
     }
 }
 
-struct Acc {
-    float s = 0.0f, t2 = 0.0f;
-    int cnt = 0;        // per lane
-    uint32_t wcnt = 0;  // per wave (already summed over its lanes)
-};
-
-// One element of phase 2.  The clamp keeps a -inf logit at weight 0 and
-// contribution 0 (instead of 0 * -inf).
-__device__ __forceinline__ void absorb_sum(Acc& a, float x, float nm) {
-    const float t = __builtin_fmaxf(__builtin_fmaf(x, kLog2e, nm), -256.0f);
-    const float e = fast_exp2(t);
-    a.s += e;
-    a.t2 = __builtin_fmaf(e, t, a.t2);
+// The constant of t = x log2 e + base.
+__device__ __forceinline__ float base_of(float m2) {
+    return m2 == -__builtin_inff() ? 0.0f : -m2;
 }
-__device__ __forceinline__ void absorb(Acc& a, float x, float nm, float thr) {
-    absorb_sum(a, x, nm);
-    a.cnt += (x >= thr) ? 1 : 0;
+
+typedef int16_t i16x2 __attribute__((ext_vector_type(2)));
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+
+// Makes what was derived from the words be derived again: the unpacked values
+// of one path shall not be kept in registers for another.
+template <int U>
+__device__ __forceinline__ void forget(u32x4 (&buf)[U]) {
+#pragma unroll
+    for (int k = 0; k < U; ++k) asm volatile("" : "+v"(buf[k]));
+}
+
+// The largest of a lane's logits, NaN passed over.  As integers, floats of the
+// positive sign keep their order and lie above all of the negative sign, whose
+// order is reversed: one signed maximum, on two 16-bit logits at a time or two
+// operands of a three-way maximum, settles every lane that holds a logit >= 0
+// (half an instruction per logit, without unpacking).  Lanes of negative logits
+// take the unsigned minimum, and a NaN that comes out on top the float maximum.
+template <int LT, int U>
+__device__ __forceinline__ float lane_max(u32x4 (&buf)[U]) {
+    constexpr uint32_t kInf = LT == DT_F32 ? 0x7F800000u : (LT == DT_BF16 ? 0x7F80u : 0x7C00u);
+    float best;
+    bool low, nan;
+    if constexpr (LT == DT_F32) {
+        int32_t top = INT32_MIN;
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int32_t w = (int32_t)buf[k][i];
+                top = w > top ? w : top;
+            }
+        best = __builtin_bit_cast(float, top);
+        low = top < 0;
+        nan = top > (int32_t)kInf;
+    } else {
+        i16x2 top = {INT16_MIN, INT16_MIN};
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t w = buf[k][i];
+                top = __builtin_elementwise_max(top, __builtin_bit_cast(i16x2, w));
+            }
+        const int lo = top.x, hi = top.y;
+        const int t = hi > lo ? hi : lo;
+        best = bits_f32<LT>((uint32_t)t & 0xFFFFu);
+        low = t < 0;
+        nan = t > (int)kInf;
+    }
+    if (__ballot(low)) {
+        if constexpr (LT == DT_F32) {
+            uint32_t top = 0xFFFFFFFFu;
+#pragma unroll
+            for (int k = 0; k < U; ++k)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t w = buf[k][i];
+                    top = w < top ? w : top;
+                }
+            if (low) {
+                best = __builtin_bit_cast(float, top);
+                nan = top > (0x80000000u | kInf);
+            }
+        } else {
+            u16x2 top = {0xFFFFu, 0xFFFFu};
+#pragma unroll
+            for (int k = 0; k < U; ++k)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t w = buf[k][i];
+                    top = __builtin_elementwise_min(top, __builtin_bit_cast(u16x2, w));
+                }
+            const uint32_t lo = top.x, hi = top.y;
+            const uint32_t t = hi < lo ? hi : lo;
+            if (low) {
+                best = bits_f32<LT>(t);
+                nan = t > (0x8000u | kInf);
+            }
+        }
+    }
+    if (__ballot(nan)) {
+        forget(buf);
+        best = -__builtin_inff();
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            float x[LT == DT_F32 ? 4 : 8];
+            unpack<LT>(buf[k], x);
+#pragma unroll
+            for (int u = 0; u < (LT == DT_F32 ? 4 : 8); ++u) best = __builtin_fmaxf(best, x[u]);
+        }
+    }
+    return best;
+}
+
+// The sums over a lane's logits, and over the wave the number of those >= thr
+// (one compare each; the ballot is counted on the scalar unit).  CLAMP keeps a
+// -inf or NaN logit at weight 0 and contribution 0; without it those make s.t2
+// NaN and the caller asks again.
+template <int LT, int U, bool COUNT, bool CLAMP>
+__device__ __forceinline__ void add_up(u32x4 (&buf)[U], float base, const float (&thr)[U],
+                                       float& s, float& t2, uint32_t& wcnt) {
+    constexpr int VW = LT == DT_F32 ? 4 : 8;
+    s = 0.0f;
+    t2 = 0.0f;
+    forget(buf);
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+        float x[VW];
+        unpack<LT>(buf[k], x);
+#pragma unroll
+        for (int u = 0; u < VW; ++u) {
+            float t = __builtin_fmaf(x[u], kLog2e, base);
+            if constexpr (CLAMP) t = __builtin_fmaxf(t, -256.0f);
+            const float e = fast_exp2(t);
+            s += e;
+            t2 = __builtin_fmaf(e, t, t2);
+            if constexpr (COUNT) wcnt += (uint32_t)__popcll(__ballot(x[u] >= thr[k]));
+        }
+        __builtin_amdgcn_sched_barrier(0);           // registers: one word's logits
+    }
 }
 
 // One block per (item, vocabulary slice).  Dense: item = candidate * max_len
@@ -193,17 +316,28 @@ __device__ __forceinline__ void absorb(Acc& a, float x, float nm, float thr) {
 // nodes + u, token tree_tokens[item]; it is judged when u < tree_len[group]
 // and its parent is a node of the group (or none), and its logits row is
 // 1 + parent within the group's 1 + nodes rows.
-template <int LT, bool VEC, bool TREE>
-__global__ __launch_bounds__(kRowThreads) void verify_rows_kernel(
+template <int LT, bool TREE>
+__global__ __launch_bounds__(kRowThreads, 5) void verify_rows_kernel(
     const void* __restrict__ logits, int64_t row_stride, const int32_t* __restrict__ drafts,
-    const int32_t* __restrict__ draft_len, int max_len, int vocab, int slice_len, int n_slices,
-    Partial* __restrict__ partial, const int32_t* __restrict__ tree_parent,
+    const int32_t* __restrict__ draft_len, int max_len, int vocab, int slice_vecs, int n_slices,
+    int64_t n_items, Partial* __restrict__ partial, const int32_t* __restrict__ tree_parent,
     const int32_t* __restrict__ tree_len, int nodes) {
     constexpr int VW = (LT == DT_F32) ? 4 : 8;      // elements per 16-byte load
     constexpr int ES = (LT == DT_F32) ? 4 : 2;      // element size
-    const int item = blockIdx.x;
+    constexpr int U = kNV;
+    int item = blockIdx.x;
     const int slice = blockIdx.y;
     const int tid = threadIdx.x;
+    int cand = 0, pos = 0;
+    if constexpr (!TREE) {
+        // Blocks go to the XCDs in turn, and of ragged drafts the first
+        // positions are judged most often: a candidate's positions are dealt
+        // out from a place of its own, so that no XCD has position 0 of all.
+        cand = item / max_len;
+        pos = (int)(((uint32_t)(item - cand * max_len) + ((uint32_t)cand * 0x9E3779B1u >> 16)) %
+                    (uint32_t)max_len);
+        item = cand * max_len + pos;
+    }
     int64_t row = item;
     // The row's token and the loads that decide whether the row is judged
     // are requested together (every index is in range either way).
@@ -215,160 +349,118 @@ __global__ __launch_bounds__(kRowThreads) void verify_rows_kernel(
         if (u >= tl || par < -1 || par >= nodes) return;   // uniform over the block
         row = (int64_t)g * (nodes + 1) + 1 + par;
     } else {
-        const int c = item / max_len, j = item - c * max_len;
-        int len = draft_len ? draft_len[c] : max_len;
+        int len = draft_len ? draft_len[cand] : max_len;
         len = len < 0 ? 0 : (len > max_len ? max_len : len);
-        if (j >= len) return;                        // uniform over the block
+        if (pos >= len) return;          // uniform over the block
     }
 
     const bool valid = tok >= 0 && tok < vocab;
     const char* rowp = (const char*)logits + row * row_stride * ES;
     const int tk = valid ? tok : -1;                 // -1: the count is unused
 
-    const int v0 = slice * slice_len;
-    const int v1 = (v0 + slice_len < vocab) ? v0 + slice_len : vocab;
-    Acc acc;
-    float mx = -__builtin_inff();
-    __shared__ float s_max[kRowWaves];
+    // The row in 16-byte words of memory: `head` elements before the first,
+    // `words` of them, the rest behind the last.  This block's share.
+    int head = (int)(((0 - (uintptr_t)rowp) & 15) / ES);
+    head = head < vocab ? head : vocab;
+    const int words = (vocab - head) / VW;
+    const int w0 = slice * slice_vecs;
+    const int left = words - w0;
+    const int nvec = left < 0 ? 0 : (left < slice_vecs ? left : slice_vecs);
+    const int v0 = head + w0 * VW;                   // first element of the share's words
+    const u32x4* vp = (const u32x4*)(rowp + (int64_t)v0 * ES);
+    const int steps = (nvec + U * kRowThreads - 1) / (U * kRowThreads);
 
-    if constexpr (VEC) {
-        const int nvec = (v1 - v0) / VW;
-        const u32x4* vp = (const u32x4*)(rowp + (int64_t)v0 * ES);
-        u32x4 buf[kNV];
+    auto load = [&](u32x4 (&buf)[U], int s) {
 #pragma unroll
-        for (int k = 0; k < kNV; ++k) {
-            const int i = tid + k * kRowThreads;
-            buf[k] = (i < nvec) ? __builtin_nontemporal_load(vp + i) : u32x4{0u, 0u, 0u, 0u};
+        for (int k = 0; k < U; ++k) {
+            const int i = tid + (s * U + k) * kRowThreads;
+            buf[k] = __builtin_nontemporal_load(vp + (i < nvec ? i : nvec - 1));
         }
-        // Fewer than VW trailing elements (last slice only), and the judged
-        // token's logit: both requested unconditionally (clamped to a real
-        // element) together with the slice, so that no load waits for
-        // another.
-        const int vt = v0 + nvec * VW + tid;
-        const bool has_t = vt < v1;
-        const float xt_raw = load_one<LT>(rowp, has_t ? vt : v0);
-        const float xd_raw = load_one<LT>(rowp, valid ? tok : v0);
+    };
+    u32x4 ba[U], bb[U];
+    if (steps > 0) load(ba, 0);
+    // One element more for some lanes of the first wave: the row's head (first
+    // slice), what follows its last word (last slice), and the elements of the
+    // judged token's word left of it.
+    const int tail0 = head + words * VW;
+    const int dword = v0 + (tk < v0 ? 0 : (tk - v0) / VW * VW);
+    const bool is_head = slice == 0 && tid < head;
+    const bool is_tail = slice == n_slices - 1 && tid >= 8 && tail0 + tid - 8 < vocab;
+    const bool is_tie = tid >= 16 && tid < 16 + VW && tk >= v0 && tk < v0 + nvec * VW &&
+                        dword + tid - 16 < tk;
+    const int at = is_head ? tid : (is_tail ? tail0 + tid - 8 : (is_tie ? dword + tid - 16 : 0));
+    const float xe = load_one<LT>(rowp, at);
+    const float xd_raw = load_one<LT>(rowp, valid ? tok : 0);
+    __builtin_amdgcn_sched_barrier(0);
+    // The rank count's thresholds, left of d and from d on.
+    const float xd = valid ? xd_raw : __builtin_inff();
+    const float thr_lo = xd, thr_hi = next_up(xd);
+
+    State st;
+    uint32_t wcnt = 0;                               // per wave
+    auto absorb = [&](u32x4 (&buf)[U], int s) {
+        if ((s + 1) * (U * kRowThreads) > nvec) {    // the row's last words: -inf past them
+            constexpr uint32_t kNone = LT == DT_F32    ? 0xFF800000u
+                                       : LT == DT_BF16 ? 0xFF80FF80u
+                                                       : 0xFC00FC00u;
+#pragma unroll
+            for (int k = 0; k < U; ++k)
+                if (tid + (s * U + k) * kRowThreads >= nvec)
+                    buf[k] = u32x4{kNone, kNone, kNone, kNone};
+        }
+        const float top = lane_max<LT, U>(buf);
+        const float m2 = __builtin_fmaxf(st.m2, top * kLog2e);
+        raise_to(st, m2);
+        const float base = base_of(m2);
+        float thr[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+            thr[k] = v0 + (tid + (s * U + k) * kRowThreads + 1) * VW <= tk ? thr_lo : thr_hi;
+        float s1, t1;
+        // No logit of the wave reaches the judged one: nothing to count.
+        if (__ballot(top >= xd)) add_up<LT, U, true, false>(buf, base, thr, s1, t1, wcnt);
+        else add_up<LT, U, false, false>(buf, base, thr, s1, t1, wcnt);
+        if (__ballot(t1 != t1)) add_up<LT, U, false, true>(buf, base, thr, s1, t1, wcnt);
+        st.s += s1;
+        st.t2 += t1;
+    };
+    // Loads past the last step all fall on the share's last word.
+    for (int s = 0; s < steps; s += 2) {
+        load(bb, s + 1);
         __builtin_amdgcn_sched_barrier(0);
-        const float xt = has_t ? xt_raw : -__builtin_inff();
-#pragma unroll
-        for (int k = 0; k < kNV; ++k) {
-            if (tid + k * kRowThreads < nvec) {
-                float x[VW];
-                unpack<LT>(buf[k], x);
-#pragma unroll
-                for (int u = 0; u < VW; ++u) mx = __builtin_fmaxf(mx, x[u]);
-            }
-        }
-        mx = __builtin_fmaxf(mx, xt);
-        const float wm = wave_max_f(mx);
-        if ((tid & 63) == 0) s_max[tid >> 6] = wm;
-        __syncthreads();
-        const float m = waves_max(s_max);
-        mx = m;
-        // The thresholds of the rank count (left of d / from d on), formed
-        // only here, so that the judged logit's load is not waited for
-        // before phase 1.
-        const float xd = valid ? xd_raw : 0.0f;
-        const float thr_lo = xd, thr_hi = next_up(xd);
-        {
-            // An all -inf slice keeps weight 0 (t clamps) but still counts ties.
-            const float nm = (m == -__builtin_inff()) ? 0.0f : -m * kLog2e;
-            if (nvec >= kNV * kRowThreads) {
-                // A full slice (every one but a row's last): no lane is
-                // idle, so the rank count is a wave ballot per element,
-                // counted on the scalar unit (one vector compare each).
-                uint32_t wc = 0;
-#pragma unroll
-                for (int k = 0; k < kNV; ++k) {
-                    const int i = tid + k * kRowThreads;
-                    float x[VW];
-                    unpack<LT>(buf[k], x);
-                    const int vb = v0 + i * VW;
-                    const float thr = (vb + VW <= tk) ? thr_lo : thr_hi;
-#pragma unroll
-                    for (int u = 0; u < VW; ++u) {
-                        absorb_sum(acc, x[u], nm);
-                        wc += (uint32_t)__popcll(__ballot(x[u] >= thr));
-                    }
-                }
-                acc.wcnt = wc;
-            } else {
-#pragma unroll
-                for (int k = 0; k < kNV; ++k) {
-                    const int i = tid + k * kRowThreads;
-                    if (i < nvec) {
-                        float x[VW];
-                        unpack<LT>(buf[k], x);
-                        const int vb = v0 + i * VW;
-                        const float thr = (vb + VW <= tk) ? thr_lo : thr_hi;
-#pragma unroll
-                        for (int u = 0; u < VW; ++u) absorb(acc, x[u], nm, thr);
-                    }
-                }
-            }
-            if (has_t) absorb(acc, xt, nm, vt < tk ? thr_lo : thr_hi);
-            // The vector holding d was counted with x > x_d throughout; its
-            // elements left of d equal to x_d also rank above d.  Only the
-            // thread that holds it adds them (its registers, picked by
-            // selects), so no other element pays for the test.
-            const int id = (tk - v0) / VW;
-            if (tk > v0 && id < nvec && id % kRowThreads == tid && tk - (v0 + id * VW) > 0) {
-                const int kd = id / kRowThreads;
-                u32x4 w = buf[0];
-#pragma unroll
-                for (int k = 1; k < kNV; ++k) w = (k == kd) ? buf[k] : w;
-                float x[VW];
-                unpack<LT>(w, x);
-                const int nl = tk - (v0 + id * VW);
-#pragma unroll
-                for (int u = 0; u < VW; ++u) acc.cnt += (u < nl && x[u] == xd) ? 1 : 0;
-            }
-        }
-    } else {
-        // Unconditional loads (positions past the slice re-read its first
-        // element and are set to -inf), so all of them are in flight at once.
-        float x[kScalarPer];
-#pragma unroll
-        for (int k = 0; k < kScalarPer; ++k) {
-            const int v = v0 + tid + k * kRowThreads;
-            x[k] = load_one<LT>(rowp, v < v1 ? v : v0);
-        }
-        const float xd_raw = load_one<LT>(rowp, valid ? tok : v0);
+        absorb(ba, s);
+        load(ba, s + 2);
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int k = 0; k < kScalarPer; ++k) {
-            const int v = v0 + tid + k * kRowThreads;
-            if (v >= v1) x[k] = -__builtin_inff();
-            mx = __builtin_fmaxf(mx, x[k]);
-        }
-        const float wm = wave_max_f(mx);
-        if ((tid & 63) == 0) s_max[tid >> 6] = wm;
-        __syncthreads();
-        const float m = waves_max(s_max);
-        mx = m;
-        const float xd = valid ? xd_raw : 0.0f;
-        const float thr_lo = xd, thr_hi = next_up(xd);   // left of d / from d on
-        {
-            const float nm = (m == -__builtin_inff()) ? 0.0f : -m * kLog2e;
-#pragma unroll
-            for (int k = 0; k < kScalarPer; ++k) {
-                const int v = v0 + tid + k * kRowThreads;
-                if (v < v1) absorb(acc, x[k], nm, v < tk ? thr_lo : thr_hi);
-            }
-        }
+        if (s + 1 < steps) absorb(bb, s + 1);
+    }
+
+    int cnt = 0;
+    if (is_head || is_tail) {
+        const float m2 = __builtin_fmaxf(st.m2, xe * kLog2e);
+        raise_to(st, m2);
+        const float t = __builtin_fmaxf(__builtin_fmaf(xe, kLog2e, base_of(m2)), -256.0f);
+        const float e = fast_exp2(t);
+        st.s += e;
+        st.t2 = __builtin_fmaf(e, t, st.t2);
+        cnt = xe >= (at < tk ? thr_lo : thr_hi) ? 1 : 0;
+    } else if (is_tie) {
+        // The word holding d was counted with x > x_d throughout; its
+        // elements left of d equal to x_d also rank above d.
+        cnt = xe == xd ? 1 : 0;
     }
 
     // Block sums in a fixed order.
-    const float ws = wave_sum_f(acc.s), wt = wave_sum_f(acc.t2);
-    const int wc = wave_sum_i(acc.cnt) + (int)acc.wcnt;
+    raise_to(st, wave_max_f(st.m2));
+    const float ws = wave_sum_f(st.s), wt = wave_sum_f(st.t2);
+    const int wc = wave_sum_i(cnt) + (int)wcnt;
     __shared__ Partial s_w[kRowWaves];
-    if ((tid & 63) == 0) s_w[tid >> 6] = Partial{mx, ws, wt, wc};
+    if ((tid & 63) == 0) s_w[tid >> 6] = Partial{st.m2, ws, wt, wc};
     __syncthreads();
     if (tid == 0) {
-        Partial p{mx, pair_sum<kRowWaves, float>([&](int w) { return s_w[w].s; }, 0),
-                  pair_sum<kRowWaves, float>([&](int w) { return s_w[w].t2; }, 0),
-                  pair_sum<kRowWaves, int>([&](int w) { return s_w[w].cnt; }, 0)};
-        partial[(int64_t)item * n_slices + slice] = p;
+        State a;
+        int c = 0;
+        merge_all<kRowWaves>(a, c, s_w);
+        partial[(int64_t)slice * n_items + item] = Partial{a.m2, a.s, a.t2, c};
     }
 }
 
@@ -382,27 +474,22 @@ __device__ __forceinline__ uint64_t bits_upto(int x) {  // bits 0..x set (x may 
 
 // Merge of an item's slice partials in slice order.  Loads go out in
 // batches of kMergeBatch (clamped indices, no branch around a load, so none
-// waits for the one before it); the first merge with the empty state returns
-// slice 0 unchanged.
+// waits for the one before it).
 constexpr int kMergeBatch = 8;
 
-__device__ __forceinline__ void merge_partials(const Partial* p, int n_slices, Stats* st,
-                                               int* cnt) {
-    Stats a{-__builtin_inff(), 0.0f, 0.0f};
+__device__ __forceinline__ void merge_partials(const Partial* p, int64_t n_items, int n_slices,
+                                               State* st, int* cnt) {
+    State a;
     int c = 0;
     for (int s0 = 0; s0 < n_slices; s0 += kMergeBatch) {
         Partial q[kMergeBatch];
 #pragma unroll
         for (int u = 0; u < kMergeBatch; ++u)
-            q[u] = p[(s0 + u < n_slices) ? s0 + u : n_slices - 1];
+            q[u] = p[((s0 + u < n_slices) ? s0 + u : n_slices - 1) * n_items];
 #pragma unroll
-        for (int u = 0; u < kMergeBatch; ++u) {
-            if (s0 + u < n_slices) {
-                a = (s0 + u == 0) ? Stats{q[u].m, q[u].s, q[u].t2}
-                                  : merge(a, Stats{q[u].m, q[u].s, q[u].t2});
-                c += q[u].cnt;
-            }
-        }
+        for (int u = 1; u < kMergeBatch; ++u)
+            if (s0 + u >= n_slices) q[u] = Partial{-__builtin_inff(), 0.0f, 0.0f, 0};
+        merge_all(a, c, q);
     }
     *st = a;
     *cnt = c;
@@ -410,7 +497,7 @@ __device__ __forceinline__ void merge_partials(const Partial* p, int n_slices, S
 
 // Row statistics of one item from its merged partials: the entropy score
 // and the rank of the judged token; bits em | ent<<1 | topk<<2.
-__device__ __forceinline__ uint8_t item_bits(const Stats& a, int cnt, int tok, int vocab,
+__device__ __forceinline__ uint8_t item_bits(const State& a, int cnt, int tok, int vocab,
                                              const GateParams& gp, float* score, int* rank) {
     const float e_nats = __logf(a.s) - (kLn2 * a.t2) / a.s;
     *score = e_nats * gp.ent_scale;
@@ -463,6 +550,7 @@ __global__ __launch_bounds__(kFinThreads) void verify_finalize_kernel(
     __shared__ uint64_t s_em[kFinChunkCands];     // exact-match bit per position
     __shared__ uint64_t s_gate[kFinChunkCands];   // gate bit per position
     const int g = blockIdx.x;
+    const int64_t n_items = (int64_t)gridDim.x * group_size * max_len;
     const int by_rows = kFinChunkRows / max_len;
     const int chunk_cands = by_rows < kFinChunkCands ? by_rows : kFinChunkCands;
     const uint64_t in_draft = bits_upto(max_len - 1);
@@ -484,9 +572,9 @@ __global__ __launch_bounds__(kFinThreads) void verify_finalize_kernel(
             // the draft were not written and are not used).
             int len = draft_len ? draft_len[c] : max_len;
             const int tok = drafts[row];
-            Stats st;
+            State st;
             int cnt;
-            merge_partials(partial + row * n_slices, n_slices, &st, &cnt);
+            merge_partials(partial + row, n_items, n_slices, &st, &cnt);
             len = len < 0 ? 0 : (len > max_len ? max_len : len);
             uint8_t bits = 0;
             float score = 0.0f;
@@ -565,6 +653,7 @@ __global__ __launch_bounds__(kFinThreads) void verify_finalize_tree_kernel(
     __shared__ uint8_t s_len[kMaxGroup];        // per draft: its length
     const int g = blockIdx.x;
     const int nodes = group_size * max_len;
+    const int64_t n_items = (int64_t)gridDim.x * nodes;
     const int L = tree_len[g] < nodes ? tree_len[g] : nodes;
     const uint64_t in_draft = bits_upto(max_len - 1);
     for (int cl = threadIdx.x; cl < group_size; cl += kFinThreads) {
@@ -578,9 +667,9 @@ __global__ __launch_bounds__(kFinThreads) void verify_finalize_tree_kernel(
         // judged were not written and are not used).
         const int tok = tree_tokens[item];
         const int par = tree_parent[item];
-        Stats st;
+        State st;
         int cnt;
-        merge_partials(partial + (int64_t)item * n_slices, n_slices, &st, &cnt);
+        merge_partials(partial + item, n_items, n_slices, &st, &cnt);
         uint8_t bits = 0;
         float score = 0.0f;
         int rank = vocab;
@@ -652,15 +741,38 @@ __global__ __launch_bounds__(kFinThreads) void verify_finalize_tree_kernel(
 }
 
 struct Plan {
-    bool vec;
     int n_slices;
-    int slice_len;
+    int slice_vecs;                // 16-byte words per slice: whole steps of a block
 };
 
-Plan plan_slices(int vocab, int dtype, bool vec) {
-    const int vw = (dtype == DT_F32) ? 4 : 8;
-    const int slice_len = vec ? kRowThreads * kNV * vw : kRowThreads * kScalarPer;
-    return Plan{vec, (vocab + slice_len - 1) / slice_len, slice_len};
+constexpr int kStepVecs = kRowThreads * kNV;
+// Slices: at most 8 steps (128 KiB; longer ones leave the last blocks of a large
+// batch alone; 2 to 16 steps within 2 % of each other).  A small batch is cut
+// finer, to 4096 slices of two steps or more, since rows of a ragged batch or
+// of a trie may be dead (64 + 16 drafts of 8, 152064 bf16, 7 tenths judged:
+// 24.8 us with 4 slices a row, 21.8 with 7, 23.4 with 10), and to one step each
+// only up to 512 of them (16 x 6 ragged rows of 128256 bf16: 7.8 us in slices
+// of one step, 7.3 of two).
+constexpr int64_t kSliceSteps = 8, kFillBlocks = 4096, kFillSingle = 512;
+
+// The most slices of a row, whatever the logits' type: one step of 16-bit
+// logits each.  The workspace holds one partial for each of them.
+int most_slices(int vocab) { return (int)(((int64_t)vocab + 8 * kStepVecs - 1) / (8 * kStepVecs)); }
+
+Plan make_plan(int logits_dtype, int64_t n_items, int vocab) {
+    const int vw = logits_dtype == DT_F32 ? 4 : 8;
+    const int64_t steps = ((int64_t)vocab + (int64_t)vw * kStepVecs - 1) / ((int64_t)vw * kStepVecs);
+    const int64_t by_size = (steps + kSliceSteps - 1) / kSliceSteps;
+    const int64_t pairs = (steps + 1) / 2;
+    const int64_t fill = (kFillBlocks + n_items - 1) / n_items;
+    const int64_t single = (kFillSingle + n_items - 1) / n_items;
+    int64_t n = fill < pairs ? fill : pairs;
+    n = n > by_size ? n : by_size;
+    n = n > single ? n : single;
+    const int64_t most = most_slices(vocab);
+    n = n < most ? n : most;
+    const int64_t per = (steps + n - 1) / n;
+    return Plan{(int)((steps + per - 1) / per), (int)(per * kStepVecs)};
 }
 
 template <int LT, bool TREE>
@@ -669,14 +781,9 @@ hipError_t launch_rows_t(const void* logits, int64_t row_stride, const int32_t* 
                          const Plan& pl, Partial* part, const int32_t* tree_parent,
                          const int32_t* tree_len, int nodes, hipStream_t stream) {
     const dim3 grid((unsigned)n_items, (unsigned)pl.n_slices);
-    if (pl.vec)
-        hipLaunchKernelGGL((verify_rows_kernel<LT, true, TREE>), grid, dim3(kRowThreads), 0,
-                           stream, logits, row_stride, tokens, draft_len, max_len, vocab,
-                           pl.slice_len, pl.n_slices, part, tree_parent, tree_len, nodes);
-    else
-        hipLaunchKernelGGL((verify_rows_kernel<LT, false, TREE>), grid, dim3(kRowThreads), 0,
-                           stream, logits, row_stride, tokens, draft_len, max_len, vocab,
-                           pl.slice_len, pl.n_slices, part, tree_parent, tree_len, nodes);
+    hipLaunchKernelGGL((verify_rows_kernel<LT, TREE>), grid, dim3(kRowThreads), 0, stream, logits, row_stride, tokens, draft_len,
+                       max_len, vocab, pl.slice_vecs, pl.n_slices, n_items, part, tree_parent,
+                       tree_len, nodes);
     return hipGetLastError();
 }
 
@@ -702,18 +809,10 @@ hipError_t launch_rows(const void* logits, int logits_dtype, int64_t row_stride,
     }
 }
 
-Plan make_plan(const void* logits, int logits_dtype, int64_t row_stride, int vocab) {
-    const int es = (logits_dtype == DT_F32) ? 4 : 2;
-    const bool vec = ((uintptr_t)logits % 16 == 0) && ((row_stride * es) % 16 == 0);
-    return plan_slices(vocab, logits_dtype, vec);
-}
-
 }  // namespace
 
 size_t verify_workspace_bytes(int n_cand, int max_len, int vocab) {
-    // The unaligned-row plan has the most slices.
-    const Plan p = plan_slices(vocab, DT_BF16, false);
-    return (size_t)n_cand * (size_t)max_len * (size_t)p.n_slices * sizeof(Partial);
+    return (size_t)n_cand * (size_t)max_len * (size_t)most_slices(vocab) * sizeof(Partial);
 }
 
 size_t verify_tree_workspace_bytes(int n_cand, int max_len, int vocab, int n_groups) {
@@ -730,7 +829,7 @@ hipError_t launch_verify(const void* logits, int logits_dtype, int64_t row_strid
                          uint8_t* out_masks, int32_t* out_rank, void* workspace,
                          hipStream_t stream) {
     if (n_cand == 0) return hipSuccess;
-    const Plan pl = make_plan(logits, logits_dtype, row_stride, vocab);
+    const Plan pl = make_plan(logits_dtype, (int64_t)n_cand * max_len, vocab);
     Partial* part = (Partial*)workspace;
     hipError_t e = launch_rows<false>(logits, logits_dtype, row_stride, drafts, draft_len,
                                       (int64_t)n_cand * max_len, max_len, vocab, pl, part,
@@ -751,7 +850,7 @@ hipError_t launch_verify_tree(const void* logits, int logits_dtype, int64_t row_
                               uint8_t* out_masks, int32_t* out_rank, void* workspace,
                               hipStream_t stream) {
     if (n_cand == 0) return hipSuccess;
-    const Plan pl = make_plan(logits, logits_dtype, row_stride, vocab);
+    const Plan pl = make_plan(logits_dtype, (int64_t)n_cand * max_len, vocab);
     Partial* part = (Partial*)workspace;
     const int gs = n_cand / n_groups;
     const int nodes = gs * max_len;

@@ -215,3 +215,34 @@ def test_nan_logits_stay_in_range():
     assert ((best >= 0) & (best < c // 2)).all()
     rank = out["rank"].cpu().numpy()
     assert ((rank >= 0) & (rank <= v)).all()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("v", [1, 5, 8, 23, 4096, 8191, 8205, 16389, 41000])
+def test_rows_at_every_alignment_and_step_edge(dtype, v):
+    """Rows of an odd stride, so that they start at every element of a 16-byte
+    word, of sizes around a block's step (1024 words) and below one word; lanes
+    whose logits are all negative (the maximum's other branch), rows with
+    masked (-inf) logits, and judged tokens in the head, at both ends of a word
+    and in the tail, with equal logits left of them."""
+    logits, drafts = structured(41, 6, 8, v, p_match=0.5, dtype=dtype)
+    logits[1::2] = logits[1::2] - 64.0               # every logit below zero
+    logits[2, :, 1::3] = -float("inf")
+    for j in range(8):
+        d = min(v - 1, [0, 1, 7, 8, v // 2, v - 8, v - 2, v - 1][j] % v)
+        drafts[3, j] = drafts[4, j] = d
+        for w in range(max(0, d - 3), d):
+            logits[4, j, w] = logits[4, j, d]
+    stride = v + (1 - v % 2)
+    flat = torch.zeros(6 * 8 * stride + 8, dtype=TDT[dtype])
+    rows = flat[3:3 + 6 * 8 * stride].view(6, 8, stride)
+    rows[..., :v] = logits
+    rows[..., v:] = 100.0                            # padding: beyond the vocabulary
+    dev = flat.to(DEV)[3:3 + 6 * 8 * stride].view(6, 8, stride)
+    lens = np.array([8, 8, 8, 8, 8, 3], dtype=np.int32)
+    out = sense.sense_soft_gate_verify(dev, drafts.to(DEV), torch.as_tensor(lens).to(DEV),
+                                       n_groups=2, vocab=v)
+    torch.cuda.synchronize()
+    ref = oracle.soft_gate_verify(host_bits(logits.contiguous()), dtype, drafts.numpy(), lens,
+                                  n_groups=2)
+    check_verify(out, ref, 0.05, lens)
