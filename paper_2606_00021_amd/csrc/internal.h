@@ -273,20 +273,15 @@ hipError_t launch_query_split(const float* queries, int nq, int d, int key_dtype
                               const float* key_norm_max, void* scratch, hipStream_t stream);
 
 // Batched scan of short keys (d <= kSmallDim) on the matrix cores, for at
-// most 64 queries of a split batch (see scan_short.hip).  Row r of the scan
-// is stored row r * row_step.  WRITE: scores[q * n_rows + r].  FILTER: a row
-// whose packed key (score, r * row_step) is at least tau[q] goes to
-// cand[q * cap + ...]: wave w of short_scan_waves(n_rows) fills its slots
-// [w * kShortSlots, (w + 1) * kShortSlots) (the rest padding keys), and the
-// overflow is appended at counts[q] (which starts at the slot area's size).
-constexpr int kShortSlots = 4;
-int64_t short_scan_waves(int64_t n_rows);
+// most 64 queries of a split batch (see scan_short.hip): every score
+// (launch_scan_short), or each query's best score per group of group_rows
+// consecutive rows (launch_scan_groups), whose best groups' rows
+// launch_score_groups then packs into selection keys.
 struct ShortScan {
     const void* keys;
     int key_dtype;
     int64_t ld;
     int64_t n_rows;
-    int64_t row_step;
     int d;
     const uint16_t* qhi;
     const uint16_t* qlo;
@@ -294,13 +289,34 @@ struct ShortScan {
     int nq;
     bool split;
     const float* inv_norm;
-    float* scores;            // WRITE mode
-    const uint64_t* tau;      // FILTER mode
-    int32_t* counts;
-    uint64_t* cand;
-    int64_t cap;
+    float* scores;            // scores[q * n_rows + r]
+    int group_rows;
+    int64_t n_groups;
+    float* gmax;              // gmax[q * n_groups + g]
 };
+constexpr int kMaxGroupRows = 64;
+int short_group_rows(int64_t n_rows);
+// Rows the sizing of a short-key candidate list counts beside the store's.
+int64_t short_list_slots(int64_t n_rows);
 hipError_t launch_scan_short(const ShortScan& s, hipStream_t stream);
+hipError_t launch_scan_groups(const ShortScan& s, hipStream_t stream);
+// What follows the group maxima, in one launch where it fits (best_groups_fit).
+struct TopkOut {
+    int k;
+    int64_t* ids;
+    float* scores;
+    int32_t* drafts;
+    int32_t* draft_len;
+    const int32_t* spans;
+    const int32_t* span_len;
+    int max_span;
+    int64_t span_stride;
+};
+bool best_groups_fit(const ShortScan& s, int n_hits);
+hipError_t launch_best_groups(const ShortScan& s, int n_hits, const TopkOut& o,
+                              hipStream_t stream);
+hipError_t launch_score_groups(const ShortScan& s, const int64_t* ids, int k, int n_hits,
+                               uint64_t* keys, hipStream_t stream);
 // tau[q] = packed key of the k-th best row of a strided sample (the sample
 // top-k's ids are sample positions; row = id * row_step), its score lowered
 // by margin[q] when margin is not NULL; counts[q] = slot_area.

@@ -13,22 +13,21 @@
 // (hi, lo) MFMA 16x16x32 instructions.
 //
 // The 64 x n score matrix would be 256 MB at n = 1M: writing it and reading
-// it back for the top-k costs more than reading the keys.  So the scan runs
-// twice: first over a strided sample of rows writing scores, whose per-query
-// k-th best packed key tau bounds the final k-th best from below; then over
-// all rows, keeping only rows whose packed key reaches tau: each wave has a
-// few slots per query (about k * rows_per_wave / sample rows survive per
-// wave, ~1-2 at the bench shape), filled in order (ballot + popcount), and a
-// query's overflow list takes what does not fit.
-// Every true top-k row passes, so the result is exact; the scores of both
-// passes come from the same instructions, hence the same bits.
+// it back for the top-k costs more than reading the keys.  So a large store is
+// cut into groups of 16 to 64 consecutive rows, and the scan stores each
+// query's best score per group only (scan_groups_kernel).  The k best groups by
+// (score descending, group ascending) hold the k best rows by (score
+// descending, row ascending): the best rows of those k groups precede any row
+// of another group.  The rows of these groups are scored again
+// (score_groups_kernel) and their top k is the result.  Both passes and the
+// plain scan form a score with the same instructions, hence the same bits.
 #include "internal.h"
 #include "lds_dma.h"
+#include "topk_device.h"
+
+#include <type_traits>
 
 namespace sense {
-
-int64_t short_rows_per_wave(int64_t n_rows);
-
 namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -38,7 +37,6 @@ typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int kShortThreads = 256;
 constexpr int kShortDepth = 4;     // 16-key tiles in flight per wave
-static_assert(kShortSlots <= 16, "one padding slot per lane of a 16-lane group");
 
 template <int KT>
 __device__ __forceinline__ f32x4 mfma(const u32x4& a, const u32x4& b, const f32x4& c) {
@@ -51,24 +49,13 @@ __device__ __forceinline__ f32x4 mfma(const u32x4& a, const u32x4& b, const f32x
 }
 
 // NT query tiles of 16, KS k-steps of 32 dims (d <= 32 * KS).
-template <int KT, int NT, int KS, bool SPLIT, bool FILTER>
+template <int KT, int NT, int KS, bool SPLIT>
 __global__ __launch_bounds__(kShortThreads, 2) void scan_short_kernel(ShortScan s,
                                                                   int64_t rows_per_wave) {
-    // Per query: {scale 1/|q|, threshold score}, in LDS (read in the
-    // epilogue without a wait on the key loads in flight, and without
-    // registers).  A row passes the filter when its score is not below the
-    // threshold score: a superset of the rows whose packed key reaches tau
-    // (a NaN threshold, from a NaN tau or a sample without k rows, lets
-    // every row through).  Queries past nq get +inf and are also checked by
-    // index before anything is stored.
-    __shared__ float2 s_qt[64];
-    if (threadIdx.x < 64) {
-        const int q = threadIdx.x;
-        float th = 0.0f;
-        if constexpr (FILTER)
-            th = q < s.nq ? key_score((uint32_t)(s.tau[q] >> 32)) : __builtin_inff();
-        s_qt[q] = float2{q < 16 * NT ? s.inv_qn[q] : 0.0f, th};
-    }
+    // The scales 1/|q| in LDS (read in the epilogue without a wait on the key
+    // loads in flight, and without registers).
+    __shared__ float s_qn[64];
+    if (threadIdx.x < 64) s_qn[threadIdx.x] = threadIdx.x < 16 * NT ? s.inv_qn[threadIdx.x] : 0.0f;
     __syncthreads();
     const int lane = threadIdx.x & 63;
     // The wave index is uniform: the row loop below is then a scalar loop.
@@ -93,12 +80,6 @@ __global__ __launch_bounds__(kShortThreads, 2) void scan_short_kernel(ShortScan 
                 alo[t][ks] = ok ? *(const u32x4*)(s.qlo + qrow * s.d + dim) : u32x4{0u, 0u, 0u, 0u};
         }
     }
-    int cnt[NT][4];       // FILTER: survivors so far per query (same in a 16-lane group)
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) cnt[t][i] = 0;
-
     // This lane's key row advances by 16 rows per tile: pointers step by a
     // fixed stride (no 64-bit multiplies per tile).  Every load is issued
     // unconditionally, so the compiler can count the loads in flight exactly
@@ -108,12 +89,12 @@ __global__ __launch_bounds__(kShortThreads, 2) void scan_short_kernel(ShortScan 
     // comes in with the tile (keys and the key norm): a load issued later and
     // consumed earlier would make the wave wait for all the tiles in flight
     // before it.
-    const int64_t key_step = 16 * s.row_step * s.ld;
-    const int64_t norm_step = s.inv_norm ? 16 * s.row_step : 0;
+    const int64_t key_step = 16 * s.ld;
+    const int64_t norm_step = s.inv_norm ? 16 : 0;
     const int64_t row_first = (r0 + col < r1) ? r0 + col : r1 - 1;
-    const uint16_t* kp = (const uint16_t*)s.keys + row_first * s.row_step * s.ld;
+    const uint16_t* kp = (const uint16_t*)s.keys + row_first * s.ld;
     // Without key norms the norm load reads a fixed valid word (unused).
-    const float* np = s.inv_norm ? s.inv_norm + row_first * s.row_step : s.inv_qn;
+    const float* np = s.inv_norm ? s.inv_norm + row_first : s.inv_qn;
     const bool dim0 = 8 * grp < s.d;                 // this lane's dims hold key elements
     const bool dim1 = 8 * grp + 32 < s.d;            // ... in the second k-step
     const int off0 = dim0 ? 8 * grp : 0;
@@ -144,10 +125,8 @@ __global__ __launch_bounds__(kShortThreads, 2) void scan_short_kernel(ShortScan 
             }
         }
     };
-    // Scores of row r (this lane's key) for every query, then the store
-    // (scores) or the filter (survivor keys).
+    // Scores of row r (this lane's key) for every query.
     auto epilogue = [&](int64_t r, const f32x4 (&acc)[NT], float kn) {
-        const bool ok = r < r1;
         float v[NT][4];
 #pragma unroll
         for (int t = 0; t < NT; ++t)
@@ -155,61 +134,16 @@ __global__ __launch_bounds__(kShortThreads, 2) void scan_short_kernel(ShortScan 
             for (int i = 0; i < 4; ++i) {
                 v[t][i] = acc[t][i];
                 if (s.inv_norm) v[t][i] = v[t][i] * kn;
-                v[t][i] = v[t][i] * s_qt[16 * t + 4 * grp + i].x;
+                v[t][i] = v[t][i] * s_qn[16 * t + 4 * grp + i];
             }
-        if constexpr (!FILTER) {
-            if (!ok) return;
+        if (r >= r1) return;
 #pragma unroll
-            for (int t = 0; t < NT; ++t)
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int q = 16 * t + 4 * grp + i;
-                    if (q < s.nq) s.scores[(int64_t)q * s.n_rows + r] = v[t][i];
-                }
-        } else {
-            // One float compare per score, all of them (and their threshold
-            // reads) before any branch; then a branch per query and key
-            // group only where something passed.
-            uint64_t bal[NT][4];
-#pragma unroll
-            for (int t = 0; t < NT; ++t)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    bal[t][i] = __ballot(ok & !(v[t][i] < s_qt[16 * t + 4 * grp + i].y));
-            // Survivors go to this wave's own slots of the query (a slot
-            // index from the ballot, no atomic: a returned atomic would make
-            // the wave wait for its tiles in flight); a wave with more than
-            // kShortSlots survivors for one query appends the rest to the
-            // query's overflow list.
-            const int64_t orig = r * s.row_step;
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    if (bal[t][i] == 0) continue;
-                    const int q = 16 * t + 4 * grp + i;
-                    const bool pass = (bal[t][i] >> lane) & 1;
-                    const uint32_t gm = (uint32_t)(bal[t][i] >> (16 * grp)) & 0xFFFFu;
-                    const int slot = cnt[t][i] + __popc(gm & ((1u << col) - 1u));
-                    if (pass && q < s.nq) {
-                        const uint64_t key = pack_key(v[t][i], (uint32_t)orig);
-                        uint64_t* cq = s.cand + (int64_t)q * s.cap;
-                        if (slot < kShortSlots) {
-                            cq[wave * kShortSlots + slot] = key;
-                        } else {
-                            // Rare.  The empty asm keeps this store apart
-                            // from the slot store: merged, every survivor
-                            // would wait for the atomic's result and with it
-                            // for all the tiles in flight.
-                            const int pos = atomicAdd(&s.counts[q], 1);
-                            cq[pos] = key;
-                            __asm__ volatile("" ::: "memory");
-                        }
-                    }
-                    cnt[t][i] += __popc(gm);
-                }
+            for (int i = 0; i < 4; ++i) {
+                const int q = 16 * t + 4 * grp + i;
+                if (q < s.nq) s.scores[(int64_t)q * s.n_rows + r] = v[t][i];
             }
-        }
     };
 
     u32x4 buf[kShortDepth][KS];
@@ -234,108 +168,125 @@ __global__ __launch_bounds__(kShortThreads, 2) void scan_short_kernel(ShortScan 
             epilogue(base + 16 * u + col, acc, knu);
         }
     }
-    if constexpr (FILTER) {
-        // Unused slots become padding keys.  Lane col 0 of each group saw
-        // every tile its group saw, so its counts are the group's.
+}
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x),
+                                                                 CTRL, 0xF, 0xF, false));
+}
+
+// Maxima that pass over a quiet NaN (every operand here is a product or one of
+// these); as instructions, since fmaxf quiets each operand first.
+__device__ __forceinline__ float max_f(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ float max3_f(float a, float b, float c) {
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+// One step of a transposing maximum over lane pairs (the lanes that CTRL swaps
+// differ in `bit`): of each two values a lane keeps one and gives the other
+// away, the lane with the bit set keeps the second.
+template <int CTRL, int N>
+__device__ __forceinline__ void swap_max(float (&v)[16], bool bit) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int c0 = __shfl(cnt[t][i], lane & ~15, 64);
-                const int q = 16 * t + 4 * grp + i;
-                if (q < s.nq && col >= c0 && col < kShortSlots)
-                    s.cand[(int64_t)q * s.cap + wave * kShortSlots + col] = 0;
-            }
+    for (int j = 0; j < N / 2; ++j) {
+        const float keep = bit ? v[2 * j + 1] : v[2 * j], give = bit ? v[2 * j] : v[2 * j + 1];
+        v[j] = max_f(keep, dpp_f<CTRL>(give));
     }
 }
 
-// The filtered pass over 64-dim keys with the keys staged in LDS.  Loading
-// the matrix-core operand layout straight from HBM (above) reads 64 bytes of
-// each of 16 rows per load instruction, a pattern this device serves well
-// below its streaming rate, and holds every tile in flight in registers (four
-// per wave at most).  Here global_load_lds_dwordx4 moves whole 128-byte rows
-// (8 rows per instruction) into a private ring of kRing tile slots per wave,
-// kRing - 1 tiles ahead of the products, and each lane reads its operand
-// from LDS: lane L = 8p + w of an instruction writes entry w of row p and
-// fetches unit (w + p) mod 8 of that row (unit u of row p sits at entry
-// (u - p) mod 8, rows 8-15 at entries 64 + ...), so the 8 rows a matrix-core
-// read touches in each half fall on 8 distinct 16-byte groups.  A tile's 16
-// key norms come the same way (global_load_lds_dword; inner product loads a
-// valid dummy word and uses a scale of 1).  Every iteration issues the same
-// three loads (tiles past the end reload the last one), so the wait for a
-// tile is a fixed count; the loop holds no load into registers, whose waits
-// the compiler would take for every load in flight.  The products and the
-// filter are those of scan_short_kernel in the same order: the same bits.
-// The pass is bound by its per-score instructions, not by HBM; the register
-// room the ring frees lets the epilogue take the key scale and the
-// row-valid mask once per tile instead of once per score.
+// The best score of every group of group_rows rows (a multiple of 16) for each
+// query, gmax[q * n_groups + g]; NaN where no row of the group has a number.
+//
+// Reading the matrix-core operand layout straight from HBM (as above) takes 64
+// bytes of each of 16 rows per load instruction, a pattern this device serves
+// below its streaming rate, and holds every tile in flight in registers.  Here
+// global_load_lds_dwordx4 moves whole rows (8 per instruction) into a private
+// ring of kRing tile slots per wave, kRing - 1 tiles ahead of the products, and
+// each lane reads its operand from LDS: lane L = 8p + w of an instruction
+// writes entry w of row p and fetches unit (w + p) mod 8 of that row (unit u of
+// row p sits at entry (u - p) mod 8, rows 8-15 at entries 64 + ...), so the 8
+// rows a matrix-core read touches in each half fall on 8 distinct 16-byte
+// groups.  Units past a row shorter than 64 dims re-read its first and are
+// zeroed as operands.  A tile's 16 key norms come the same way (inner product
+// loads a valid dummy word and uses a scale of 1).  Every iteration issues the
+// same three loads (tiles past the end reload the last one), so the wait for a
+// tile is a fixed count.
+//
+// A lane keeps the running maxima of its key column for its 4 * NT queries (one
+// product and one maximum per score); at a group's end 16 columns meet in four
+// transposing steps that leave each lane one query's maximum.  The query's
+// scale, a factor >= 0, goes on the maximum: rounding is monotone, so that is
+// the maximum of the scaled scores.
+//
+// Bound: the read of the keys, 34 us for 1M x 64 bf16 and 64 queries (4.1 TB/s;
+// 33 without the products: loads alone, norms and stores of the maxima), of
+// which a wave's start is about 6.  Four slots and twice the waves: 36-38 us.
+// With the selection, rescore and top-k behind it 100 -> 75.7 us a search
+// against a strided sample's k-th best as the threshold of a filtered pass.
 constexpr int kRing = 8;           // tile slots per wave
 constexpr int kDmaOps = 3;         // loads per tile: two key halves, the norms
 
 template <int KT, int NT, bool SPLIT>
-__global__ __launch_bounds__(kShortThreads, 2) void scan_short_lds_kernel(ShortScan s,
-                                                                      int64_t rows_per_wave) {
-    __shared__ float2 s_qt[64];
+__global__ __launch_bounds__(kShortThreads, 2) void scan_groups_kernel(ShortScan s,
+                                                                       int64_t groups_per_wave) {
     __shared__ __attribute__((aligned(16))) u32x4 s_key[kShortThreads / 64][kRing][128];
     __shared__ __attribute__((aligned(16))) float s_norm[kShortThreads / 64][kRing][64];
-    if (threadIdx.x < 64) {
-        const int q = threadIdx.x;
-        const float th = q < s.nq ? key_score((uint32_t)(s.tau[q] >> 32)) : __builtin_inff();
-        s_qt[q] = float2{q < 16 * NT ? s.inv_qn[q] : 0.0f, th};
-    }
-    __syncthreads();
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t wave = (int64_t)blockIdx.x * (kShortThreads / 64) + wv;
-    const int64_t r0 = wave * rows_per_wave;
+    const int64_t g0 = wave * groups_per_wave;
+    const int64_t r0 = g0 * s.group_rows;
     if (r0 >= s.n_rows) return;                      // uniform over the wave
-    const int64_t r1 = (r0 + rows_per_wave < s.n_rows) ? r0 + rows_per_wave : s.n_rows;
-    const int64_t ntiles = (r1 - r0 + 15) / 16;
+    const int64_t r_end = (g0 + groups_per_wave) * s.group_rows;
+    const int64_t r1 = r_end < s.n_rows ? r_end : s.n_rows;
+    const int ntiles = (int)((r1 - r0 + 15) / 16);
     const int col = lane & 15, grp = lane >> 4;
+    const bool dim0 = 8 * grp < s.d, dim1 = 8 * grp + 32 < s.d;   // this lane's dims exist
 
-    // Query fragments (d = 64: two k-steps), taken into registers before the
-    // first LDS load is issued.
-    u32x4 ahi[NT][2], alo[NT][2];
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            const int64_t qoff = (int64_t)(16 * t + col) * 64 + 8 * grp + 32 * ks;
-            ahi[t][ks] = *(const u32x4*)(s.qhi + qoff);
-            if constexpr (SPLIT) alo[t][ks] = *(const u32x4*)(s.qlo + qoff);
-        }
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            asm volatile("" : "+v"(ahi[t][ks]));
-            if constexpr (SPLIT) asm volatile("" : "+v"(alo[t][ks]));
-        }
-    int cnt[NT][4];       // survivors so far per query (same in a 16-lane group)
-#pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) cnt[t][i] = 0;
-
+    // This lane's sources: its unit of rows dp and 8 + dp of the next tile to
+    // request, and its column's norm; they step by a tile at a time and stay on
+    // the last one.
     const uint16_t* keys = (const uint16_t*)s.keys;
-    const int64_t rstride = s.row_step * s.ld;
     const bool cosine = s.inv_norm != nullptr;
     const int dp = lane >> 3;                        // row within a load instruction
-    const int du = ((lane & 7) + dp) & 7;            // 16-byte unit it fetches
-    auto issue = [&](int64_t tile) {
-        const int64_t tc = tile < ntiles ? tile : ntiles - 1;
-        const int slot = (int)(tile % kRing);
-        const int64_t base = r0 + tc * 16;
+    int du = ((lane & 7) + dp) & 7;                  // 16-byte unit it fetches
+    du = 8 * du < s.d ? du : 0;
+    const int64_t step = 16 * s.ld, nstep = cosine ? 16 : 0;
+    const uint16_t* src[2];
+    const float* nsrc;
+    auto at_tile = [&](int t) {                      // on clamped rows
+        const int64_t base = r0 + 16 * (int64_t)t;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            int64_t row = base + 8 * i + dp;
-            if (row >= r1) row = r1 - 1;
-            dma16_nt(keys + row * rstride + du * 8, &s_key[wv][slot][64 * i]);
+            const int64_t row = base + 8 * i + dp;
+            src[i] = keys + (row < r1 ? row : r1 - 1) * s.ld + du * 8;
         }
-        int64_t nrow = base + col;
-        if (nrow >= r1) nrow = r1 - 1;
-        dma4(cosine ? (const void*)(s.inv_norm + nrow * s.row_step) : (const void*)s.inv_qn,
-                  &s_norm[wv][slot][0]);
+        const int64_t nrow = base + col;
+        nsrc = cosine ? s.inv_norm + (nrow < r1 ? nrow : r1 - 1) : s.inv_qn;
+    };
+    at_tile(0);
+    int req = 0;                                     // the tile src stands on
+    const bool ragged = r0 + 16 * (int64_t)ntiles > r1;
+    auto issue = [&](int slot) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) dma16_nt(src[i], &s_key[wv][slot][64 * i]);
+        dma4(nsrc, &s_norm[wv][slot][0]);
+        if (++req < ntiles) {
+            if (ragged && req == ntiles - 1) {
+                at_tile(req);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 2; ++i) src[i] += step;
+                nsrc += nstep;
+            }
+        }
     };
     // Operand entry of this lane in a tile for k-step ks: row col, unit
     // grp + 4 ks.
@@ -347,73 +298,319 @@ __global__ __launch_bounds__(kShortThreads, 2) void scan_short_lds_kernel(ShortS
 
 #pragma unroll
     for (int t = 0; t < kRing - 1; ++t) issue(t);
-    for (int64_t t = 0; t < ntiles; ++t) {
-        wait_vmcnt<(kRing - 2) * kDmaOps>();           // tile t is in LDS
-        issue(t + kRing - 1);                       // the slot read at t - 1
-        const int slot = (int)(t % kRing);
-        const u32x4 b0 = s_key[wv][slot][e0], b1 = s_key[wv][slot][e1];
-        const float kn = s_norm[wv][slot][col];
-        f32x4 acc[NT];
+    // Query fragments A[m = col][k = 8*grp + 32*ks], requested behind the
+    // first tiles and taken into registers before the loop.
+    u32x4 ahi[NT][2], alo[NT][2];
 #pragma unroll
-        for (int q = 0; q < NT; ++q) {
-            acc[q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            acc[q] = mfma<KT>(ahi[q][0], b0, acc[q]);
-            if constexpr (SPLIT) acc[q] = mfma<KT>(alo[q][0], b0, acc[q]);
-            acc[q] = mfma<KT>(ahi[q][1], b1, acc[q]);
-            if constexpr (SPLIT) acc[q] = mfma<KT>(alo[q][1], b1, acc[q]);
-        }
-        const int64_t r = r0 + t * 16 + col;
-        // Inner product scales by 1 (x * 1 is x: the same bits as no scale).
-        const float ks = cosine ? kn : 1.0f;
-        const uint64_t okm = __ballot(r < r1);
-        float v[NT][4];
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int q = 0; q < NT; ++q)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[q][i] = (acc[q][i] * ks) * s_qt[16 * q + 4 * grp + i].x;
-        uint64_t bal[NT][4];
-#pragma unroll
-        for (int q = 0; q < NT; ++q)
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                bal[q][i] = __ballot(!(v[q][i] < s_qt[16 * q + 4 * grp + i].y)) & okm;
-        const int64_t orig = r * s.row_step;
-#pragma unroll
-        for (int q = 0; q < NT; ++q) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if (bal[q][i] == 0) continue;
-                const int qi = 16 * q + 4 * grp + i;
-                const bool pass = (bal[q][i] >> lane) & 1;
-                const uint32_t gm = (uint32_t)(bal[q][i] >> (16 * grp)) & 0xFFFFu;
-                const int slot_i = cnt[q][i] + __popc(gm & ((1u << col) - 1u));
-                if (pass && qi < s.nq) {
-                    const uint64_t key = pack_key(v[q][i], (uint32_t)orig);
-                    uint64_t* cq = s.cand + (int64_t)qi * s.cap;
-                    if (slot_i < kShortSlots) {
-                        cq[wave * kShortSlots + slot_i] = key;
-                    } else {
-                        const int pos = atomicAdd(&s.counts[qi], 1);
-                        cq[pos] = key;
-                        __asm__ volatile("" ::: "memory");
-                    }
-                }
-                cnt[q][i] += __popc(gm);
+        for (int ks = 0; ks < 2; ++ks) {
+            const bool in = ks ? dim1 : dim0;
+            const int64_t qoff = (int64_t)(16 * t + col) * s.d + (in ? 8 * grp + 32 * ks : 0);
+            ahi[t][ks] = *(const u32x4*)(s.qhi + qoff);
+            if constexpr (SPLIT) alo[t][ks] = *(const u32x4*)(s.qlo + qoff);
+            if (!in) {
+                ahi[t][ks] = u32x4{0u, 0u, 0u, 0u};
+                if constexpr (SPLIT) alo[t][ks] = u32x4{0u, 0u, 0u, 0u};
             }
         }
-    }
-    wait_vmcnt<0>();
-    // Unused slots become padding keys (lane col 0 of each group saw every
-    // tile its group saw).
+    // The query this lane stores: value 4 t + i of its group's 16 ends up in
+    // the lane whose column is that number with its bits reversed.
+    const int mine = (int)(__builtin_bitreverse32((uint32_t)col) >> 28);
+    const int oq = 16 * (mine >> 2) + 4 * grp + (mine & 3);
+    const bool out = oq < s.nq;
+    float scale = s.inv_qn[out ? oq : 0];
+    float* dst = s.gmax + (int64_t)(out ? oq : 0) * s.n_groups + g0;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            asm volatile("" : "+v"(ahi[t][ks]));
+            if constexpr (SPLIT) asm volatile("" : "+v"(alo[t][ks]));
+        }
+    asm volatile("" : "+v"(scale));
+
+    float m[NT][4];
 #pragma unroll
     for (int q = 0; q < NT; ++q)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int c0 = __shfl(cnt[q][i], lane & ~15, 64);
-            const int qi = 16 * q + 4 * grp + i;
-            if (qi < s.nq && col >= c0 && col < kShortSlots)
-                s.cand[(int64_t)qi * s.cap + wave * kShortSlots + col] = 0;
+        for (int i = 0; i < 4; ++i) m[q][i] = __builtin_nanf("");
+    // Tile t's operands and column scale, after its three loads are complete.
+    // Inner product scales by 1 (x * 1 is x: the same bits as no scale); rows
+    // past the last one score NaN, which no maximum takes.
+    auto take = [&](int t, u32x4& b0, u32x4& b1, float& ks) {
+        const int slot = t % kRing;
+        b0 = s_key[wv][slot][e0];
+        b1 = s_key[wv][slot][e1];
+        const float kn = s_norm[wv][slot][col];
+        if (s.d < 64) {                              // uniform
+            if (!dim0) b0 = u32x4{0u, 0u, 0u, 0u};
+            if (!dim1) b1 = u32x4{0u, 0u, 0u, 0u};
         }
+        ks = cosine ? kn : 1.0f;
+        if (ragged && t == ntiles - 1 && r0 + 16 * (int64_t)t + col >= r1) ks = __builtin_nanf("");
+    };
+    // Scores of TN tiles (each its own sums, query tiles between the steps of
+    // one sum), into the maxima.
+    auto score = [&](auto tn, const u32x4 (&b)[2][2], const float (&ks)[2]) {
+        constexpr int TN = decltype(tn)::value;
+#pragma unroll
+        for (int q = 0; q < NT; ++q) {
+            f32x4 acc[TN];
+#pragma unroll
+            for (int u = 0; u < TN; ++u)
+                acc[u] = mfma<KT>(ahi[q][0], b[u][0], f32x4{0.0f, 0.0f, 0.0f, 0.0f});
+            if constexpr (SPLIT)
+#pragma unroll
+                for (int u = 0; u < TN; ++u) acc[u] = mfma<KT>(alo[q][0], b[u][0], acc[u]);
+#pragma unroll
+            for (int u = 0; u < TN; ++u) acc[u] = mfma<KT>(ahi[q][1], b[u][1], acc[u]);
+            if constexpr (SPLIT)
+#pragma unroll
+                for (int u = 0; u < TN; ++u) acc[u] = mfma<KT>(alo[q][1], b[u][1], acc[u]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if constexpr (TN == 2)
+                    m[q][i] = max3_f(m[q][i], acc[0][i] * ks[0], acc[1][i] * ks[1]);
+                else
+                    m[q][i] = max_f(m[q][i], acc[0][i] * ks[0]);
+            }
+        }
+    };
+    const int per_group = s.group_rows / 16;
+    int left = per_group;                            // tiles to the end of the group
+    for (int t = 0; t < ntiles;) {
+        u32x4 b[2][2];
+        float ks[2];
+        if (left >= 2 && t + 2 <= ntiles) {
+            wait_vmcnt<(kRing - 3) * kDmaOps>();       // tiles t and t + 1 are in LDS
+            take(t, b[0][0], b[0][1], ks[0]);
+            take(t + 1, b[1][0], b[1][1], ks[1]);
+            issue((t + kRing - 1) % kRing);          // the slot read last
+            score(std::integral_constant<int, 2>{}, b, ks);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // tile t was read
+            issue((t + kRing) % kRing);
+            t += 2;
+            left -= 2;
+        } else {
+            wait_vmcnt<(kRing - 2) * kDmaOps>();
+            take(t, b[0][0], b[0][1], ks[0]);
+            issue((t + kRing - 1) % kRing);
+            score(std::integral_constant<int, 1>{}, b, ks);
+            t += 1;
+            left -= 1;
+        }
+        if (left == 0 || t == ntiles) {
+            float v[16];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    v[4 * q + i] = q < NT ? m[q < NT ? q : 0][i] : 0.0f;
+                    if (q < NT) m[q < NT ? q : 0][i] = __builtin_nanf("");
+                }
+            swap_max<0x140, 16>(v, col & 8);         // row mirror
+            swap_max<0x141, 8>(v, col & 4);          // half-row mirror
+            swap_max<0x4E, 4>(v, col & 2);           // quad xor 2
+            swap_max<0xB1, 2>(v, col & 1);           // quad xor 1
+            if (out) *dst = v[0] * scale;
+            ++dst;
+            left = per_group;
+        }
+    }
+    wait_vmcnt<0>();
+}
+
+// The scores of the rows of each query's best groups: one wave per (query,
+// group), its tiles from the store in the operand layout, every row of A the
+// one query, so that lane (grp, col) has row col of each tile and stores that
+// of tile grp.  keys[q * count + j * group_rows + row], count = n_hits *
+// group_rows; 0 (a padding key) past the store and for a missing group.
+template <int KT, bool SPLIT>
+__global__ __launch_bounds__(kShortThreads) void score_groups_kernel(
+    ShortScan s, const int64_t* __restrict__ ids, int k, int n_hits,
+    uint64_t* __restrict__ out_keys) {
+    const int lane = threadIdx.x & 63, col = lane & 15, grp = lane >> 4;
+    const int q = blockIdx.y;
+    const int j = blockIdx.x * (kShortThreads / 64) +
+                  __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (j >= n_hits) return;                         // uniform over the wave
+    const int64_t id = ids[(int64_t)q * k + j];
+    const bool dim[2] = {8 * grp < s.d, 8 * grp + 32 < s.d};
+    u32x4 ahi[2], alo[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        const int64_t qoff = (int64_t)q * s.d + (dim[ks] ? 8 * grp + 32 * ks : 0);
+        ahi[ks] = *(const u32x4*)(s.qhi + qoff);
+        if constexpr (SPLIT) alo[ks] = *(const u32x4*)(s.qlo + qoff);
+        if (!dim[ks]) {
+            ahi[ks] = u32x4{0u, 0u, 0u, 0u};
+            if constexpr (SPLIT) alo[ks] = u32x4{0u, 0u, 0u, 0u};
+        }
+    }
+    const float qn = s.inv_qn[q];
+    const int64_t r0 = (id < 0 ? 0 : id) * s.group_rows;
+    u32x4 b[4][2];
+    float kn[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {                    // tiles past the group re-read rows
+        int64_t r = r0 + 16 * t + col;
+        r = r < s.n_rows ? r : s.n_rows - 1;
+        const uint16_t* row = (const uint16_t*)s.keys + r * s.ld;
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+            b[t][ks] = *(const u32x4*)(row + (dim[ks] ? 8 * grp + 32 * ks : 0));
+        kn[t] = s.inv_norm ? s.inv_norm[r] : 1.0f;
+    }
+    float mine = 0.0f;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+            if (!dim[ks]) b[t][ks] = u32x4{0u, 0u, 0u, 0u};
+        f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks) {
+            acc = mfma<KT>(ahi[ks], b[t][ks], acc);
+            if constexpr (SPLIT) acc = mfma<KT>(alo[ks], b[t][ks], acc);
+        }
+        const float v = (acc[0] * kn[t]) * qn;
+        mine = grp == t ? v : mine;
+    }
+    const int64_t r = r0 + lane;                     // row 16 grp + col
+    if (lane < s.group_rows)
+        out_keys[((int64_t)q * n_hits + j) * s.group_rows + lane] =
+            (id >= 0 && r < s.n_rows) ? pack_key(mine, (uint32_t)r) : 0ull;
+}
+
+// score_groups_kernel and the selections on either side of it in one block per
+// query: the n_hits best of at most 16384 group maxima, the scores of their
+// rows (at most kTailRows) straight into registers, and the top k of those with
+// its output.
+//
+// Bound: latency (one compute unit per query; loads, barriers and histogram
+// passes in turn), which is why more rows are scored by all compute units and
+// selected in launches of their own: whole search, 64 queries over 131072 x 64,
+// k = 100 (1600 rows) 48.4 us so and 55.0 in three launches; over 1M, k = 64
+// (4096 rows) 79.3 so and 75.7 in three.
+constexpr int kTailThreads = 1024;
+constexpr int kTailGroups = 16384;
+constexpr int kTailRows = 2048;
+
+template <int KT, bool SPLIT>
+__global__ __launch_bounds__(kTailThreads) void best_groups_kernel(
+    ShortScan s, int n_hits, int k, int64_t* __restrict__ out_ids,
+    float* __restrict__ out_scores, int32_t* __restrict__ out_drafts,
+    int32_t* __restrict__ out_draft_len, const int32_t* __restrict__ spans,
+    const int32_t* __restrict__ span_len, int max_span, int64_t span_stride) {
+    constexpr int W = kTailThreads / 64;
+    constexpr int GP = kTailGroups / kTailThreads, P = kTailRows / kTailThreads;
+    __shared__ uint64_t s_sel[kMaxK];
+    __shared__ uint64_t s_sorted[kMaxK];
+    __shared__ __align__(16) uint32_t s_hist[W * 256];        // read 16 bytes at a time
+    __shared__ uint32_t s_info[4];
+    __shared__ uint32_t s_nzw[W], s_wc[W];
+    __shared__ uint64_t s_andw[W], s_orw[W];
+    __shared__ uint32_t s_loww[W], s_highw[W];
+    const StatsLds lds{s_nzw, s_andw, s_orw, s_loww, s_highw};
+    const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, grp = lane >> 4;
+
+    // The query, every row of A (see score_groups_kernel).
+    const bool dim[2] = {8 * grp < s.d, 8 * grp + 32 < s.d};
+    u32x4 ahi[2], alo[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        const int64_t qoff = (int64_t)q * s.d + (dim[ks] ? 8 * grp + 32 * ks : 0);
+        ahi[ks] = *(const u32x4*)(s.qhi + qoff);
+        if constexpr (SPLIT) alo[ks] = *(const u32x4*)(s.qlo + qoff);
+    }
+    const float qn = s.inv_qn[q];
+
+    // The best groups, in any order.
+    {
+        const float* src = s.gmax + (int64_t)q * s.n_groups;
+        const int len = (int)s.n_groups;
+        float sv[GP];
+#pragma unroll
+        for (int e = 0; e < GP; ++e) {
+            const int i = tid + e * kTailThreads;
+            sv[e] = src[i < len ? i : len - 1];
+        }
+        uint32_t sw[GP];
+        uint64_t key[GP];
+#pragma unroll
+        for (int e = 0; e < GP; ++e) {
+            const int i = tid + e * kTailThreads;
+            sw[e] = score_key(sv[e]);
+            key[e] = i < len ? (((uint64_t)sw[e] << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)i))
+                             : 0ull;
+        }
+        const ChunkStats cs = score_stats<kTailThreads, GP>(sw, key, n_hits, 0, len, lds);
+        SelectState st{1ull, ~0ull};
+        if (cs.nz > (uint32_t)n_hits)
+            st = radix_select<kTailThreads, GP, true>(key, n_hits, cs, s_hist, s_info);
+        compact_taken<kTailThreads, GP>(key, st.mask, st.prefix, s_sel, n_hits, s_wc);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+        if (!dim[ks]) {
+            ahi[ks] = u32x4{0u, 0u, 0u, 0u};
+            if constexpr (SPLIT) alo[ks] = u32x4{0u, 0u, 0u, 0u};
+        }
+
+    // Their rows, four tiles of 16 per wave and key slot: lane (grp, col) keeps
+    // row col of tile grp.
+    const int per = s.group_rows / 16;               // tiles per group
+    const int tiles = n_hits * per;
+    uint64_t key[P];
+#pragma unroll
+    for (int e = 0; e < P; ++e) {
+        const int c0 = 4 * (wv + W * e);
+        u32x4 b[4][2];
+        float kn[4];
+        int64_t my_row = 0;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {                // tiles past the last re-read it
+            const int c = c0 + t < tiles ? c0 + t : tiles - 1;
+            const int hit = c / per;
+            const int64_t r = (int64_t)key_row(s_sel[hit]) * s.group_rows +
+                              16 * (c - hit * per) + col;
+            const int64_t rc = r < s.n_rows ? r : s.n_rows - 1;
+            const uint16_t* row = (const uint16_t*)s.keys + rc * s.ld;
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+                b[t][ks] = *(const u32x4*)(row + (dim[ks] ? 8 * grp + 32 * ks : 0));
+            kn[t] = s.inv_norm ? s.inv_norm[rc] : 1.0f;
+            my_row = grp == t ? r : my_row;
+        }
+        float mine = 0.0f;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+                if (!dim[ks]) b[t][ks] = u32x4{0u, 0u, 0u, 0u};
+            f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+                acc = mfma<KT>(ahi[ks], b[t][ks], acc);
+                if constexpr (SPLIT) acc = mfma<KT>(alo[ks], b[t][ks], acc);
+            }
+            const float v = (acc[0] * kn[t]) * qn;
+            mine = grp == t ? v : mine;
+        }
+        key[e] = (c0 + grp < tiles && my_row < s.n_rows) ? pack_key(mine, (uint32_t)my_row) : 0ull;
+    }
+    const ChunkStats cs = chunk_stats<kTailThreads, P, true>(key, k, lds);
+    SelectState st{1ull, ~0ull};
+    if (cs.nz > (uint32_t)k)
+        st = radix_select<kTailThreads, P, true>(key, k, cs, s_hist, s_info);
+    const uint32_t tot = compact_taken<kTailThreads, P>(key, st.mask, st.prefix, s_sel, k, s_wc);
+    const int nt = (int)tot < k ? (int)tot : k;
+    final_output<kTailThreads>(s_sel, s_sorted, nt, k, q, out_ids, out_scores, out_drafts,
+                               out_draft_len, spans, span_len, max_span, span_stride);
 }
 
 __global__ void short_tau_kernel(const int64_t* __restrict__ ids, const float* __restrict__ scores,
@@ -431,39 +628,66 @@ __global__ void short_tau_kernel(const int64_t* __restrict__ ids, const float* _
     counts[q] = slot_area;          // overflow entries follow the wave slots
 }
 
-template <int KT, int NT, int KS, bool SPLIT, bool FILTER>
-hipError_t launch_variant(const ShortScan& s, hipStream_t stream) {
-    auto kern = scan_short_kernel<KT, NT, KS, SPLIT, FILTER>;
-    const int64_t rpw = short_rows_per_wave(s.n_rows);
-    const int64_t waves = (s.n_rows + rpw - 1) / rpw;
-    const int64_t blocks = (waves + (kShortThreads / 64) - 1) / (kShortThreads / 64);
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kShortThreads), 0, stream, s, rpw);
-    return hipGetLastError();
+// Two resident waves per SIMD (scan_short_kernel's register use allows two).
+int64_t short_rows_per_wave(int64_t n_rows) {
+    const int64_t waves_max = (int64_t)device_cus() * 8;
+    int64_t rpw = (n_rows + waves_max - 1) / waves_max;
+    return (rpw + 16 * kShortDepth - 1) / (16 * kShortDepth) * (16 * kShortDepth);
+}
+
+unsigned blocks_of(int64_t waves) {
+    return (unsigned)((waves + (kShortThreads / 64) - 1) / (kShortThreads / 64));
 }
 
 template <int KT, int NT, int KS>
 hipError_t launch_mode(const ShortScan& s, hipStream_t stream) {
-    const bool filter = s.cand != nullptr;
-    if constexpr (KS == 2) {
-        // 64-dim keys, filtered: the LDS-staged pass (16-byte aligned rows).
-        if (filter && s.d == 64 && ((uintptr_t)s.keys % 16) == 0 && (s.row_step * s.ld) % 8 == 0) {
-            const int64_t rpw = short_rows_per_wave(s.n_rows);
-            const int64_t waves = (s.n_rows + rpw - 1) / rpw;
-            const int64_t blocks = (waves + (kShortThreads / 64) - 1) / (kShortThreads / 64);
-            if (s.split)
-                hipLaunchKernelGGL((scan_short_lds_kernel<KT, NT, true>), dim3((unsigned)blocks),
-                                   dim3(kShortThreads), 0, stream, s, rpw);
-            else
-                hipLaunchKernelGGL((scan_short_lds_kernel<KT, NT, false>), dim3((unsigned)blocks),
-                                   dim3(kShortThreads), 0, stream, s, rpw);
-            return hipGetLastError();
-        }
-    }
+    const int64_t rpw = short_rows_per_wave(s.n_rows);
+    const dim3 grid(blocks_of((s.n_rows + rpw - 1) / rpw));
     if (s.split)
-        return filter ? launch_variant<KT, NT, KS, true, true>(s, stream)
-                      : launch_variant<KT, NT, KS, true, false>(s, stream);
-    return filter ? launch_variant<KT, NT, KS, false, true>(s, stream)
-                  : launch_variant<KT, NT, KS, false, false>(s, stream);
+        hipLaunchKernelGGL((scan_short_kernel<KT, NT, KS, true>), grid, dim3(kShortThreads), 0,
+                           stream, s, rpw);
+    else
+        hipLaunchKernelGGL((scan_short_kernel<KT, NT, KS, false>), grid, dim3(kShortThreads), 0,
+                           stream, s, rpw);
+    return hipGetLastError();
+}
+
+template <int KT, int NT>
+hipError_t launch_groups(const ShortScan& s, hipStream_t stream) {
+    // One resident round (two waves per SIMD: the ring's LDS): a wave's start
+    // (query fragments, first tiles) costs as much as several groups.
+    const int64_t waves_max = (int64_t)device_cus() * 8;
+    const int64_t gpw = (s.n_groups + waves_max - 1) / waves_max;
+    const dim3 grid(blocks_of((s.n_groups + gpw - 1) / gpw));
+    if (s.split)
+        hipLaunchKernelGGL((scan_groups_kernel<KT, NT, true>), grid, dim3(kShortThreads), 0,
+                           stream, s, gpw);
+    else
+        hipLaunchKernelGGL((scan_groups_kernel<KT, NT, false>), grid, dim3(kShortThreads), 0,
+                           stream, s, gpw);
+    return hipGetLastError();
+}
+
+template <int KT>
+hipError_t launch_score_groups_t(const ShortScan& s, const int64_t* ids, int k, int n_hits,
+                                 uint64_t* keys, hipStream_t stream) {
+    const dim3 grid(blocks_of(n_hits), (unsigned)s.nq);
+    if (s.split)
+        hipLaunchKernelGGL((score_groups_kernel<KT, true>), grid, dim3(kShortThreads), 0, stream,
+                           s, ids, k, n_hits, keys);
+    else
+        hipLaunchKernelGGL((score_groups_kernel<KT, false>), grid, dim3(kShortThreads), 0, stream,
+                           s, ids, k, n_hits, keys);
+    return hipGetLastError();
+}
+
+template <int KT, bool SPLIT>
+hipError_t launch_best_groups_t(const ShortScan& s, int n_hits, const TopkOut& o,
+                                hipStream_t stream) {
+    hipLaunchKernelGGL((best_groups_kernel<KT, SPLIT>), dim3((unsigned)s.nq), dim3(kTailThreads),
+                       0, stream, s, n_hits, o.k, o.ids, o.scores, o.drafts, o.draft_len, o.spans, o.span_len, o.max_span,
+                       o.span_stride);
+    return hipGetLastError();
 }
 
 template <int KT, int KS>
@@ -478,23 +702,57 @@ hipError_t launch_tiles(const ShortScan& s, hipStream_t stream) {
 
 }  // namespace
 
-int64_t short_rows_per_wave(int64_t n_rows) {
-    // Two resident waves per SIMD (the kernels' register use allows two).
-    const int64_t waves_max = (int64_t)device_cus() * 8;
-    int64_t rpw = (n_rows + waves_max - 1) / waves_max;
-    return (rpw + 16 * kShortDepth - 1) / (16 * kShortDepth) * (16 * kShortDepth);
-}
-
-int64_t short_scan_waves(int64_t n_rows) {
-    const int64_t rpw = short_rows_per_wave(n_rows);
-    return (n_rows + rpw - 1) / rpw;
-}
-
 hipError_t launch_scan_short(const ShortScan& s, hipStream_t stream) {
     const bool two = s.d > 32;
     if (s.key_dtype == DT_BF16)
         return two ? launch_tiles<DT_BF16, 2>(s, stream) : launch_tiles<DT_BF16, 1>(s, stream);
     return two ? launch_tiles<DT_F16, 2>(s, stream) : launch_tiles<DT_F16, 1>(s, stream);
+}
+
+template <int KT>
+static hipError_t launch_groups_t(const ShortScan& s, hipStream_t stream) {
+    switch ((s.nq + 15) / 16) {
+        case 1: return launch_groups<KT, 1>(s, stream);
+        case 2: return launch_groups<KT, 2>(s, stream);
+        case 3: return launch_groups<KT, 3>(s, stream);
+        default: return launch_groups<KT, 4>(s, stream);
+    }
+}
+
+// Rows per group: at most 16384 groups (one block's selection) up to a million
+// rows; groups of 64 beyond (one wave's rescore).
+int short_group_rows(int64_t n_rows) {
+    const int64_t g = 16 * ((n_rows + 16 * 16384 - 1) / (16 * 16384));
+    return (int)(g < kMaxGroupRows ? g : kMaxGroupRows);
+}
+
+int64_t short_list_slots(int64_t n_rows) {
+    const int64_t rpw = short_rows_per_wave(n_rows);
+    return (n_rows + rpw - 1) / rpw * 4;
+}
+
+hipError_t launch_scan_groups(const ShortScan& s, hipStream_t stream) {
+    return s.key_dtype == DT_BF16 ? launch_groups_t<DT_BF16>(s, stream)
+                                  : launch_groups_t<DT_F16>(s, stream);
+}
+
+bool best_groups_fit(const ShortScan& s, int n_hits) {
+    return s.n_groups <= kTailGroups && n_hits * s.group_rows <= kTailRows;
+}
+
+hipError_t launch_best_groups(const ShortScan& s, int n_hits, const TopkOut& o,
+                              hipStream_t stream) {
+    if (s.key_dtype == DT_BF16)
+        return s.split ? launch_best_groups_t<DT_BF16, true>(s, n_hits, o, stream)
+                       : launch_best_groups_t<DT_BF16, false>(s, n_hits, o, stream);
+    return s.split ? launch_best_groups_t<DT_F16, true>(s, n_hits, o, stream)
+                   : launch_best_groups_t<DT_F16, false>(s, n_hits, o, stream);
+}
+
+hipError_t launch_score_groups(const ShortScan& s, const int64_t* ids, int k, int n_hits,
+                               uint64_t* keys, hipStream_t stream) {
+    return s.key_dtype == DT_BF16 ? launch_score_groups_t<DT_BF16>(s, ids, k, n_hits, keys, stream)
+                                  : launch_score_groups_t<DT_F16>(s, ids, k, n_hits, keys, stream);
 }
 
 hipError_t launch_short_tau(const int64_t* ids, const float* scores, int nq, int k,

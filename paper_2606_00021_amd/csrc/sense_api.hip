@@ -93,10 +93,13 @@ struct RetrieveLayout {
     size_t q_off, m_off, s_off, t_off, total;
 };
 
-// Batched queries over short keys: the matrix-core short-key scan, with a
-// sampled threshold and a filtered pass when the store is large.
-constexpr int64_t kShortSample = 32768;      // rows of the threshold sample
-constexpr int64_t kShortDirectMax = 131072;  // up to this many rows: plain scores + top-k
+// Batched queries over short keys: the matrix-core short-key scan, by groups of
+// rows when the store is large.
+// Up to this many rows: plain scores + top-k, with two launches fewer (64
+// queries x 64 dims: 32768 rows 37.6 us so and 42.3 by groups, 65539 rows 48.6
+// and 44.5).
+constexpr int64_t kShortDirectMax = 32768;
+constexpr int64_t kShortSample = 32768;     // scores per query of the sample area
 
 bool short_batched(const sense_index* ix, int nq) {
     return ix->d <= sense::kSmallDim && nq >= sense::kMfmaMinQueries;
@@ -146,7 +149,7 @@ ShortLayout short_layout(const sense_index* ix, int nq, int k) {
     // candidates per query: the wave slots, then an overflow list of up to
     // every row; also the plain score matrix of small stores
     const int64_t cap = long_keys ? sense::mfma_scan_waves(rows) * sense::kMfmaSlots + rows
-                                  : sense::short_scan_waves(rows) * sense::kShortSlots + rows;
+                                  : sense::short_list_slots(rows) + rows;
     l.cap = cap;
     l.cand_off = take((size_t)g * cap * sizeof(uint64_t));
     l.fws_off = take(sense::topk_workspace_bytes(cap, g, k));
@@ -438,9 +441,9 @@ SENSE_EXPORT sense_status_t sense_retrieve_workspace_size(const sense_index_t* i
     return ok();
 }
 
-// Short keys, query batch: per group of <= 64 queries either plain scores +
-// top-k (small stores) or a strided sample's k-th best key as a threshold,
-// a filtered pass over every row, and the top-k of the survivors.
+// Short keys, query batch: per 64 queries either plain scores + top-k (small
+// stores), or the best score of every group of rows, the k best groups, the
+// scores of their rows and the top k of those.
 static hipError_t retrieve_short(const sense_index* ix, const float* qptr, int nq, int k,
                                  bool split, int64_t* out_ids, float* out_scores,
                                  int32_t* out_drafts, int32_t* out_draft_len, char* ws,
@@ -453,8 +456,16 @@ static hipError_t retrieve_short(const sense_index* ix, const float* qptr, int n
                                        nullptr, ws + L.m_off, st)) != hipSuccess)
         return e;
     const sense::QuerySplit qs = sense::query_split_parts(ws + L.m_off, nq, ix->d);
-    const bool sample = n > kShortDirectMax;
-    const int64_t step = sample ? n / kShortSample : 1;
+    const bool direct = n <= kShortDirectMax;
+    const int group_rows = sense::short_group_rows(n);
+    const int64_t n_groups = (n + group_rows - 1) / group_rows;
+    const int n_hits = (int)(k < n_groups ? k : n_groups);
+    // The candidate area (per query at least n entries of 8 bytes) holds the
+    // group maxima, then the keys of the hit groups' rows: for n > 32768 and
+    // k <= 1024 less than n / 2 + 8 K bytes and 8 n_hits * group_rows.
+    float* gmax = (float*)(ws + L.cand_off);
+    uint64_t* cand = (uint64_t*)(ws + L.cand_off +
+                                 round_up((size_t)(nq < 64 ? nq : 64) * n_groups * 4, 256));
     for (int g0 = 0; g0 < nq; g0 += 64) {
         const int ng = nq - g0 < 64 ? nq - g0 : 64;
         sense::ShortScan S{};
@@ -468,13 +479,12 @@ static hipError_t retrieve_short(const sense_index* ix, const float* qptr, int n
         S.nq = ng;
         S.split = split;
         S.inv_norm = ix->inv_norm;
+        S.n_rows = n;
         int64_t* gid = out_ids + (int64_t)g0 * k;
         float* gsc = out_scores ? out_scores + (int64_t)g0 * k : nullptr;
         int32_t* gdr = out_drafts ? out_drafts + (int64_t)g0 * k * ix->max_span : nullptr;
         int32_t* gdl = out_draft_len ? out_draft_len + (int64_t)g0 * k : nullptr;
-        if (!sample) {
-            S.n_rows = n;
-            S.row_step = 1;
+        if (direct) {
             S.scores = (float*)(ws + L.cand_off);
             if ((e = sense::launch_scan_short(S, st)) != hipSuccess) return e;
             if ((e = sense::launch_topk_gather(S.scores, n, ng, k, ix->spans, ix->span_len,
@@ -483,35 +493,26 @@ static hipError_t retrieve_short(const sense_index* ix, const float* qptr, int n
                 return e;
             continue;
         }
-        // Threshold from the sample rows 0, step, 2 step, ...
-        S.n_rows = kShortSample;
-        S.row_step = step;
-        S.scores = (float*)(ws + L.ss_off);
-        if ((e = sense::launch_scan_short(S, st)) != hipSuccess) return e;
-        int64_t* sid = (int64_t*)(ws + L.sid_off);
-        float* ssc = (float*)(ws + L.ssc_off);
-        if ((e = sense::launch_topk_gather(S.scores, kShortSample, ng, k, nullptr, nullptr, 1, 1,
-                                           sid, ssc, nullptr, nullptr, ws + L.sws_off, st)) !=
-            hipSuccess)
+        S.group_rows = group_rows;
+        S.n_groups = n_groups;
+        S.gmax = gmax;
+        if ((e = sense::launch_scan_groups(S, st)) != hipSuccess) return e;
+        if (sense::best_groups_fit(S, n_hits)) {
+            const sense::TopkOut O{k, gid, gsc, gdr, gdl, ix->spans, ix->span_len, ix->max_span,
+                                   ix->span_stride};
+            if ((e = sense::launch_best_groups(S, n_hits, O, st)) != hipSuccess) return e;
+            continue;
+        }
+        int64_t* hit = (int64_t*)(ws + L.sid_off);
+        if ((e = sense::launch_topk_gather(gmax, n_groups, ng, n_hits, nullptr, nullptr, 1, 1,
+                                           hit, nullptr, nullptr, nullptr, ws + L.fws_off,
+                                           st)) != hipSuccess)
             return e;
-        uint64_t* tau = (uint64_t*)(ws + L.tau_off);
-        int32_t* cnt = (int32_t*)(ws + L.cnt_off);
-        const int64_t slot_area = sense::short_scan_waves(n) * sense::kShortSlots;
-        if ((e = sense::launch_short_tau(sid, ssc, ng, k, step, (int32_t)slot_area, nullptr,
-                                         tau, cnt, st)) != hipSuccess)
+        if ((e = sense::launch_score_groups(S, hit, n_hits, n_hits, cand, st)) != hipSuccess)
             return e;
-        // Every row; only keys >= tau are kept.
-        S.n_rows = n;
-        S.row_step = 1;
-        S.scores = nullptr;
-        S.tau = tau;
-        S.counts = cnt;
-        S.cand = (uint64_t*)(ws + L.cand_off);
-        S.cap = slot_area + n;
-        if ((e = sense::launch_scan_short(S, st)) != hipSuccess) return e;
-        if ((e = sense::launch_topk_keys(S.cand, S.cap, ng, k, ix->spans, ix->span_len,
-                                         ix->max_span, ix->span_stride, gid, gsc, gdr, gdl, cnt,
-                                         st)) != hipSuccess)
+        if ((e = sense::launch_topk_keys(cand, (int64_t)n_hits * group_rows, ng, k, ix->spans,
+                                         ix->span_len, ix->max_span, ix->span_stride, gid, gsc,
+                                         gdr, gdl, nullptr, st)) != hipSuccess)
             return e;
     }
     return timer_mark(SENSE_TIMER_SCAN, 1, st);

@@ -551,3 +551,38 @@ def test_full_size_batched(name, full_queries):
     index.close()
     del ds, index
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f16"])
+@pytest.mark.parametrize("n,d,nq,k", [
+    (32_769, 64, 2, 1),           # just past the plain scan: one row in the last group
+    (40_007, 8, 17, 64),          # two query tiles, ragged last tile
+    (50_001, 40, 64, 128),        # 2048 rows of hit groups: the single-launch tail's most
+    (50_001, 56, 49, 129),        # one group more: separate launches
+    (262_145, 64, 33, 100),       # groups of 32 rows, the last of one row
+    (300_007, 24, 5, 1024),
+    (140_009, 64, 70, 16),        # two query groups
+    (1_048_577, 16, 16, 40),      # groups of 64 rows; more than one block's of them
+])
+def test_short_groups_are_exact_with_ties(n, d, nq, k, dt):
+    """The best groups of rows hold the best rows.  Small whole numbers, so that
+    every score is exact and many tie (the lower row first), and NaN rows, which
+    come last."""
+    g = torch.Generator().manual_seed(n + d)
+    keys = torch.randint(-3, 4, (n, d), generator=g).float()
+    keys[torch.randint(0, n, (n // 50,), generator=g)] = float("nan")
+    keys[n - 1] = 2.0                                # a real row at the very end
+    q = torch.randint(-2, 3, (nq, d), generator=g).float()
+    q[0] = 1.0                                       # its best row may be that one
+    tdt = {"bf16": torch.bfloat16, "f16": torch.float16}[dt]
+    spans = torch.arange(2 * n, dtype=torch.int32).view(n, 2)
+    index = sense.sense_build_index(keys.to(tdt).to(DEV), spans.to(DEV), None, metric="ip")
+    ids, scores, drafts, _ = sense.sense_retrieve(index, q.to(DEV), k)
+    torch.cuda.synchronize()
+    want = (q.double() @ keys.double().T).nan_to_num(nan=-1e9)
+    for i in range(nq):
+        order = torch.from_numpy(np.lexsort((np.arange(n), -want[i].numpy()))[:k].copy())
+        assert torch.equal(ids[i].cpu(), order), f"query {i}"
+        assert torch.equal(scores[i].cpu().double(), want[i][order])
+        assert torch.equal(drafts[i].cpu(), spans[order])
+    index.close()
