@@ -110,20 +110,18 @@ hipError_t launch_key_norms(const void* keys, int key_dtype, int64_t n, int d, i
 // single query runs the GEMV, whose fp32 query needs no hi/lo split.
 constexpr int kMfmaMinQueries = 2;
 
-// scores[q * n + i] = similarity of query q and row i for q in [0, nq).
-// queries: nq x d fp32 (already converted).  inv_norm NULL for IP.  split:
-// the queries are not exactly representable in the key type (MFMA path
-// multiplies a hi and a lo half).  scratch: scan_scratch_bytes(nq, d) bytes.
+// scores[q * n + i] = similarity of query q and row i for q in [0, nq), a GEMV
+// each.  queries: nq x d fp32 (already converted).  inv_norm NULL for IP.
 hipError_t launch_scan(const void* keys, int key_dtype, int64_t n, int d, int64_t ld,
-                       const float* queries, int nq, bool split, const float* inv_norm,
-                       float* scores, void* scratch, hipStream_t stream);
+                       const float* queries, int nq, const float* inv_norm, float* scores,
+                       hipStream_t stream);
 size_t scan_mfma_scratch_bytes(int nq, int d);
 // One query group (<= 64 queries, already split) of the batched scan over
 // rows 0, row_step, 2 row_step, ... (n_rows of them) of a store of row
 // stride ld.  WRITE mode (scores != NULL): scores[q * n_rows + i].  FILTER
 // mode (cand != NULL): rows whose score reaches the score of tau[q] go to
-// query q's candidate list cand + q * cap as packed (score, row) keys: slots
-// [w * kMfmaSlots, (w + 1) * kMfmaSlots) of wave w (the rest padding keys),
+// query q's candidate list cand + q * cap as packed (score, row) keys: the slots
+// of each workgroup's waves, 4 * kMfmaSlots (the rest padding keys),
 // then an overflow list whose next position is counts[q] (to be initialised
 // to the slot area, mfma_scan_waves(n_rows) * kMfmaSlots).
 struct MfmaScan {
@@ -153,8 +151,23 @@ struct MfmaScan {
 constexpr int kMfmaSlots = 32;
 hipError_t launch_scan_mfma_rows(const MfmaScan& s, bool split, hipStream_t stream);
 int64_t mfma_scan_waves(int64_t n_rows);
-hipError_t launch_scan_mfma(const void* keys, int key_dtype, int64_t n, int d, int64_t ld,
-                            const float* queries, int nq, bool split, const float* inv_norm,
+// A query batch to be split: nq x d values of dtype (fp32 or either 16-bit type).
+// f32 (may be NULL) receives them in fp32; with mean (may be NULL) centre[q] =
+// mean . query q.
+struct QueryBatch {
+    const void* q;
+    int dtype;
+    int nq;
+    int d;
+    float* f32;
+    const float* mean;
+    float* centre;
+};
+// The same for a batch on the matrix cores; split: the queries are not exactly
+// representable in the key type (a hi and a lo half are multiplied).  scratch:
+// scan_mfma_scratch_bytes(nq, d) bytes.
+hipError_t launch_scan_mfma(const void* keys, int key_dtype, int64_t n, int64_t ld,
+                            const QueryBatch& b, bool split, const float* inv_norm,
                             float* scores, void* scratch, hipStream_t stream);
 
 // Single-query scans of keys with d <= kSmallDim (several rows per load
@@ -170,8 +183,8 @@ size_t project_workspace_bytes(int x_dtype, int64_t n, int d_in, int d_out);
 // matrix cores: centring, normalisation and the store in the epilogue.
 constexpr int kMfmaProjOut = 64;
 hipError_t launch_project_mfma(const void* x, int x_dtype, int64_t n, int d_in, int64_t x_stride,
-                               const float* basis, int d_out, const float* centre, int normalize,
-                               void* out, int out_dtype, int64_t out_stride, void* scratch,
+                               const float* basis, int d_out, const float* mean, float* centre,
+                               int normalize, void* out, int out_dtype, int64_t out_stride, void* scratch,
                                hipStream_t stream);
 hipError_t launch_project(const void* x, int x_dtype, int64_t n, int d_in, int64_t x_stride,
                           const float* mean, const float* basis, int d_out, int normalize,
@@ -269,7 +282,7 @@ struct QuerySplit {
 QuerySplit query_split_parts(void* scratch, int nq, int d);
 // key_norm_max (inner product, may be NULL): the store's largest key norm,
 // which scales the inner-product margin.
-hipError_t launch_query_split(const float* queries, int nq, int d, int key_dtype, bool cosine,
+hipError_t launch_query_split(const QueryBatch& b, int key_dtype, bool cosine,
                               const float* key_norm_max, void* scratch, hipStream_t stream);
 
 // Batched scan of short keys (d <= kSmallDim) on the matrix cores, for at

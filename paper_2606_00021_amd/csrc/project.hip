@@ -36,19 +36,6 @@ __device__ __forceinline__ void store_out(void* p, int dt, int64_t i, float v) {
     else ((uint16_t*)p)[i] = to_bits16(v, dt);
 }
 
-// centre[o] = mean . basis[o]  (one wave per output).
-__global__ __launch_bounds__(kProjThreads) void project_center_kernel(
-    const float* __restrict__ mean, const float* __restrict__ basis, int d_in, int d_out,
-    float* __restrict__ centre) {
-    const int lane = threadIdx.x & 63;
-    const int o = blockIdx.x * (kProjThreads / 64) + (threadIdx.x >> 6);
-    if (o >= d_out) return;
-    float a = 0.0f;
-    for (int t = lane; t < d_in; t += 64) a = __builtin_fmaf(mean[t], basis[(int64_t)o * d_in + t], a);
-    a = wsum(a);
-    if (lane == 0) centre[o] = a;
-}
-
 // Rows [i0, i0 + kFinRows) of S (d_out x n): subtract the centre, normalise,
 // store row-major in the output type.
 constexpr int kFinRows = 32;
@@ -275,18 +262,13 @@ hipError_t launch_project(const void* x, int x_dtype, int64_t n, int d_in, int64
                            normalize, out, out_dtype, out_stride);
         return hipGetLastError();
     }
-    if (mean) {
-        hipLaunchKernelGGL(project_center_kernel,
-                           dim3((unsigned)((d_out + kProjThreads / 64 - 1) / (kProjThreads / 64))),
-                           dim3(kProjThreads), 0, stream, mean, basis, d_in, d_out, centre);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
     if (project_fused(d_out))
-        return launch_project_mfma(x, x_dtype, n, d_in, x_stride, basis, d_out, centre, normalize,
-                                   out, out_dtype, out_stride, ws + c_bytes, stream);
+        return launch_project_mfma(x, x_dtype, n, d_in, x_stride, basis, d_out, mean, centre,
+                                   normalize, out, out_dtype, out_stride, ws + c_bytes, stream);
     void* scratch = ws + c_bytes + up256((size_t)d_out * n * sizeof(float));
-    if ((e = launch_scan_mfma(x, x_dtype, n, d_in, x_stride, basis, d_out, true, nullptr, s,
-                              scratch, stream)) != hipSuccess)
+    const QueryBatch b{basis, DT_F32, d_out, d_in, nullptr, mean, centre};
+    if ((e = launch_scan_mfma(x, x_dtype, n, x_stride, b, true, nullptr, s, scratch, stream)) !=
+        hipSuccess)
         return e;
     hipLaunchKernelGGL(project_finish_kernel, dim3((unsigned)((n + kFinRows - 1) / kFinRows)),
                        dim3(kProjThreads), 0, stream, s, n, d_out, centre, normalize, out,

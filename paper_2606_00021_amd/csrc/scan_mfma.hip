@@ -78,38 +78,74 @@ __device__ __forceinline__ float from_key_bits(uint16_t b) {
 // evaluation is good to ~d * 2^-24).  An overflowing split (an f16 hi half
 // of |x| > 65504) or an infinite key gives an infinite or NaN margin: every
 // row then passes.  One block (256 threads) per padded query row.
-template <int KT>
-__global__ __launch_bounds__(256) void query_split_kernel(const float* __restrict__ q, int nq,
-                                                          int d, bool cosine,
-                                                          uint16_t* __restrict__ qhi,
-                                                          uint16_t* __restrict__ qlo,
-                                                          float* __restrict__ inv_qn,
-                                                          const float* __restrict__ key_norm_max,
-                                                          float* __restrict__ margin) {
-    const int row = blockIdx.x;
-    float ss = 0.0f, ll = 0.0f;
-    for (int t = threadIdx.x; t < d; t += 256) {
-        const float x = row < nq ? q[(int64_t)row * d + t] : 0.0f;
-        const uint16_t hb = to_key_bits<KT>(x);
-        const float lo = x - from_key_bits<KT>(hb);
-        qhi[(int64_t)row * d + t] = hb;
-        qlo[(int64_t)row * d + t] = to_key_bits<KT>(lo);
-        ss = __builtin_fmaf(x, x, ss);
-        ll = __builtin_fmaf(lo, lo, ll);
-    }
-    __shared__ float s_part[2][256];
-    s_part[0][threadIdx.x] = ss;
-    s_part[1][threadIdx.x] = ll;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) {
-            s_part[0][threadIdx.x] += s_part[0][threadIdx.x + off];
-            s_part[1][threadIdx.x] += s_part[1][threadIdx.x + off];
+//
+// The queries come in fp32 or either 16-bit type (QT); with f32 they are also
+// stored in fp32, and with mean (a projection's basis as the queries)
+// centre[row] = mean . row.
+// Bound: latency; a thread's loads of up to 4096 dims go out together (64 rows
+// of 8192 fp32 14.3 -> 7.0 us, of 4096 with the mean 30 in two launches -> 6.7).
+template <int KT, int QT>
+__global__ __launch_bounds__(256) void query_split_kernel(
+    const void* __restrict__ q, int nq, int d, bool cosine, uint16_t* __restrict__ qhi,
+    uint16_t* __restrict__ qlo, float* __restrict__ inv_qn,
+    const float* __restrict__ key_norm_max, float* __restrict__ margin, float* __restrict__ f32,
+    const float* __restrict__ mean, float* __restrict__ centre) {
+    constexpr int U = 4;
+    const int row = blockIdx.x, tid = threadIdx.x;
+    const int64_t src = (int64_t)(row < nq ? row : 0) * d;
+    float part[3] = {0.0f, 0.0f, 0.0f};           // x x, lo lo, mean x
+    for (int t0 = 0; t0 < d; t0 += 1024 * U) {
+        float v[U][4], mv[U][4];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int t = t0 + 1024 * u + 4 * tid;
+            const int tc = t < d ? t : 0;
+            if constexpr (QT != DT_F32) {
+                u32x2 w;                              // rows at any element
+                __builtin_memcpy(&w, (const uint16_t*)q + src + tc, 8);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    v[u][i] = from_key_bits<QT>((uint16_t)(w[i / 2] >> (16 * (i & 1))));
+            } else {
+                __builtin_memcpy(v[u], (const float*)q + src + tc, 16);
+            }
+            if (mean) __builtin_memcpy(mv[u], mean + tc, 16);
         }
-        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int t = t0 + 1024 * u + 4 * tid;
+            if (t >= d) continue;
+            uint32_t hb[4], lb[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float x = row < nq ? v[u][i] : 0.0f;
+                hb[i] = to_key_bits<KT>(x);
+                const float lo = x - from_key_bits<KT>((uint16_t)hb[i]);
+                lb[i] = to_key_bits<KT>(lo);
+                part[0] = __builtin_fmaf(x, x, part[0]);
+                part[1] = __builtin_fmaf(lo, lo, part[1]);
+                if (mean) part[2] = __builtin_fmaf(mv[u][i], x, part[2]);
+            }
+            const int64_t at = (int64_t)row * d + t;
+            *(u32x2*)(qhi + at) = u32x2{hb[0] | (hb[1] << 16), hb[2] | (hb[3] << 16)};
+            *(u32x2*)(qlo + at) = u32x2{lb[0] | (lb[1] << 16), lb[2] | (lb[3] << 16)};
+            if (f32 && row < nq) *(f32x4*)(f32 + at) = f32x4{v[u][0], v[u][1], v[u][2], v[u][3]};
+        }
     }
-    if (threadIdx.x == 0) {
-        const float s = s_part[0][0];
+    __shared__ float s_part[3][4];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) part[i] += __shfl_xor(part[i], off, 64);
+        if ((tid & 63) == 0) s_part[i][tid >> 6] = part[i];
+    }
+    __syncthreads();
+    if (tid == 0) {
+        auto total = [&](int i) {
+            return (s_part[i][0] + s_part[i][1]) + (s_part[i][2] + s_part[i][3]);
+        };
+        if (mean && row < nq) centre[row] = total(2);
+        const float s = total(0);
         float v = 1.0f;
         if (row >= nq) v = 0.0f;
         else if (cosine) v = (s > 0.0f) ? 1.0f / __builtin_sqrtf(s) : 0.0f;
@@ -119,7 +155,7 @@ __global__ __launch_bounds__(256) void query_split_kernel(const float* __restric
         const float depth = (float)((d + 31) / 32 + 8) + (float)(d / 128 + 8) +
                             2.0f * (float)(d / 64 + 16) + 4.0f;
         const float rnd = depth * 5.9604645e-8f;              // x 2^-24
-        const float lon = __builtin_sqrtf(s_part[1][0]);       // ||q - hi||
+        const float lon = __builtin_sqrtf(total(1));           // ||q - hi||
         float m = 0.0f;
         if (row < nq && cosine)
             m = 2.0f * (1.01f * lon * v + 2.0f * 1.01f * rnd);
@@ -148,17 +184,19 @@ __global__ __launch_bounds__(256) void query_split_kernel(const float* __restric
 constexpr int kTileVec = 128;                 // 16-byte entries per key tile
 constexpr int kTileSecond = 64;               // first entry of rows 8-15
 
-// One workgroup (4 waves) per contiguous run of key blocks; a block is 4*T
-// tiles of 16 keys, T tiles per wave; MT tiles of 16 queries (nq <= 16*MT of
-// them are real).  The scanned rows are rows 0, row_step, 2 row_step, ... of
-// the store (a strided sample when row_step > 1).
+// One workgroup (8 waves) per contiguous run of rows_per_group rows, taken in
+// blocks of 8*T tiles of 16 keys, T tiles per wave (the last block may be part
+// full); MT tiles of 16 queries (nq <= 16*MT of them are real).  The scanned
+// rows are rows 0, row_step, 2 row_step, ... of the store (a strided sample when
+// row_step > 1).
 //
 // Everything the matrix cores read goes through LDS, filled by
 // global_load_lds_dwordx4 (HBM/L2 -> LDS without registers) into a ring of P
 // stages; a stage is two 32-dimension steps: each wave's T key tiles (private
 // to the wave, laid out as above) and the 2*MT*(1+SPLIT) query fragments of
-// the two steps, shared by the four waves (each wave loads its share).
-// Loading stays P-1 stages ahead of the matrix cores.  Every stage a wave
+// the two steps, shared by the waves (each wave loads its share).
+// Loading stays P-1 stages ahead of the matrix cores, also from one block of
+// rows into the next.  Every stage a wave
 // issues the same number of loads (stages past the end reload a valid
 // clamped address), so the wait for a stage is a fixed vmcnt; a workgroup
 // barrier then makes the other waves' query fragments visible and frees the
@@ -182,17 +220,33 @@ constexpr int kTileSecond = 64;               // first entry of rows 8-15
 // that cut the scan's read rate by a fifth; the survivors are ~k*row_step.
 constexpr int kModeWrite = 0, kModeFilter = 1, kModeProject = 2;
 
+//
+// Bound: the read of the keys (128 bytes of a row at a time), shared with the
+// LDS and the matrix cores between two barriers.  Two waves per SIMD, so that
+// one's products run beside the other's LDS reads: against four waves of twice
+// the tiles, 262144 x 4096 bf16 onto 64 outputs (split basis) 440 -> 425 us
+// (400 for the key loads alone), 64 queries over 100003 x 3584 227 -> 196 us a
+// search, 64 over 1M x 8192 2800 -> 2778.  Tried and no faster: refilling a
+// wave's own key slots before its products (2672 against 2546 us), 256 bytes of
+// each row per stage in two slots (2579; 142 against 125 us for 13 queries over
+// 100003 x 3584).
+constexpr int kWaves = 8;
+constexpr int kThreads = 64 * kWaves;
+// A workgroup's slots of a candidate list, 4 * kMfmaSlots, dealt to its waves.
+constexpr int kWaveSlots = 4 * kMfmaSlots / kWaves;
+static_assert(kWaveSlots * kWaves == 4 * kMfmaSlots, "slots per wave");
+
 template <int KT, int MT, int T, int P, bool SPLIT, int MODE>
-__global__ __launch_bounds__(256) void scan_mfma_kernel(MfmaScan s, int64_t blocks_per_group) {
+__global__ __launch_bounds__(kThreads) void scan_mfma_kernel(MfmaScan s, int64_t rows_per_group) {
     constexpr bool FILTER = MODE == kModeFilter;
     constexpr int NA = MT * (SPLIT ? 2 : 1);      // query fragments per step
     constexpr int NAS = 2 * NA;                   // per stage
-    constexpr int NA_W = (NAS + 3) / 4;           // loaded per wave
+    constexpr int NA_W = (NAS + kWaves - 1) / kWaves;   // loaded per wave
     constexpr int OPS = 2 * T + NA_W;             // DMA loads per wave per stage
-    constexpr int KB = 64 * T;                    // keys per workgroup block
+    constexpr int KB = 16 * kWaves * T;           // keys per workgroup block
     static_assert((P - 2) * OPS < 64, "vmcnt range");
-    __shared__ __attribute__((aligned(16))) u32x4 kring[P][4][T][kTileVec];
-    __shared__ __attribute__((aligned(16))) u32x4 aring[P][NA_W * 4][64];
+    __shared__ __attribute__((aligned(16))) u32x4 kring[P][kWaves][T][kTileVec];
+    __shared__ __attribute__((aligned(16))) u32x4 aring[P][NAS][64];
     const uint16_t* __restrict__ keys = (const uint16_t*)s.keys;
     const int d = s.d;
     const int64_t n = s.n_rows;
@@ -202,21 +256,22 @@ __global__ __launch_bounds__(256) void scan_mfma_kernel(MfmaScan s, int64_t bloc
     const int col = lane & 15, grp = lane >> 4;
     const int dp = lane >> 3;                     // DMA: row within the instruction
     const int du = ((lane & 7) + dp) & 7;         // DMA: 16-byte unit fetched
-    const int64_t nblk = (n + KB - 1) / KB;
-    const int64_t b0 = (int64_t)blockIdx.x * blocks_per_group;
-    const int64_t b1 = (b0 + blocks_per_group < nblk) ? b0 + blocks_per_group : nblk;
+    const int64_t r0 = (int64_t)blockIdx.x * rows_per_group;
+    const int64_t r1 = (r0 + rows_per_group < n) ? r0 + rows_per_group : n;
+    const int nblk = (int)((r1 - r0 + KB - 1) / KB);
     const int nks = (d + 31) / 32;
     const int nst = (nks + 1) / 2;
     const bool ragged = (d & 31) != 0;
 
-    // This wave's share of the query fragments: fs = wv + 4*j in [0, NAS),
+    // This wave's share of the query fragments: fs = wv + kWaves*j in [0, NAS),
     // step-in-stage fs / NA, fragment fs % NA (< MT: hi tile, else lo tile).
     const uint16_t* qsrc[NA_W];
-    int qstep[NA_W];
+    int qstep[NA_W], qslot[NA_W];
 #pragma unroll
     for (int j = 0; j < NA_W; ++j) {
-        int fs = wv + 4 * j;
-        if (fs >= NAS) fs = NAS - 1;              // idle slot: harmless duplicate
+        int fs = wv + kWaves * j;
+        if (fs >= NAS) fs = NAS - 1;              // no share: the last one's again, same bytes
+        qslot[j] = __builtin_amdgcn_readfirstlane(fs);
         const int f = fs % NA;
         const uint16_t* base = (f < MT) ? s.qhi : s.qlo;
         const int mt = f % MT;
@@ -245,56 +300,65 @@ __global__ __launch_bounds__(256) void scan_mfma_kernel(MfmaScan s, int64_t bloc
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int i = 0; i < 4; ++i) cnt[mt][i] = 0;
-    const int64_t wave_slot = ((int64_t)blockIdx.x * 4 + wv) * kMfmaSlots;
+    const int64_t wave_slot = ((int64_t)blockIdx.x * kWaves + wv) * kWaveSlots;
     // B-operand entry of this lane inside a key tile, for unit u = 4*step + grp.
     const int ri = col >> 3, rp = col & 7;
     auto bentry = [&](int step) { return ri * kTileSecond + 8 * rp + (((4 * step + grp) - rp) & 7); };
 
-    for (int64_t blk = b0; blk < b1; ++blk) {
-        const int64_t key0 = blk * KB + (int64_t)wv * 16 * T;
-        const uint16_t* kp[T][2];
-        bool kv[T];
-#pragma unroll
-        for (int t = 0; t < T; ++t) {
-            kv[t] = key0 + t * 16 + col < n;
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                int64_t row = key0 + t * 16 + 8 * i + dp;
-                if (row >= n) row = n - 1;
-                kp[t][i] = keys + row * rstride + du * 8;
-            }
-        }
-        auto issue = [&](int st) {
-            const int sc = st < nst ? st : nst - 1;
-            const int slot = st % P;
-            // kp already points at this lane's unit; past d it falls back to
-            // the row's first 16 bytes (a valid address, zeroed at use).
-            const int ko = (sc * 64 + du * 8 < d) ? sc * 64 : -du * 8;
-#pragma unroll
-            for (int t = 0; t < T; ++t)
-#pragma unroll
-                for (int i = 0; i < 2; ++i) dma16_nt(kp[t][i] + ko, &kring[slot][wv][t][i * kTileSecond]);
-#pragma unroll
-            for (int j = 0; j < NA_W; ++j) {
-                const int qd = (sc * 2 + qstep[j]) * 32 + grp * 8;
-                const int qo = qd < d ? qd - grp * 8 : -grp * 8;   // past d: the row's start
-                dma16(qsrc[j] + qo, &aring[slot][wv + 4 * j][0]);
-            }
-        };
-        f32x4 acc[T][MT];
+    // The next stage to request (stage qst of block qblk) with this lane's
+    // sources in the block's rows (rows past the last re-read it).  It runs on
+    // over the blocks; past the last one that one's rows are read again.
+    const uint16_t* kp[T][2];
+    int qblk = 0, qst = 0;
+    auto set_rows = [&]() {
+        const int64_t key0 = r0 + (int64_t)qblk * KB + wv * 16 * T;
 #pragma unroll
         for (int t = 0; t < T; ++t)
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) acc[t][mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            for (int i = 0; i < 2; ++i) {
+                int64_t row = key0 + t * 16 + 8 * i + dp;
+                if (row >= r1) row = r1 - 1;
+                kp[t][i] = keys + row * rstride + du * 8;
+            }
+    };
+    set_rows();
+    auto issue = [&](int slot) {
+        // kp already points at this lane's unit; past d it falls back to
+        // the row's first 16 bytes (a valid address, zeroed at use).
+        const int ko = (qst * 64 + du * 8 < d) ? qst * 64 : -du * 8;
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) dma16_nt(kp[t][i] + ko, &kring[slot][wv][t][i * kTileSecond]);
+#pragma unroll
+        for (int j = 0; j < NA_W; ++j) {
+            const int qd = (qst * 2 + qstep[j]) * 32 + grp * 8;
+            const int qo = qd < d ? qd - grp * 8 : -grp * 8;   // past d: the row's start
+            dma16(qsrc[j] + qo, &aring[slot][qslot[j]][0]);
+        }
+        if (++qst == nst) {
+            qst = 0;
+            if (++qblk < nblk) set_rows();
+        }
+    };
+    f32x4 acc[T][MT];
+#pragma unroll
+    for (int t = 0; t < T; ++t)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) acc[t][mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
 #pragma unroll
-        for (int st = 0; st < P - 1; ++st) issue(st);
+    for (int i = 0; i < P - 1; ++i) issue(i);
+    int slot = 0;                                 // stage % P
+    for (int blk = 0; blk < nblk; ++blk) {
         for (int st = 0; st < nst; ++st) {
-            // Loads issued after stage st: stages st+1 .. st+P-2.
+            // The loads of P - 2 stages were issued behind this one's.  Every
+            // wave's reads of the stage before have returned when it reaches
+            // the barrier, which frees that stage's slot.
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             wait_vmcnt<(P - 2) * OPS>();
             barrier_no_fence();
-            issue(st + P - 1);                    // refills the slot read at st-1
-            const int slot = st % P;
+            issue(slot == 0 ? P - 1 : slot - 1);
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const int ks = 2 * st + j;
@@ -318,11 +382,12 @@ __global__ __launch_bounds__(256) void scan_mfma_kernel(MfmaScan s, int64_t bloc
                     }
                 }
             }
+            slot = slot + 1 == P ? 0 : slot + 1;
         }
-        // Drain the surplus loads and let every wave finish reading the ring
-        // before the next block's prologue refills it.
-        wait_vmcnt<0>();
-        barrier_no_fence();
+        const int64_t key0 = r0 + (int64_t)blk * KB + wv * 16 * T;
+        bool kv[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) kv[t] = key0 + t * 16 + col < r1;
 
         // Key norms of this lane's keys, all requested before any is used
         // (rows past n read the last row; their scores are not stored).
@@ -433,7 +498,7 @@ __global__ __launch_bounds__(256) void scan_mfma_kernel(MfmaScan s, int64_t bloc
                         if (pass && q < s.nq) {
                             uint64_t* cq = s.cand + (int64_t)q * s.cap;
                             const uint64_t pk = pack_key(v[mt][i], orig);
-                            if (slot < kMfmaSlots) {
+                            if (slot < kWaveSlots) {
                                 cq[wave_slot + slot] = pk;
                             } else {
                                 const int pos = atomicAdd(&s.counts[q], 1);
@@ -445,7 +510,12 @@ __global__ __launch_bounds__(256) void scan_mfma_kernel(MfmaScan s, int64_t bloc
                 }
             }
         }
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[t][mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     }
+    wait_vmcnt<0>();                              // the surplus loads
     if constexpr (FILTER) {
         // Unused slots become padding keys.  Lane col 0 of each group saw
         // every tile its group saw, so its counts are the group's.
@@ -456,7 +526,7 @@ __global__ __launch_bounds__(256) void scan_mfma_kernel(MfmaScan s, int64_t bloc
                 const int c0 = __shfl(cnt[mt][i], lane & ~15, 64);
                 const int q = mt * 16 + grp * 4 + i;
                 if (q < s.nq)
-                    for (int j = col; j < kMfmaSlots; j += 16)
+                    for (int j = col; j < kWaveSlots; j += 16)
                         if (j >= c0) s.cand[(int64_t)q * s.cap + wave_slot + j] = 0;
             }
     }
@@ -464,31 +534,54 @@ __global__ __launch_bounds__(256) void scan_mfma_kernel(MfmaScan s, int64_t bloc
 
 // Grid of the batched scan: one resident workgroup per compute unit (the
 // kernels' LDS ring allows one), an equal run of blocks each.
-int64_t mfma_groups(int64_t n_rows, int T) {
-    const int64_t nblk = (n_rows + 64 * T - 1) / (64 * T);
+int64_t mfma_groups(int64_t n_rows, int block_rows) {
+    const int64_t nblk = (n_rows + block_rows - 1) / block_rows;
     const int64_t groups_max = (int64_t)device_cus();
     int64_t bpg = (nblk + groups_max - 1) / groups_max;
     if (bpg < 1) bpg = 1;
     return (nblk + bpg - 1) / bpg;
 }
 
+// Workgroups of a kernel with rings of `lds` bytes that fit a compute unit.
+constexpr int resident(int lds) { return 160 * 1024 / lds < 1 ? 1 : 160 * 1024 / lds; }
+
 template <int KT, int MT, int T, int P, bool SPLIT>
 hipError_t launch_tile(const MfmaScan& s, hipStream_t stream) {
-    const int64_t nblk = (s.n_rows + 64 * T - 1) / (64 * T);
-    const int64_t groups = mfma_groups(s.n_rows, T);
-    const int64_t bpg = (nblk + groups - 1) / groups;
-    if (s.cand)
+    if (s.cand) {
+        // Whole blocks: the slot area is sized by this grid.
+        constexpr int KB = 16 * kWaves * T;
+        const int64_t nblk = (s.n_rows + KB - 1) / KB;
+        const int64_t groups = mfma_groups(s.n_rows, KB);
+        const int64_t bpg = (nblk + groups - 1) / groups;
         hipLaunchKernelGGL((scan_mfma_kernel<KT, MT, T, P, SPLIT, kModeFilter>),
-                           dim3((unsigned)groups), dim3(256), 0, stream, s, bpg);
-    else if (s.proj_out) {
-        if constexpr (SPLIT && T == 4)   // projections split the fp32 basis
-            hipLaunchKernelGGL((scan_mfma_kernel<KT, MT, T, P, SPLIT, kModeProject>),
-                               dim3((unsigned)groups), dim3(256), 0, stream, s, bpg);
+                           dim3((unsigned)groups), dim3(kThreads), 0, stream, s, bpg * KB);
+        return hipGetLastError();
+    }
+    // An equal run of 16-row tiles for every workgroup that can be resident (a
+    // run's last block may be part full: its missing rows are the last one's
+    // again, which costs no traffic), so that no compute unit has a block more
+    // than another.
+    constexpr int NA = MT * (SPLIT ? 2 : 1);
+    constexpr int kLds = P * 2048 * (kWaves * T + NA);
+    auto run = [&](int64_t groups) { return ((s.n_rows + groups - 1) / groups + 15) / 16 * 16; };
+    int64_t rpg = run((int64_t)device_cus() * resident(kLds));
+    if (rpg < 16 * kWaves * T) {
+        // Less than a block each: one workgroup per compute unit, of no more
+        // than a block (a strided sample of 32768 rows, 2 queries x 4096: 44 us
+        // in half blocks, 34 in whole ones).
+        rpg = run(device_cus());
+        rpg = rpg < 16 * kWaves * T ? rpg : 16 * kWaves * T;
+    }
+    const dim3 grid((unsigned)((s.n_rows + rpg - 1) / rpg));
+    if (s.proj_out) {
+        if constexpr (SPLIT && T == 2)   // projections split the fp32 basis
+            hipLaunchKernelGGL((scan_mfma_kernel<KT, MT, T, P, SPLIT, kModeProject>), grid,
+                               dim3(kThreads), 0, stream, s, rpg);
         else
             return hipErrorInvalidValue;
     } else
-        hipLaunchKernelGGL((scan_mfma_kernel<KT, MT, T, P, SPLIT, kModeWrite>),
-                           dim3((unsigned)groups), dim3(256), 0, stream, s, bpg);
+        hipLaunchKernelGGL((scan_mfma_kernel<KT, MT, T, P, SPLIT, kModeWrite>), grid,
+                           dim3(kThreads), 0, stream, s, rpg);
     return hipGetLastError();
 }
 
@@ -499,23 +592,23 @@ hipError_t launch_tile(const MfmaScan& s, hipStream_t stream) {
 template <int KT>
 hipError_t launch_group_narrow(const MfmaScan& s, hipStream_t stream) {
     switch ((s.nq + 15) / 16) {
-        case 1: return launch_tile<KT, 1, 2, 4, false>(s, stream);
-        case 2: return launch_tile<KT, 2, 2, 4, false>(s, stream);
-        case 3: return launch_tile<KT, 3, 2, 4, false>(s, stream);
-        default: return launch_tile<KT, 4, 2, 4, false>(s, stream);
+        case 1: return launch_tile<KT, 1, 1, 4, false>(s, stream);
+        case 2: return launch_tile<KT, 2, 1, 4, false>(s, stream);
+        case 3: return launch_tile<KT, 3, 1, 4, false>(s, stream);
+        default: return launch_tile<KT, 4, 1, 4, false>(s, stream);
     }
 }
 
 template <int KT, bool SPLIT>
 hipError_t launch_group(const MfmaScan& s, hipStream_t stream) {
     if constexpr (!SPLIT)
-        if (s.cand == nullptr && mfma_groups(s.n_rows, 4) < (int64_t)device_cus())
+        if (s.cand == nullptr && mfma_groups(s.n_rows, 256) < (int64_t)device_cus())
             return launch_group_narrow<KT>(s, stream);
     switch ((s.nq + 15) / 16) {
-        case 1: return launch_tile<KT, 1, 4, 4, SPLIT>(s, stream);
-        case 2: return launch_tile<KT, 2, 4, 3, SPLIT>(s, stream);
-        case 3: return launch_tile<KT, 3, 4, 3, SPLIT>(s, stream);
-        default: return launch_tile<KT, 4, 4, 3, SPLIT>(s, stream);
+        case 1: return launch_tile<KT, 1, 2, 4, SPLIT>(s, stream);
+        case 2: return launch_tile<KT, 2, 2, 3, SPLIT>(s, stream);
+        case 3: return launch_tile<KT, 3, 2, 3, SPLIT>(s, stream);
+        default: return launch_tile<KT, 4, 2, 3, SPLIT>(s, stream);
     }
 }
 
@@ -691,19 +784,27 @@ QuerySplit query_split_parts(void* scratch, int nq, int d) {
                       (float*)((char*)scratch + 2 * half + vec), qpad};
 }
 
-hipError_t launch_query_split(const float* queries, int nq, int d, int key_dtype, bool cosine,
+template <int KT>
+static void launch_query_split_t(const QueryBatch& b, bool cosine, const float* key_norm_max,
+                                 const QuerySplit& p, hipStream_t stream) {
+    auto kern = b.dtype == DT_F32   ? query_split_kernel<KT, DT_F32>
+                : b.dtype == DT_F16 ? query_split_kernel<KT, DT_F16>
+                                    : query_split_kernel<KT, DT_BF16>;
+    hipLaunchKernelGGL(kern, dim3(p.qpad), dim3(256), 0, stream, b.q, b.nq, b.d, cosine, p.hi,
+                       p.lo, p.inv_qn, key_norm_max, p.margin, b.f32, b.mean, b.centre);
+}
+
+hipError_t launch_query_split(const QueryBatch& b, int key_dtype, bool cosine,
                               const float* key_norm_max, void* scratch, hipStream_t stream) {
-    const QuerySplit p = query_split_parts(scratch, nq, d);
+    const QuerySplit p = query_split_parts(scratch, b.nq, b.d);
     if (key_dtype == DT_BF16)
-        hipLaunchKernelGGL(query_split_kernel<DT_BF16>, dim3(p.qpad), dim3(256), 0, stream,
-                           queries, nq, d, cosine, p.hi, p.lo, p.inv_qn, key_norm_max, p.margin);
+        launch_query_split_t<DT_BF16>(b, cosine, key_norm_max, p, stream);
     else
-        hipLaunchKernelGGL(query_split_kernel<DT_F16>, dim3(p.qpad), dim3(256), 0, stream,
-                           queries, nq, d, cosine, p.hi, p.lo, p.inv_qn, key_norm_max, p.margin);
+        launch_query_split_t<DT_F16>(b, cosine, key_norm_max, p, stream);
     return hipGetLastError();
 }
 
-int64_t mfma_scan_waves(int64_t n_rows) { return mfma_groups(n_rows, 4) * 4; }
+int64_t mfma_scan_waves(int64_t n_rows) { return mfma_groups(n_rows, 256) * 4; }
 
 hipError_t launch_scan_mfma_rows(const MfmaScan& s, bool split, hipStream_t stream) {
     if (s.key_dtype == DT_BF16)
@@ -711,12 +812,12 @@ hipError_t launch_scan_mfma_rows(const MfmaScan& s, bool split, hipStream_t stre
     return split ? launch_group<DT_F16, true>(s, stream) : launch_group<DT_F16, false>(s, stream);
 }
 
-hipError_t launch_scan_mfma(const void* keys, int key_dtype, int64_t n, int d, int64_t ld,
-                            const float* queries, int nq, bool split, const float* inv_norm,
+hipError_t launch_scan_mfma(const void* keys, int key_dtype, int64_t n, int64_t ld,
+                            const QueryBatch& b, bool split, const float* inv_norm,
                             float* scores, void* scratch, hipStream_t stream) {
+    const int nq = b.nq, d = b.d;
     const QuerySplit p = query_split_parts(scratch, nq, d);
-    hipError_t e = launch_query_split(queries, nq, d, key_dtype, inv_norm != nullptr, nullptr,
-                                      scratch, stream);
+    hipError_t e = launch_query_split(b, key_dtype, inv_norm != nullptr, nullptr, scratch, stream);
     if (e != hipSuccess) return e;
     for (int g0 = 0; g0 < nq; g0 += 64) {
         MfmaScan s{};
@@ -738,12 +839,14 @@ hipError_t launch_scan_mfma(const void* keys, int key_dtype, int64_t n, int d, i
 }
 
 hipError_t launch_project_mfma(const void* x, int x_dtype, int64_t n, int d_in, int64_t x_stride,
-                               const float* basis, int d_out, const float* centre, int normalize,
+                               const float* basis, int d_out, const float* mean, float* centre,
+                               int normalize,
                                void* out, int out_dtype, int64_t out_stride, void* scratch,
                                hipStream_t stream) {
     if (d_out < 1 || d_out > kMfmaProjOut) return hipErrorInvalidValue;
     const QuerySplit p = query_split_parts(scratch, d_out, d_in);
-    hipError_t e = launch_query_split(basis, d_out, d_in, x_dtype, false, nullptr, scratch, stream);
+    const QueryBatch b{basis, DT_F32, d_out, d_in, nullptr, mean, centre};
+    hipError_t e = launch_query_split(b, x_dtype, false, nullptr, scratch, stream);
     if (e != hipSuccess) return e;
     MfmaScan s{};
     s.keys = x;
@@ -756,7 +859,7 @@ hipError_t launch_project_mfma(const void* x, int x_dtype, int64_t n, int d_in, 
     s.qlo = p.lo;
     s.inv_qn = p.inv_qn;
     s.nq = d_out;
-    s.centre = centre;
+    s.centre = mean ? centre : nullptr;
     s.proj_out = out;
     s.proj_dtype = out_dtype;
     s.proj_stride = out_stride;

@@ -444,16 +444,17 @@ SENSE_EXPORT sense_status_t sense_retrieve_workspace_size(const sense_index_t* i
 // Short keys, query batch: per 64 queries either plain scores + top-k (small
 // stores), or the best score of every group of rows, the k best groups, the
 // scores of their rows and the top k of those.
-static hipError_t retrieve_short(const sense_index* ix, const float* qptr, int nq, int k,
-                                 bool split, int64_t* out_ids, float* out_scores,
+static hipError_t retrieve_short(const sense_index* ix, const void* queries, int q_dtype, int nq,
+                                 int k, bool split, int64_t* out_ids, float* out_scores,
                                  int32_t* out_drafts, int32_t* out_draft_len, char* ws,
                                  hipStream_t st) {
     const ShortLayout L = short_layout(ix, nq, k);
     const int64_t n = ix->n;
     hipError_t e;
     if ((e = timer_mark(SENSE_TIMER_SCAN, 0, st)) != hipSuccess) return e;
-    if ((e = sense::launch_query_split(qptr, nq, ix->d, ix->key_dtype, ix->inv_norm != nullptr,
-                                       nullptr, ws + L.m_off, st)) != hipSuccess)
+    const sense::QueryBatch qb{queries, q_dtype, nq, ix->d, nullptr, nullptr, nullptr};
+    if ((e = sense::launch_query_split(qb, ix->key_dtype, ix->inv_norm != nullptr, nullptr,
+                                       ws + L.m_off, st)) != hipSuccess)
         return e;
     const sense::QuerySplit qs = sense::query_split_parts(ws + L.m_off, nq, ix->d);
     const bool direct = n <= kShortDirectMax;
@@ -540,15 +541,19 @@ static hipError_t retrieve_short(const sense_index* ix, const float* qptr, int n
 //
 // Timers: SCAN spans the query split, the sample, its top-k and the filtered
 // pass; FILTER the first query group's filtered pass alone; TOPK the rest.
-static hipError_t retrieve_batched(const sense_index* ix, const float* qptr, int nq, int k,
-                                   bool split, int64_t* out_ids, float* out_scores,
+static hipError_t retrieve_batched(const sense_index* ix, const void* queries, int q_dtype,
+                                   int nq, int k, bool split, int64_t* out_ids, float* out_scores,
                                    int32_t* out_drafts, int32_t* out_draft_len, char* ws,
                                    hipStream_t st) {
     const ShortLayout L = short_layout(ix, nq, k);
     const int64_t n = ix->n;
     hipError_t e;
     if ((e = timer_mark(SENSE_TIMER_SCAN, 0, st)) != hipSuccess) return e;
-    if ((e = sense::launch_query_split(qptr, nq, ix->d, ix->key_dtype, ix->inv_norm != nullptr,
+    // The rescore reads the queries in fp32.
+    float* qf = q_dtype == SENSE_F32 ? nullptr : (float*)(ws + L.q_off);
+    const float* qptr = qf ? qf : (const float*)queries;
+    const sense::QueryBatch qb{queries, q_dtype, nq, ix->d, qf, nullptr, nullptr};
+    if ((e = sense::launch_query_split(qb, ix->key_dtype, ix->inv_norm != nullptr,
                                        (const float*)ix->key_norm_max, ws + L.m_off, st)) !=
         hipSuccess)
         return e;
@@ -663,32 +668,32 @@ SENSE_EXPORT sense_status_t sense_retrieve(const sense_index_t* ix, const void* 
     float* qf = (float*)(ws + L.q_off);
     float* scores = (float*)(ws + L.s_off);
     hipError_t e;
+    const bool split = q_dtype != ix->key_dtype;  // key-typed queries need no lo half
+    if (short_batched(ix, nq)) {
+        if ((e = retrieve_short(ix, queries, q_dtype, nq, k, split, out_ids, out_scores, out_drafts,
+                                out_draft_len, ws, st)) != hipSuccess)
+            return hip_fail(e, "short-key batched retrieval");
+        return ok();
+    }
+    if (long_batched(ix, nq)) {
+        if ((e = retrieve_batched(ix, queries, q_dtype, nq, k, split, out_ids, out_scores, out_drafts,
+                                  out_draft_len, ws, st)) != hipSuccess)
+            return hip_fail(e, "batched retrieval");
+        return ok();
+    }
     const float* qptr = (const float*)queries;
     if (q_dtype != SENSE_F32) {
         if ((e = sense::launch_query_to_f32(queries, q_dtype, nq, ix->d, qf, st)) != hipSuccess)
             return hip_fail(e, "query conversion");
         qptr = qf;
     }
-    const bool split = q_dtype != ix->key_dtype;  // key-typed queries need no lo half
-    if (short_batched(ix, nq)) {
-        if ((e = retrieve_short(ix, qptr, nq, k, split, out_ids, out_scores, out_drafts,
-                                out_draft_len, ws, st)) != hipSuccess)
-            return hip_fail(e, "short-key batched retrieval");
-        return ok();
-    }
-    if (long_batched(ix, nq)) {
-        if ((e = retrieve_batched(ix, qptr, nq, k, split, out_ids, out_scores, out_drafts,
-                                  out_draft_len, ws, st)) != hipSuccess)
-            return hip_fail(e, "batched retrieval");
-        return ok();
-    }
     if ((e = timer_mark(SENSE_TIMER_SCAN, 0, st)) != hipSuccess) return hip_fail(e, "timer");
-    if (ix->d <= sense::kSmallDim && nq < sense::kMfmaMinQueries)
+    if (ix->d <= sense::kSmallDim)
         e = sense::launch_scan_small(ix->keys, ix->key_dtype, ix->n, ix->d, ix->ld, qptr, nq,
                                      ix->inv_norm, scores, st);
     else
-        e = sense::launch_scan(ix->keys, ix->key_dtype, ix->n, ix->d, ix->ld, qptr, nq, split,
-                               ix->inv_norm, scores, ws + L.m_off, st);
+        e = sense::launch_scan(ix->keys, ix->key_dtype, ix->n, ix->d, ix->ld, qptr, nq,
+                               ix->inv_norm, scores, st);
     if (e != hipSuccess) return hip_fail(e, "similarity scan");
     if ((e = timer_mark(SENSE_TIMER_SCAN, 1, st)) != hipSuccess) return hip_fail(e, "timer");
     if ((e = timer_mark(SENSE_TIMER_TOPK, 0, st)) != hipSuccess) return hip_fail(e, "timer");

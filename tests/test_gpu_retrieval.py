@@ -586,3 +586,26 @@ def test_short_groups_are_exact_with_ties(n, d, nq, k, dt):
         assert torch.equal(scores[i].cpu().double(), want[i][order])
         assert torch.equal(drafts[i].cpu(), spans[order])
     index.close()
+
+
+@pytest.mark.parametrize("kt,qt", [("bf16", "f16"), ("f16", "bf16"), ("f16", "f16")])
+@pytest.mark.parametrize("n,d,nq", [(5000, 64, 3), (40_001, 24, 20), (6000, 136, 5),
+                                    (140_007, 72, 18)])
+def test_16_bit_queries_of_either_type(n, d, nq, kt, qt):
+    """Queries in a 16-bit type, that of the keys or the other one, from a row
+    start of any alignment.  Small whole numbers: every score is exact."""
+    tdt = {"bf16": torch.bfloat16, "f16": torch.float16}
+    g = torch.Generator().manual_seed(n)
+    keys = torch.randint(-3, 4, (n, d), generator=g).float()
+    flat = torch.randint(-2, 3, (nq * d + 1,), generator=g).float().to(tdt[qt]).to(DEV)
+    q = flat[1:].view(nq, d)
+    spans = torch.zeros((n, 1), dtype=torch.int32, device=DEV)
+    index = sense.sense_build_index(keys.to(tdt[kt]).to(DEV), spans, None, metric="ip")
+    ids, scores, _, _ = sense.sense_retrieve(index, q, 10)
+    torch.cuda.synchronize()
+    want = q.cpu().double() @ keys.double().T
+    for i in range(nq):
+        order = torch.from_numpy(np.lexsort((np.arange(n), -want[i].numpy()))[:10].copy())
+        assert torch.equal(ids[i].cpu(), order), f"query {i}"
+        assert torch.equal(scores[i].cpu().double(), want[i][order])
+    index.close()
