@@ -548,14 +548,16 @@ constexpr int resident(int lds) { return 160 * 1024 / lds < 1 ? 1 : 160 * 1024 /
 template <int KT, int MT, int T, int P, bool SPLIT>
 hipError_t launch_tile(const MfmaScan& s, hipStream_t stream) {
     if (s.cand) {
-        // Whole blocks: the slot area is sized by this grid.
-        constexpr int KB = 16 * kWaves * T;
-        const int64_t nblk = (s.n_rows + KB - 1) / KB;
-        const int64_t groups = mfma_groups(s.n_rows, KB);
-        const int64_t bpg = (nblk + groups - 1) / groups;
-        hipLaunchKernelGGL((scan_mfma_kernel<KT, MT, T, P, SPLIT, kModeFilter>),
-                           dim3((unsigned)groups), dim3(kThreads), 0, stream, s, bpg * KB);
-        return hipGetLastError();
+        if constexpr (T == 2) {                  // filtered passes take whole blocks of T = 2:
+            constexpr int KB = 16 * kWaves * T;  // the slot area is sized by this grid
+            const int64_t nblk = (s.n_rows + KB - 1) / KB;
+            const int64_t groups = mfma_groups(s.n_rows, KB);
+            const int64_t bpg = (nblk + groups - 1) / groups;
+            hipLaunchKernelGGL((scan_mfma_kernel<KT, MT, T, P, SPLIT, kModeFilter>),
+                               dim3((unsigned)groups), dim3(kThreads), 0, stream, s, bpg * KB);
+            return hipGetLastError();
+        }
+        return hipErrorInvalidValue;
     }
     // An equal run of 16-row tiles for every workgroup that can be resident (a
     // run's last block may be part full: its missing rows are the last one's
@@ -574,7 +576,7 @@ hipError_t launch_tile(const MfmaScan& s, hipStream_t stream) {
     }
     const dim3 grid((unsigned)((s.n_rows + rpg - 1) / rpg));
     if (s.proj_out) {
-        if constexpr (SPLIT && T == 2)   // projections split the fp32 basis
+        if constexpr (SPLIT)             // projections split the fp32 basis
             hipLaunchKernelGGL((scan_mfma_kernel<KT, MT, T, P, SPLIT, kModeProject>), grid,
                                dim3(kThreads), 0, stream, s, rpg);
         else
@@ -599,11 +601,35 @@ hipError_t launch_group_narrow(const MfmaScan& s, hipStream_t stream) {
     }
 }
 
+template <int KT, int T, int P>
+hipError_t launch_group_split(const MfmaScan& s, hipStream_t stream) {
+    switch ((s.nq + 15) / 16) {
+        case 1: return launch_tile<KT, 1, T, P, true>(s, stream);
+        case 2: return launch_tile<KT, 2, T, P, true>(s, stream);
+        case 3: return launch_tile<KT, 3, T, P, true>(s, stream);
+        default: return launch_tile<KT, 4, T, P, true>(s, stream);
+    }
+}
+
 template <int KT, bool SPLIT>
 hipError_t launch_group(const MfmaScan& s, hipStream_t stream) {
     if constexpr (!SPLIT)
         if (s.cand == nullptr && mfma_groups(s.n_rows, 256) < (int64_t)device_cus())
             return launch_group_narrow<KT>(s, stream);
+    if constexpr (SPLIT) {
+        // The query fragments, hi and lo, are read again for every block of
+        // rows: as much as half the keys' bytes at 256 rows and 64 queries.
+        // Blocks of 512 rows in two stages halve that where a compute unit has
+        // the rows (262144 x 4096 onto 64 outputs 443 -> 380 us, 100001 x 1024
+        // 62.3 -> 58.5); where it has not, a stage of fewer rows and more of
+        // them (30000 x 8192 269 us in blocks of 512, 181 of 256, 141 of 128;
+        // 2000 x 4096 120, 79, 57).
+        const int64_t rows = (s.n_rows + device_cus() - 1) / device_cus();
+        if (s.cand == nullptr && rows <= 16 * kWaves)
+            return launch_group_split<KT, 1, 4>(s, stream);
+        if (s.cand == nullptr && rows > 32 * kWaves)
+            return launch_group_split<KT, 4, 2>(s, stream);
+    }
     switch ((s.nq + 15) / 16) {
         case 1: return launch_tile<KT, 1, 2, 4, SPLIT>(s, stream);
         case 2: return launch_tile<KT, 2, 2, 3, SPLIT>(s, stream);

@@ -283,3 +283,26 @@ def test_full_size_short_key_retrieval(nq):
         assert np.array_equal(dr[qq].cpu().numpy(), oracle.gather(spans, None, g_ids)[0])
     print(f"[short-scan] {nq} queries ok", flush=True)
     index.close()
+
+
+@pytest.mark.parametrize("n,d_in,d_out", [
+    (32_769, 72, 64), (33_001, 1000, 33),            # 129 rows a compute unit: blocks of 256
+    (65_537, 136, 17), (70_003, 64, 96),             # 257 rows: blocks of 512, the last part full
+    (131_073, 40, 5),                                # two blocks of 512, the second of few rows
+    (513, 4104, 48),                                 # one block of 128 rows for some, none for most
+])
+@pytest.mark.parametrize("dt", [torch.bfloat16, torch.float16])
+def test_block_shapes_of_a_store_projection(n, d_in, d_out, dt):
+    """Every block shape of the matrix-core projection, with ragged last blocks
+    and a ragged last 64-dim stage, against 64 bits: the split basis leaves 2^-16
+    (bf16) of each product, d_in of them of either sign, beside unit rows."""
+    g = torch.Generator(device="cuda").manual_seed(n)
+    x = torch.randn((n, d_in), generator=g, device="cuda").to(dt)
+    basis = torch.randn((d_out, d_in), generator=g, device="cuda") / d_in ** 0.5
+    mean = 0.1 * torch.randn((d_in,), generator=g, device="cuda")
+    out = torch.full((n, d_out), float("nan"), device="cuda")
+    sense.sense_project(x, basis, mean, out=out)
+    torch.cuda.synchronize()
+    want = (x.double() - mean.double()) @ basis.double().T
+    want = want / want.norm(dim=1, keepdim=True)
+    assert (out.double() - want).abs().max().item() < 2.0 ** -12
