@@ -106,7 +106,7 @@ bool short_batched(const sense_index* ix, int nq) {
 }
 
 // Long keys, query batches: the matrix-core scan.  Stores of more than
-// kBatchDirectMax rows are searched like the short keys (a strided sample's
+// kBatchDirectMax rows are searched by a threshold (a strided sample's
 // k-th best as the threshold of a filtered pass), smaller ones through the
 // plain score matrix.
 constexpr int64_t kBatchSample = 32768;
@@ -122,7 +122,7 @@ struct ShortLayout {
     int64_t cap;    // entries of one query's candidate list
 };
 
-// Workspace of the sampled-threshold retrieval (short keys, or long keys in
+// Workspace of the batched retrieval (short keys, or long keys in
 // batches): query split, sample scores and top-k, thresholds and counts, the
 // candidate lists (wave slots + an overflow list of up to every row) or, for
 // a store searched directly, the plain score matrix in the same area.
@@ -692,8 +692,8 @@ SENSE_EXPORT sense_status_t sense_retrieve(const sense_index_t* ix, const void* 
         e = sense::launch_scan_small(ix->keys, ix->key_dtype, ix->n, ix->d, ix->ld, qptr, nq,
                                      ix->inv_norm, scores, st);
     else
-        e = sense::launch_scan(ix->keys, ix->key_dtype, ix->n, ix->d, ix->ld, qptr, nq,
-                               ix->inv_norm, scores, st);
+        e = sense::launch_scan(ix->keys, ix->key_dtype, ix->n, ix->d, ix->ld, qptr, nq, split,
+                               ix->inv_norm, scores, ws + L.m_off, st);
     if (e != hipSuccess) return hip_fail(e, "similarity scan");
     if ((e = timer_mark(SENSE_TIMER_SCAN, 1, st)) != hipSuccess) return hip_fail(e, "timer");
     if ((e = timer_mark(SENSE_TIMER_TOPK, 0, st)) != hipSuccess) return hip_fail(e, "timer");
