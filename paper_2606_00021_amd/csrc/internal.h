@@ -6,6 +6,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include "filter_lists.h"
+
 namespace sense {
 
 // Element encodings (same numbering as sense_dtype_t).
@@ -121,10 +123,10 @@ size_t scan_mfma_scratch_bytes(int nq, int d);
 // rows 0, row_step, 2 row_step, ... (n_rows of them) of a store of row
 // stride ld.  WRITE mode (scores != NULL): scores[q * n_rows + i].  FILTER
 // mode (cand != NULL): rows whose score reaches the score of tau[q] go to
-// query q's candidate list cand + q * cap as packed (score, row) keys: the slots
-// of each workgroup's waves, 4 * kMfmaSlots (the rest padding keys),
-// then an overflow list whose next position is counts[q] (to be initialised
-// to the slot area, mfma_scan_waves(n_rows) * kMfmaSlots).
+// query q's candidate list cand + q * cap as packed (score, row) keys: kFilterSlots
+// slots of each workgroup, dealt to its waves (the rest padding keys), then an
+// overflow list of up to n_rows whose next position is counts[q] (to be
+// initialised to filter_slots(n_rows, device_cus()); see filter_lists.h).
 struct MfmaScan {
     const void* keys;
     int key_dtype;
@@ -149,9 +151,7 @@ struct MfmaScan {
     int normalize;
     int proj_vec;             // 4 outputs per store (16-byte base, stride % 4, nq % 4)
 };
-constexpr int kMfmaSlots = 32;
 hipError_t launch_scan_mfma_rows(const MfmaScan& s, bool split, hipStream_t stream);
-int64_t mfma_scan_waves(int64_t n_rows);
 // A query batch to be split: nq x d values of dtype (fp32 or either 16-bit type).
 // f32 (may be NULL) receives them in fp32; with mean (may be NULL) centre[q] =
 // mean . query q.

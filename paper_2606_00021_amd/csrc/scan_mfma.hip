@@ -214,7 +214,7 @@ constexpr int kTileSecond = 64;               // first entry of rows 8-15
 // rows whose score reaches the query's threshold (tau, the packed key of the
 // k-th best row of a sample: every row of the true top k reaches it) as
 // packed (score, row) keys in the query's candidate list: this wave's
-// kMfmaSlots slots first (positions from ballot prefix counts), then the
+// kWaveSlots slots first (positions from ballot prefix counts), then the
 // query's overflow list (atomic position).  At Q = 64 the score matrix would
 // be 64 x 4 bytes per row of 16 KiB, few bytes but scattered 64-byte writes
 // that cut the scan's read rate by a fifth; the survivors are ~k*row_step.
@@ -232,9 +232,9 @@ constexpr int kModeWrite = 0, kModeFilter = 1, kModeProject = 2;
 // 100003 x 3584).
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
-// A workgroup's slots of a candidate list, 4 * kMfmaSlots, dealt to its waves.
-constexpr int kWaveSlots = 4 * kMfmaSlots / kWaves;
-static_assert(kWaveSlots * kWaves == 4 * kMfmaSlots, "slots per wave");
+// A workgroup's slots of a candidate list, dealt to its waves.
+constexpr int kWaveSlots = kFilterSlots / kWaves;
+static_assert(kWaveSlots * kWaves == kFilterSlots, "slots per wave");
 
 template <int KT, int MT, int T, int P, bool SPLIT, int MODE>
 __global__ __launch_bounds__(kThreads) void scan_mfma_kernel(MfmaScan s, int64_t rows_per_group) {
@@ -532,29 +532,21 @@ __global__ __launch_bounds__(kThreads) void scan_mfma_kernel(MfmaScan s, int64_t
     }
 }
 
-// Grid of the batched scan: one resident workgroup per compute unit (the
-// kernels' LDS ring allows one), an equal run of blocks each.
-int64_t mfma_groups(int64_t n_rows, int block_rows) {
-    const int64_t nblk = (n_rows + block_rows - 1) / block_rows;
-    const int64_t groups_max = (int64_t)device_cus();
-    int64_t bpg = (nblk + groups_max - 1) / groups_max;
-    if (bpg < 1) bpg = 1;
-    return (nblk + bpg - 1) / bpg;
-}
-
 // Workgroups of a kernel with rings of `lds` bytes that fit a compute unit.
 constexpr int resident(int lds) { return 160 * 1024 / lds < 1 ? 1 : 160 * 1024 / lds; }
 
 template <int KT, int MT, int T, int P, bool SPLIT>
 hipError_t launch_tile(const MfmaScan& s, hipStream_t stream) {
     if (s.cand) {
-        if constexpr (T == 2) {                  // filtered passes take whole blocks of T = 2:
-            constexpr int KB = 16 * kWaves * T;  // the slot area is sized by this grid
-            const int64_t nblk = (s.n_rows + KB - 1) / KB;
-            const int64_t groups = mfma_groups(s.n_rows, KB);
+        if constexpr (16 * kWaves * T == kFilterRows) {
+            // Whole blocks, one workgroup per compute unit (the ring's LDS
+            // allows one): the lists' slots are those of this grid.
+            const int64_t nblk = (s.n_rows + kFilterRows - 1) / kFilterRows;
+            const int64_t groups = filter_groups(s.n_rows, device_cus());
             const int64_t bpg = (nblk + groups - 1) / groups;
             hipLaunchKernelGGL((scan_mfma_kernel<KT, MT, T, P, SPLIT, kModeFilter>),
-                               dim3((unsigned)groups), dim3(kThreads), 0, stream, s, bpg * KB);
+                               dim3((unsigned)groups), dim3(kThreads), 0, stream, s,
+                               bpg * kFilterRows);
             return hipGetLastError();
         }
         return hipErrorInvalidValue;
@@ -614,7 +606,7 @@ hipError_t launch_group_split(const MfmaScan& s, hipStream_t stream) {
 template <int KT, bool SPLIT>
 hipError_t launch_group(const MfmaScan& s, hipStream_t stream) {
     if constexpr (!SPLIT)
-        if (s.cand == nullptr && mfma_groups(s.n_rows, 256) < (int64_t)device_cus())
+        if (s.cand == nullptr && filter_groups(s.n_rows, device_cus()) < (int64_t)device_cus())
             return launch_group_narrow<KT>(s, stream);
     if constexpr (SPLIT) {
         // The query fragments, hi and lo, are read again for every block of
@@ -829,8 +821,6 @@ hipError_t launch_query_split(const QueryBatch& b, int key_dtype, bool cosine,
         launch_query_split_t<DT_F16>(b, cosine, key_norm_max, p, stream);
     return hipGetLastError();
 }
-
-int64_t mfma_scan_waves(int64_t n_rows) { return mfma_groups(n_rows, 256) * 4; }
 
 hipError_t launch_scan_mfma_rows(const MfmaScan& s, bool split, hipStream_t stream) {
     if (s.key_dtype == DT_BF16)

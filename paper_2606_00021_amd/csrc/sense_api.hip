@@ -148,8 +148,9 @@ ShortLayout short_layout(const sense_index* ix, int nq, int k) {
     l.cnt_off = take((size_t)g * sizeof(int32_t));
     // candidates per query: the wave slots, then an overflow list of up to
     // every row; also the plain score matrix of small stores
-    const int64_t cap = long_keys ? sense::mfma_scan_waves(rows) * sense::kMfmaSlots + rows
-                                  : sense::short_list_slots(rows) + rows;
+    const int64_t cap = long_keys
+                            ? sense::filter_list_entries(ix->n, ix->capacity, sense::device_cus())
+                            : sense::short_list_slots(rows) + rows;
     l.cap = cap;
     l.cand_off = take((size_t)g * cap * sizeof(uint64_t));
     l.fws_off = take(sense::topk_workspace_bytes(cap, g, k));
@@ -562,7 +563,8 @@ static hipError_t retrieve_batched(const sense_index* ix, const void* queries, i
     const bool rescore = sample;
     const bool mfma_split = split && !rescore;
     const int64_t step = sample ? n / kBatchSample : 1;
-    const int64_t slot_area = sense::mfma_scan_waves(n) * sense::kMfmaSlots;
+    const int64_t slot_area = sense::filter_slots(n, sense::device_cus());
+    if (sample && slot_area + n > L.cap) return hipErrorInvalidValue;   // the lists' stride below
     for (int g0 = 0; g0 < nq; g0 += 64) {
         const int ng = nq - g0 < 64 ? nq - g0 : 64;
         sense::MfmaScan S{};

@@ -311,6 +311,34 @@ def test_dynamic_cache_batched_sampled(metric):
     cache.close()
 
 
+def test_growing_cache_between_grid_steps():
+    """A cache whose capacity takes fewer workgroups than the rows it holds now:
+    769 blocks of 256 rows are four a workgroup on 256 compute units (193 of
+    them), 768 are three (256 workgroups, and their candidate slots).  The
+    workspace, sized by the capacity, ends where a guard begins that no launch
+    may touch, and the hits are the oracle's."""
+    n, capacity, d, nq, k, m = 196_608, 196_645, 72, 64, 64, 4
+    print(f"[case] cache of {capacity} rows holding {n} d={d} Q={nq} k={k}", flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(53)
+    rows = torch.randn((n, d), generator=g, device=DEV).to(torch.bfloat16)
+    tok = torch.randint(0, 32000, (n,), generator=g, device=DEV, dtype=torch.int32)
+    q = torch.randn((nq, d), generator=g, device=DEV)
+    cache = sense.sense_build_dynamic_index(d, capacity, m, key_dtype=torch.bfloat16)
+    sense.sense_index_append(cache, rows, tok)
+    need, guard = sense.sense_retrieve_workspace_size(cache, nq, k), 1 << 22
+    buf = torch.full((need + guard,), 0xA5, dtype=torch.uint8, device=DEV)
+    ids, scores, _, _ = sense.sense_retrieve(cache, q, k, workspace=buf[:need])
+    torch.cuda.synchronize()
+    assert (buf[need:] == 0xA5).all(), "written past the workspace"
+    kb, qh = host_bits(rows), q.cpu().numpy()
+    o_s = oracle.scores(kb, "bf16", qh, "f32")
+    bounds = query_bounds(kb, "bf16", qh, "cosine")
+    for qi in range(nq):
+        check_topk(ids[qi].cpu().numpy(), scores[qi].cpu().numpy(), o_s[qi], k, bounds[qi])
+    cache.close()
+
+
 @pytest.mark.parametrize("metric", ["cosine", "ip"])
 def test_batched_sampled_all_rows_tie(metric):
     """Every stored row the same key: every row reaches the sampled threshold
