@@ -223,7 +223,9 @@ __device__ __forceinline__ void swap_max(float (&v)[16], bool bit) {
 // product and one maximum per score); at a group's end 16 columns meet in four
 // transposing steps that leave each lane one query's maximum.  The query's
 // scale, a factor >= 0, goes on the maximum: rounding is monotone, so that is
-// the maximum of the scaled scores.
+// the maximum of the scaled scores, but for a scale of 0 (a query whose squared
+// norm is beyond fp32) on an infinite maximum.  Such a wave goes over its rows
+// again with the scale on every score.
 //
 // Bound: the read of the keys, 34 us for 1M x 64 bf16 and 64 queries (4.1 TB/s;
 // 33 without the products: loads alone, norms and stores of the maxima), of
@@ -379,6 +381,7 @@ __global__ __launch_bounds__(kShortThreads, 2) void scan_groups_kernel(ShortScan
     };
     const int per_group = s.group_rows / 16;
     int left = per_group;                            // tiles to the end of the group
+    bool over = false;                               // this lane's query had an infinite maximum
     for (int t = 0; t < ntiles;) {
         u32x4 b[2][2];
         float ks[2];
@@ -414,11 +417,46 @@ __global__ __launch_bounds__(kShortThreads, 2) void scan_groups_kernel(ShortScan
             swap_max<0x4E, 4>(v, col & 2);           // quad xor 2
             swap_max<0xB1, 2>(v, col & 1);           // quad xor 1
             if (out) *dst = v[0] * scale;
+            over |= v[0] == __builtin_inff();
             ++dst;
             left = per_group;
         }
     }
     wait_vmcnt<0>();
+    if (!__ballot(out && over && scale == 0.0f)) return;
+    // A finite product of the query makes the row's score 0, another NaN.
+    float* again = s.gmax + (int64_t)(out ? oq : 0) * s.n_groups + g0;
+    for (int64_t r = r0; r < r1; r += s.group_rows, ++again) {
+        const int64_t r_top = r + s.group_rows < r1 ? r + s.group_rows : r1;
+        float v[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) v[i] = __builtin_nanf("");
+        for (int64_t base = r; base < r_top; base += 16) {
+            const bool row_in = base + col < r_top;
+            const int64_t row = row_in ? base + col : r_top - 1;
+            const uint16_t* kp = keys + row * s.ld;
+            u32x4 b0 = *(const u32x4*)(kp + (dim0 ? 8 * grp : 0));
+            u32x4 b1 = *(const u32x4*)(kp + (dim1 ? 8 * grp + 32 : 0));
+            const float kn = cosine ? s.inv_norm[row] : 1.0f;
+            if (!dim0) b0 = u32x4{0u, 0u, 0u, 0u};
+            if (!dim1) b1 = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int q = 0; q < NT; ++q) {
+                f32x4 acc = mfma<KT>(ahi[q][0], b0, f32x4{0.0f, 0.0f, 0.0f, 0.0f});
+                if constexpr (SPLIT) acc = mfma<KT>(alo[q][0], b0, acc);
+                acc = mfma<KT>(ahi[q][1], b1, acc);
+                if constexpr (SPLIT) acc = mfma<KT>(alo[q][1], b1, acc);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (row_in && __builtin_fabsf(acc[i] * kn) < __builtin_inff()) v[4 * q + i] = 0.0f;
+            }
+        }
+        swap_max<0x140, 16>(v, col & 8);
+        swap_max<0x141, 8>(v, col & 4);
+        swap_max<0x4E, 4>(v, col & 2);
+        swap_max<0xB1, 2>(v, col & 1);
+        if (out && scale == 0.0f) *again = v[0];
+    }
 }
 
 // The scores of the rows of each query's best groups: one wave per (query,

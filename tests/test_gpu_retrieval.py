@@ -311,6 +311,42 @@ def test_dynamic_cache_batched_sampled(metric):
     cache.close()
 
 
+@pytest.mark.parametrize("d,nq,n", [(64, 3, 40_000), (24, 20, 140_011)])
+def test_short_batch_norm_beyond_fp32(d, nq, n):
+    """Cosine scores of a query whose squared norm overflows fp32 are 0 for a row
+    whose product is finite and NaN for one whose product overflows.  A row of
+    either kind in one group of rows must not hide the others': the hits are the
+    first finite rows.  The other queries of the batch are ordinary ones."""
+    print(f"[case] norm beyond fp32 d={d} Q={nq} n={n}", flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(d)
+    keys = torch.randn((n, d), generator=g, device=DEV)
+    keys[:, 0] = keys[:, 0].abs() + 0.5
+    at = torch.arange(n, device=DEV)
+    huge = (at % 16 == 5) & (at < 4000)                # one such row in each of the first groups
+    huge |= at < 40                                    # and groups of nothing else
+    keys[huge] *= 1e15
+    keys = keys.to(torch.bfloat16)
+    spans = torch.zeros((n, 1), dtype=torch.int32, device=DEV)
+    q = torch.randn((nq, d), generator=g, device=DEV)
+    q[1] = 0.0
+    q[1, 0] = 1e28                                     # 1e28 * 1e15 overflows, 1e28 does not
+    index = sense.sense_build_index(keys, spans, None, metric="cosine")
+    k = 100
+    ids, scores, _, _ = sense.sense_retrieve(index, q, k)
+    torch.cuda.synchronize()
+    want = torch.nonzero(~huge).view(-1)[:k]
+    assert torch.equal(ids[1], want)
+    assert (scores[1] == 0).all()
+    kb, qh = host_bits(keys), q.cpu().numpy()
+    o_s = oracle.scores(kb, "bf16", qh, "f32")
+    bounds = query_bounds(kb, "bf16", qh, "cosine")
+    for qi in range(nq):
+        if qi != 1:
+            check_topk(ids[qi].cpu().numpy(), scores[qi].cpu().numpy(), o_s[qi], k, bounds[qi])
+    index.close()
+
+
 def test_growing_cache_between_grid_steps():
     """A cache whose capacity takes fewer workgroups than the rows it holds now:
     769 blocks of 256 rows are four a workgroup on 256 compute units (193 of
