@@ -28,38 +28,75 @@ __device__ __forceinline__ int shift_to_14(float big) {
     return (ex > -127 && ex < 128) ? 14 - ex : 0;
 }
 
-// The list of one key in plain fp32 (the definition, centroid by centroid):
-// for keys whose squared norm is not an ordinary number (zero, infinite, NaN
-// or out of fp32's normal range), which the matrix-core path leaves out.
+// The better of (b, r) and (ob, orow): the larger score, the lower row on a tie.
+__device__ __forceinline__ void take_better(float& b, int& r, float ob, int orow) {
+    const bool up = ob > b || (ob == b && orow < r);
+    b = up ? ob : b;
+    r = up ? orow : r;
+}
+
+// The list of one key (the same in every lane) in plain fp32, the definition
+// centroid by centroid, by a whole wave: for keys that the matrix-core path
+// leaves out.  A lane takes every 64th centroid; a key whose cosine scale is 0
+// (its squared norm overflows or vanishes in fp32) scores 0 or NaN, and the
+// first 0 ends the search.  Bound: the centroids' read by one wave, 1 MiB of
+// them at 4096 x 64 (one lane alone walked nlist * d / 2 dependent steps: 262144
+// keys, one of them zero, 11.9 ms).
 template <int KT>
 __device__ __attribute__((noinline)) int assign_one(const uint16_t* __restrict__ row, int d,
                                                     const float* __restrict__ centroids,
                                                     int nlist, int cosine) {
-    float xn = 0.0f;
-    for (int t = 0; t < d; ++t) {
-        const float x = elem_f32<KT>(row[t]);
-        xn = __builtin_fmaf(x, x, xn);
-    }
-    const float inv_x = (xn > 0.0f) ? 1.0f / __builtin_sqrtf(xn) : 0.0f;
+    const int lane = threadIdx.x & 63;
     float best = -__builtin_inff();
     int arg = 0;
-    for (int l = 0; l < nlist; ++l) {
-        const float* c = centroids + (int64_t)l * d;
-        float a0 = 0.0f, a1 = 0.0f, cn = 0.0f;
-        for (int t = 0; t < d; t += 2) {
-            a0 = __builtin_fmaf(elem_f32<KT>(row[t]), c[t], a0);
-            a1 = __builtin_fmaf(elem_f32<KT>(row[t + 1]), c[t + 1], a1);
-            cn = __builtin_fmaf(c[t], c[t], cn);
-            cn = __builtin_fmaf(c[t + 1], c[t + 1], cn);
+    for (int l0 = 0; l0 < nlist; l0 += 64) {
+        const int l = l0 + lane;
+        const float* c = centroids + (int64_t)(l < nlist ? l : 0) * d;
+        float a0 = 0.0f, a1 = 0.0f, cn = 0.0f, xn = 0.0f;
+        for (int t = 0; t < d; t += 8) {             // d is a multiple of 8
+            const u32x4 w = *(const u32x4*)(row + t);
+            float cv[8];
+            __builtin_memcpy(cv, c + t, 32);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float x0 = elem_f32<KT>(w[j] & 0xFFFFu), x1 = elem_f32<KT>(w[j] >> 16);
+                a0 = __builtin_fmaf(x0, cv[2 * j], a0);
+                a1 = __builtin_fmaf(x1, cv[2 * j + 1], a1);
+                cn = __builtin_fmaf(cv[2 * j], cv[2 * j], cn);
+                cn = __builtin_fmaf(cv[2 * j + 1], cv[2 * j + 1], cn);
+                xn = __builtin_fmaf(x0, x0, xn);
+                xn = __builtin_fmaf(x1, x1, xn);
+            }
         }
+        const float inv_x = (xn > 0.0f) ? 1.0f / __builtin_sqrtf(xn) : 0.0f;
         float s = a0 + a1;
         if (cosine) s = (s * ((cn > 0.0f) ? 1.0f / __builtin_sqrtf(cn) : 0.0f)) * inv_x;
-        if (s > best) {
+        if (l < nlist && s > best) {
             best = s;
             arg = l;
         }
+        if (cosine && inv_x == 0.0f && __ballot(best == 0.0f)) break;
     }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1)
+        take_better(best, arg, __shfl_xor(best, off, 64), __shfl_xor(arg, off, 64));
     return arg;
+}
+
+// out_list of the keys that `mask`'s lanes hold (a lane's key is row `i` of the
+// store), a wave at a time for each.
+template <int KT>
+__device__ __forceinline__ void assign_rest(uint64_t mask, int64_t i,
+                                            const uint16_t* __restrict__ keys, int64_t ld, int d,
+                                            const float* __restrict__ centroids, int nlist,
+                                            int cosine, int32_t* __restrict__ out_list) {
+    while (mask) {
+        const int src = __builtin_ctzll(mask);
+        mask &= mask - 1;
+        const int64_t key = __shfl(i, src, 64);
+        const int l = assign_one<KT>(keys + key * ld, d, centroids, nlist, cosine);
+        if ((int)(threadIdx.x & 63) == src) out_list[key] = l;
+    }
 }
 
 // out_list[i] = argmax_l sim(key i, centroid l); ties to the lower l.
@@ -130,7 +167,8 @@ __device__ __forceinline__ void two_parts(float x, _Float16& hi, _Float16& lo) {
 
 // Keys base + 16 t + col as B fragments (k = 8 grp + 32 ks .. + 7), scaled;
 // rows past n re-read row n - 1.  unscale[t] undoes the scale; bit t of the
-// result: the key's squared norm is an ordinary number.
+// result: the products serve the key, whose squared norm is an ordinary number,
+// or which is zero (every score is 0 or NaN) or holds a NaN (every score is).
 template <int KT, int KS, int T>
 __device__ __forceinline__ uint32_t load_keys(const uint16_t* __restrict__ keys, int64_t base,
                                               int64_t n, int d, int64_t ld, f16x8 (&kf)[T][KS],
@@ -164,7 +202,7 @@ __device__ __forceinline__ uint32_t load_keys(const uint16_t* __restrict__ keys,
         xn += __shfl_xor(xn, 32, 64);
         big = __builtin_fmaxf(big, __shfl_xor(big, 16, 64));
         big = __builtin_fmaxf(big, __shfl_xor(big, 32, 64));
-        plain |= (xn > 0x1p-100f && xn < 0x1p100f) ? 1u << t : 0u;
+        plain |= ((xn > 0x1p-100f && xn < 0x1p100f) || big == 0.0f || xn != xn) ? 1u << t : 0u;
         const int sh = shift_to_14(big);
         unscale[t] = __builtin_ldexpf(1.0f, -sh);
 #pragma unroll
@@ -209,13 +247,6 @@ __device__ __forceinline__ void tile_products(int l0, const f16x8 (&hi)[KS], con
         asm volatile("" : "+v"(row0[t]));
         if (t % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // registers: four sums
     }
-}
-
-// The better of (b, r) and (ob, orow): the larger score, the lower row on a tie.
-__device__ __forceinline__ void take_better(float& b, int& r, float ob, int orow) {
-    const bool up = ob > b || (ob == b && orow < r);
-    b = up ? ob : b;
-    r = up ? orow : r;
 }
 
 // The best group of four rows of each key over the four lanes that hold it.
@@ -385,8 +416,9 @@ __global__ __launch_bounds__(512) void assign_stage_kernel(
         const int64_t i = base + 16 * t + col;
         const uint16_t* row = keys + (i < n ? i : n - 1) * ld;
         const int l = settle<KT, COS>(row, d, centroids, nlist, r + grp, 16);
-        if (grp == 0 && i < n)
-            out_list[i] = (plain >> t) & 1u ? l : assign_one<KT>(row, d, centroids, nlist, COS);
+        const bool mine = grp == 0 && i < n, served = (plain >> t) & 1u;
+        if (mine && served) out_list[i] = l;
+        assign_rest<KT>(__ballot(mine && !served), i, keys, ld, d, centroids, nlist, COS, out_list);
     }
 }
 
@@ -491,7 +523,8 @@ __global__ __launch_bounds__(512) void assign_split_kernel(
         }
     }
     __syncthreads();
-    // Four lanes per key: the best group of all waves, then one row each.
+    // Four lanes per key: the best group of all waves, then one row each (whole
+    // waves: 64 T keys' lanes).
     for (int u = tid; u < 64 * T; u += 64 * W) {
         const int key = u >> 2;
         const int64_t i = base + key;
@@ -502,8 +535,9 @@ __global__ __launch_bounds__(512) void assign_split_kernel(
         for (int w = 1; w < W; ++w) take_better(b, r, s_best[w][key], s_row0[w][key]);
         const uint16_t* row = keys + (i < n ? i : n - 1) * ld;
         const int l = settle<KT, COS>(row, d, centroids, nlist, (served ? r : 0) + (u & 3), 1);
-        if ((u & 3) == 0 && i < n)
-            out_list[i] = served ? l : assign_one<KT>(row, d, centroids, nlist, COS);
+        const bool mine = (u & 3) == 0 && i < n;
+        if (mine && served) out_list[i] = l;
+        assign_rest<KT>(__ballot(mine && !served), i, keys, ld, d, centroids, nlist, COS, out_list);
     }
 }
 

@@ -400,3 +400,84 @@ def test_build_kernel_edges(case):
             assert bool((near | ~rows[i0:i0 + (1 << 15)]).all()), f"slice {j} from row {i0}"
         if ksub > 8:
             assert not bool((codes[:, j] == 8).any())
+
+
+def _special_keys(n, d, dt, g, cen):
+    """Ordinary keys with rows that a norm or a product cannot serve: zero,
+    infinite, NaN, and squared norms that overflow or vanish in fp32 (bf16)."""
+    lab = torch.randint(0, cen.shape[0], (n,), generator=g, device=DEV)
+    keys = cen[lab] + 0.5 * torch.randn(n, d, generator=g, device=DEV)
+    kind = torch.randint(0, 60, (n,), generator=g, device=DEV)
+    kind[0], kind[n - 1] = 0, 1                        # the first and the last row among them
+    keys[kind == 0] = 0.0
+    keys[kind == 1, 1] = float("inf")
+    keys[kind == 2, d - 1] = float("-inf")
+    keys[kind == 3, 0] = float("nan")
+    keys[kind == 4, 0] = float("inf")
+    keys[kind == 4, 1] = float("inf")
+    if dt == torch.bfloat16:
+        keys[kind == 5] *= 1e25
+        keys[kind == 6] *= 1e-30
+        keys[kind == 7] *= 1e18
+        keys[kind == 8] *= 1e-18
+    return keys.to(dt), kind
+
+
+@pytest.mark.parametrize("metric", ["cosine", "ip"])
+@pytest.mark.parametrize("n,d,nlist,kdt", [(2_000, 64, 130, "bf16"), (2_000, 8, 70, "f16"),
+                                           (300_001, 32, 65, "bf16"), (80_001, 128, 100, "f16")])
+def test_assign_rows_without_an_ordinary_norm(n, d, nlist, kdt, metric):
+    """The list of a key is the first centroid whose fp32 score no other exceeds;
+    list 0 where no score is a number above -inf."""
+    print(f"[ivf-assign-special] n={n} d={d} nlist={nlist} {kdt} {metric}", flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n + d)
+    cen = torch.randn(nlist, d, generator=g, device=DEV)
+    keys, kind = _special_keys(n, d, {"bf16": torch.bfloat16, "f16": torch.float16}[kdt], g, cen)
+    got = sense.sense_ivf_assign(keys, cen, metric).cpu().long()
+    rows = torch.nonzero(kind < 10).view(-1).cpu()
+    x, c = keys[rows.to(DEV)].float().cpu(), cen.cpu()
+    s = torch.empty((len(rows), nlist))
+    for i in range(0, len(rows), 512):
+        s[i:i + 512] = (x[i:i + 512, None, :] * c[None]).sum(dim=2)
+    wide = x.double() @ c.double().T
+    plain = torch.isfinite(s) & torch.isfinite(wide)
+    if metric == "cosine":
+        xn = (x * x).sum(dim=1)
+        s = s * (1.0 / c.norm(dim=1)) * torch.where(xn > 0, 1.0 / xn.sqrt(), torch.zeros(()))[:, None]
+    best = s.nan_to_num(nan=-float("inf"), posinf=float("inf"), neginf=-float("inf"))
+    top = best.max(dim=1).values
+    want = (best == top[:, None]).int().argmax(dim=1)
+    mine = best.gather(1, got[rows][:, None])[:, 0]
+    # Ordinary scores may change places within the sums' rounding (see
+    # test_build_kernel_edges); the others are exact.
+    exact = ~(plain.all(dim=1) & (top != 0))
+    assert torch.equal(got[rows][exact], want[exact])
+    near = top - mine <= 2 * (d + 8) * 2.0 ** -23 * (
+        (x.norm(dim=1) * c.norm(dim=1).max()) if metric == "ip" else torch.ones(len(rows)))
+    assert bool((near | exact).all())
+
+
+def test_assign_time_with_zero_keys():
+    """Zero keys (padding rows, empty embeddings) take the lists' ordinary path:
+    a store with one in a hundred of them is assigned in about the time of a
+    store without (one lane walking all centroids for each took 180 times it)."""
+    n, d, nlist = 262_144, 64, 4096
+    g = torch.Generator(device=DEV)
+    g.manual_seed(4)
+    cen = torch.randn(nlist, d, generator=g, device=DEV)
+    plain = torch.randn(n, d, generator=g, device=DEV).to(torch.bfloat16)
+    zeros = plain.clone()
+    zeros[torch.rand(n, generator=g, device=DEV) < 0.01] = 0.0
+    out = torch.empty(n, dtype=torch.int32, device=DEV)
+    best = {}
+    for name, keys in (("plain", plain), ("zeros", zeros)):
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            sense.sense_ivf_assign(keys, cen, "cosine", out=out)
+            b.record()
+            b.synchronize()
+            best[name] = min(best.get(name, 1e9), a.elapsed_time(b))
+    print(f"[ivf-assign-zeros] {best['plain']:.3f} ms, {best['zeros']:.3f} with zero keys", flush=True)
+    assert best["zeros"] < 3 * best["plain"]
