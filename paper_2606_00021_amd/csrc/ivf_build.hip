@@ -11,8 +11,8 @@ namespace {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 template <int KT>
 __device__ __forceinline__ float elem_f32(uint32_t bits) {
@@ -21,13 +21,6 @@ __device__ __forceinline__ float elem_f32(uint32_t bits) {
 }
 
 // ------------------------------------------------------------- assignment
-// The shift that brings a value's leading bit to 2^14 (0 for zero, infinity
-// and NaN, which stay as they are).
-__device__ __forceinline__ int shift_to_14(float big) {
-    const int ex = (int)(__builtin_bit_cast(uint32_t, big) >> 23) - 127;
-    return (ex > -127 && ex < 128) ? 14 - ex : 0;
-}
-
 // The better of (b, r) and (ob, orow): the larger score, the lower row on a tie.
 __device__ __forceinline__ void take_better(float& b, int& r, float ob, int orow) {
     const bool up = ob > b || (ob == b && orow < r);
@@ -101,20 +94,19 @@ __device__ __forceinline__ void assign_rest(uint64_t mask, int64_t i,
 
 // out_list[i] = argmax_l sim(key i, centroid l); ties to the lower l.
 //
-// Bound: the matrix cores (n * nlist * d products, twice) and, beside them, the
-// vector ALUs that prepare the centroids, in fp16 for both key types.  A key
-// is scaled by a power of two that brings its largest element to [2^14, 2^15):
-// fp16 keys and the 8-bit mantissas of bf16 are then exact down to 2^-32 of
-// that element (and to 2^-40 of it below); a positive factor does not change
-// the key's best centroid.  An fp32 centroid (normalised first under cosine;
-// scaled likewise under inner product, whose scores are scaled back) is taken
-// in two rounded fp16 parts, which leave 2^-24 of each element: the rounding
-// of one fp32 operation.  Products are exact and summed in the fp32
-// accumulators, the small part first.  A lane keeps the best score of its own
-// four rows of every 16-centroid tile and the tile it came from (strictly
-// greater, in ascending order), five instructions per four scores; at the end
-// the lanes (and waves) merge per key, and four lanes settle which of the
-// winning four rows it was, one row each, in fp32.
+// Bound: the matrix cores and, beside them, the vector ALUs that prepare the
+// centroids.  Operands are bfloat16, whose exponents are those of fp32, so that
+// a value is the exact sum of its leading 8 bits, the next 8 and the rest: an
+// fp32 centroid (normalised first under cosine) goes in as three parts, an fp16
+// key as two, a bf16 key as it is.  Nothing is scaled and no bit of either side
+// is left out; the products are exact and summed in the fp32 accumulators, the
+// small parts first.  (Two fp16 parts of a scaled centroid leave up to 2^-23 of
+// an element, and of one below 2^-17 of its row's largest only 2^-39 of that
+// largest.)  A lane keeps the best score of its own four rows of every
+// 16-centroid tile and the tile it came from (strictly greater, in ascending
+// order), five instructions per four scores; at the end the lanes (and waves)
+// merge per key, and four lanes settle which of the winning four rows it was,
+// one row each, in fp32.
 //
 // Two ways to share the centroids:
 //   assign_stage: a wave has its own T tiles of 16 keys; the block's waves
@@ -127,11 +119,13 @@ __device__ __forceinline__ void assign_rest(uint64_t mask, int64_t i,
 //     out the centroids, 16 at a time, each preparing its tile in registers:
 //     more preparation per key, but no barrier, and 16 T keys fill a block.
 //
-// 4096 centroids, 64 dims, bf16: 262144 keys 2639 us with one thread per key
-// on the VALU, 291 us staged (0.95 PFLOP/s; a large torch matrix product
-// reaches 1.2), 652 split; 16384 keys 1617, 115 and 43 us.
+// 4096 centroids, 64 dims, cosine: 262144 bf16 keys 2340 us with one thread per
+// key on the VALU, 338 us staged (1.22 PFLOP/s of products; a large torch matrix
+// product reaches 1.2 to 1.4), 561 split; 16384 keys 1614, 136 (two key tiles a
+// wave) and 42 us.  fp16 keys, twice the products: 262144 587 us staged, 16384
+// 53 us split.
 
-// The sum or maximum over the G consecutive lanes of a group (G 8, 16 or 32).
+// The sum over the G consecutive lanes of a group (G 8, 16 or 32).
 template <int CTRL>
 __device__ __forceinline__ float dpp(float x) {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x),
@@ -146,35 +140,53 @@ __device__ __forceinline__ float group_sum(float x) {
     if constexpr (G >= 32) x += __shfl_xor(x, 16, 64);
     return x;
 }
-template <int G>
-__device__ __forceinline__ float group_max(float x) {
-    x = __builtin_fmaxf(x, dpp<0xB1>(x));
-    x = __builtin_fmaxf(x, dpp<0x4E>(x));
-    x = __builtin_fmaxf(x, dpp<0x141>(x));
-    if constexpr (G >= 16) x = __builtin_fmaxf(x, dpp<0x140>(x));
-    if constexpr (G >= 32) x = __builtin_fmaxf(x, __shfl_xor(x, 16, 64));
-    return x;
-}
-
-// The two fp16 parts of x.  No contraction with the product x may come from:
-// the part and the rest must be those of the same rounded number.
-__device__ __forceinline__ void two_parts(float x, _Float16& hi, _Float16& lo) {
+// x as the exact sum of three bfloat16 values (the upper halves of part[0 .. 2]):
+// its leading 8 bits, the next 8, and the rest.  An infinite x is its first part.
+__device__ __forceinline__ void three_parts(float x, uint32_t (&part)[3]) {
 #pragma clang fp contract(off)
-    asm volatile("" : "+v"(x));
-    hi = (_Float16)x;
-    lo = (_Float16)(__builtin_fabsf(x) == __builtin_inff() ? 0.0f : x - (float)hi);
+    asm volatile("" : "+v"(x));    // one rounded number, not the product it may come from
+    part[0] = __builtin_bit_cast(uint32_t, x) & 0xFFFF0000u;
+    const float r = __builtin_fabsf(x) == __builtin_inff()
+                        ? 0.0f
+                        : x - __builtin_bit_cast(float, part[0]);
+    part[1] = __builtin_bit_cast(uint32_t, r) & 0xFFFF0000u;
+    part[2] = __builtin_bit_cast(uint32_t, r - __builtin_bit_cast(float, part[1]));
 }
 
-// Keys base + 16 t + col as B fragments (k = 8 grp + 32 ks .. + 7), scaled;
-// rows past n re-read row n - 1.  unscale[t] undoes the scale; bit t of the
-// result: the products serve the key, whose squared norm is an ordinary number,
-// or which is zero (every score is 0 or NaN) or holds a NaN (every score is).
+// The upper halves of two words, that of b on top.
+__device__ __forceinline__ uint32_t upper_halves(uint32_t a, uint32_t b) {
+    return __builtin_amdgcn_perm(b, a, 0x07060302u);
+}
+
+__device__ __forceinline__ f32x4 mfma(const u32x4& a, const u32x4& b, const f32x4& c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a),
+                                                   __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+
+// The first part of an fp16 key's element (11 bits): its leading 8 bits, or the
+// bfloat16 below where these are all of it, so that no part of a number is 0
+// (which an infinite centroid element would turn into NaN).
+__device__ __forceinline__ uint32_t key_part(float x) {
+    const uint32_t b = __builtin_bit_cast(uint32_t, x);
+    return x == 0.0f ? 0u : (b - 1u) & 0xFFFF0000u;
+}
+
+constexpr int kParts = 3;                          // of a centroid
+// Parts of a key: 8 + 3 bits of an fp16 one.
+template <int KT>
+constexpr int kKeyParts = KT == DT_F16 ? 2 : 1;
+
+// Keys base + 16 t + col as B fragments (k = 8 grp + 32 ks .. + 7); rows past n
+// re-read row n - 1.  Bit t of the result: the products serve the key, whose
+// squared norm is an ordinary number (no sum of its products overflows or
+// vanishes where the definition's does not), or which is zero (every score is 0
+// or NaN) or holds a NaN (every score is).
 template <int KT, int KS, int T>
 __device__ __forceinline__ uint32_t load_keys(const uint16_t* __restrict__ keys, int64_t base,
-                                              int64_t n, int d, int64_t ld, f16x8 (&kf)[T][KS],
-                                              float (&unscale)[T]) {
+                                              int64_t n, int d, int64_t ld,
+                                              u32x4 (&kf)[T][KS][kKeyParts<KT>]) {
     const int lane = threadIdx.x & 63, col = lane & 15, grp = lane >> 4;
-    uint32_t plain = 0;
+    uint32_t served = 0;
 #pragma unroll
     for (int t = 0; t < T; ++t) {
         const int64_t i = base + 16 * t + col;
@@ -192,51 +204,50 @@ __device__ __forceinline__ uint32_t load_keys(const uint16_t* __restrict__ keys,
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const uint32_t w = kw[ks][j];
-                const float lo = elem_f32<KT>(w & 0xFFFFu), hi = elem_f32<KT>(w >> 16);
-                xn = __builtin_fmaf(lo, lo, xn);
-                xn = __builtin_fmaf(hi, hi, xn);
-                big = __builtin_fmaxf(big, __builtin_fmaxf(__builtin_fabsf(lo), __builtin_fabsf(hi)));
+                const float x0 = elem_f32<KT>(w & 0xFFFFu), x1 = elem_f32<KT>(w >> 16);
+                xn = __builtin_fmaf(x0, x0, xn);
+                xn = __builtin_fmaf(x1, x1, xn);
+                big = __builtin_fmaxf(big, __builtin_fmaxf(__builtin_fabsf(x0), __builtin_fabsf(x1)));
+                if constexpr (KT == DT_F16) {
+                    const uint32_t b0 = key_part(x0), b1 = key_part(x1);
+                    kf[t][ks][0][j] = upper_halves(b0, b1);
+                    kf[t][ks][kKeyParts<KT> - 1][j] = upper_halves(
+                        __builtin_bit_cast(uint32_t, x0 - __builtin_bit_cast(float, b0)),
+                        __builtin_bit_cast(uint32_t, x1 - __builtin_bit_cast(float, b1)));
+                } else {
+                    kf[t][ks][0][j] = w;
+                }
             }
         }
         xn += __shfl_xor(xn, 16, 64);
         xn += __shfl_xor(xn, 32, 64);
         big = __builtin_fmaxf(big, __shfl_xor(big, 16, 64));
         big = __builtin_fmaxf(big, __shfl_xor(big, 32, 64));
-        plain |= ((xn > 0x1p-100f && xn < 0x1p100f) || big == 0.0f || xn != xn) ? 1u << t : 0u;
-        const int sh = shift_to_14(big);
-        unscale[t] = __builtin_ldexpf(1.0f, -sh);
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t w = kw[ks][j];
-                kf[t][ks][2 * j] = (_Float16)__builtin_ldexpf(elem_f32<KT>(w & 0xFFFFu), sh);
-                kf[t][ks][2 * j + 1] = (_Float16)__builtin_ldexpf(elem_f32<KT>(w >> 16), sh);
-            }
+        served |= ((xn > 0x1p-100f && xn < 0x1p100f) || big == 0.0f || xn != xn) ? 1u << t : 0u;
         if (t % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // registers: four tiles' loads
     }
-    return plain;
+    return served;
 }
 
-// The products of one centroid tile (first row l0, parts hi and lo, inner
-// product: f[i] undoes the scale of row 4 grp + i) with T key tiles.
-template <int KS, int T, bool COS>
-__device__ __forceinline__ void tile_products(int l0, const f16x8 (&hi)[KS], const f16x8 (&lo)[KS],
-                                              const float (&f)[4], const f16x8 (&kf)[T][KS],
-                                              const float (&unscale)[T], float (&best)[T],
-                                              int (&row0)[T]) {
+// The products of one centroid tile (first row l0, its parts in `a`) with T key
+// tiles.
+template <int KT, int KS, int T>
+__device__ __forceinline__ void tile_products(int l0, const u32x4 (&a)[kParts][KS],
+                                              const u32x4 (&kf)[T][KS][kKeyParts<KT>],
+                                              float (&best)[T], int (&row0)[T]) {
+    constexpr int KP = kKeyParts<KT>;
 #pragma unroll
     for (int t = 0; t < T; ++t) {
         f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+        // Parts p of the centroid and u of the key: a product's size falls with
+        // p + u.
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(lo[ks], kf[t][ks], acc, 0, 0, 0);
+        for (int o = kParts + KP - 2; o >= 0; --o)
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi[ks], kf[t][ks], acc, 0, 0, 0);
-        if constexpr (!COS)
+            for (int p = kParts - 1; p >= 0; --p)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) acc[i] = (acc[i] * unscale[t]) * f[i];
+                for (int ks = 0; ks < KS; ++ks)
+                    if (o - p >= 0 && o - p < KP) acc = mfma(a[p][ks], kf[t][ks][o - p], acc);
         const float m = __builtin_fmaxf(__builtin_fmaxf(acc[0], acc[1]),
                                         __builtin_fmaxf(acc[2], acc[3]));
         const bool up = m > best[t];
@@ -298,8 +309,7 @@ __global__ __launch_bounds__(512) void assign_stage_kernel(
     constexpr int CPP = 64 * W / 2 / LPC;          // centroids per pass of half the waves
     constexpr int NP = kTileC / 2 / CPP;           // passes over half a stage
     static_assert(LPC <= 64 && 2 * NP * CPP == kTileC, "staging shape");
-    __shared__ f16x8 s_a[2][CT][KS][2][64];
-    __shared__ float s_f[2][kTileC];               // inner product: undoes the row's scale
+    __shared__ u32x4 s_a[2][CT][kParts][KS][64];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool early = wv < W / 2;                 // waves w and w + 4 share a SIMD
@@ -331,43 +341,30 @@ __global__ __launch_bounds__(512) void assign_stage_kernel(
 #pragma unroll
                 for (int t = 0; t < 4; ++t) cn = __builtin_fmaf(x[t], x[t], cn);
                 cn = group_sum<LPC>(cn);
-                const float mul = (cn > 0.0f) ? 0x1p14f / __builtin_sqrtf(cn) : 0.0f;
+                const float mul = (cn > 0.0f) ? 1.0f / __builtin_sqrtf(cn) : 0.0f;
 #pragma unroll
                 for (int t = 0; t < 4; ++t) x[t] = x[t] * mul;
-            } else {
-                float big = 0.0f;
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const float v = __builtin_fabsf(x[t]);
-                    big = __builtin_fmaxf(big, v < __builtin_inff() ? v : 0.0f);
-                }
-                const int sh = shift_to_14(group_max<LPC>(big));
-#pragma unroll
-                for (int t = 0; t < 4; ++t) x[t] = __builtin_ldexpf(x[t], sh);
-                if (sd == 0) s_f[buf][r] = __builtin_ldexpf(1.0f, -sh);
             }
-            f16x4 hi, lo;
+            uint32_t part[4][kParts];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
+            for (int t = 0; t < 4; ++t)
                 // Rows past the last centroid score NaN: never the best.
-                _Float16 h, l;
-                two_parts(l0 + r < nlist ? x[t] : __builtin_nanf(""), h, l);
-                hi[t] = h;
-                lo[t] = l;
-            }
+                three_parts(l0 + r < nlist ? x[t] : __builtin_nanf(""), part[t]);
             // A[row r % 16][k = sd % 32 ..]: lane 16 * ((sd % 32) / 8) + r % 16.
             const int al = 16 * ((sd & 31) >> 3) + (r & 15);
             const int half = (sd >> 2) & 1;
-            ((f16x4*)&s_a[buf][r >> 4][sd >> 5][0][al])[half] = hi;
-            ((f16x4*)&s_a[buf][r >> 4][sd >> 5][1][al])[half] = lo;
+#pragma unroll
+            for (int q = 0; q < kParts; ++q)
+                ((u32x2*)&s_a[buf][r >> 4][q][sd >> 5][al])[half] =
+                    u32x2{upper_halves(part[0][q], part[1][q]), upper_halves(part[2][q], part[3][q])};
         }
     };
 
     request(0);
-    f16x8 kf[T][KS];
-    float unscale[T], best[T];
+    u32x4 kf[T][KS][kKeyParts<KT>];
+    float best[T];
     int row0[T];                                   // first row of the best's 16-row tile
-    const uint32_t plain = load_keys<KT, KS, T>(keys, base, n, d, ld, kf, unscale);
+    const uint32_t plain = load_keys<KT, KS, T>(keys, base, n, d, ld, kf);
 #pragma unroll
     for (int t = 0; t < T; ++t) {
         best[t] = -__builtin_inff();
@@ -387,17 +384,12 @@ __global__ __launch_bounds__(512) void assign_stage_kernel(
         }
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
-            f16x8 hi[KS], lo[KS];
-            float f[4] = {};
+            u32x4 a[kParts][KS];
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-                hi[ks] = s_a[buf][c][ks][0][lane];
-                lo[ks] = s_a[buf][c][ks][1][lane];
-            }
-            if constexpr (!COS)
+            for (int p = 0; p < kParts; ++p)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) f[i] = s_f[buf][16 * c + 4 * grp + i];
-            tile_products<KS, T, COS>(l0 + 16 * c, hi, lo, f, kf, unscale, best, row0);
+                for (int ks = 0; ks < KS; ++ks) a[p][ks] = s_a[buf][c][p][ks][lane];
+            tile_products<KT, KS, T>(l0 + 16 * c, a, kf, best, row0);
         }
         if (!early && more) stage(l0 + kTileC, buf ^ 1);
         __syncthreads();
@@ -450,23 +442,20 @@ __global__ __launch_bounds__(512) void assign_split_kernel(
         }
     };
     request(wv);
-    f16x8 kf[T][KS];
-    float unscale[T], best[T];
+    u32x4 kf[T][KS][kKeyParts<KT>];
+    float best[T];
     int row0[T];
-    const uint32_t plain = load_keys<KT, KS, T>(keys, base, n, d, ld, kf, unscale);
+    const uint32_t plain = load_keys<KT, KS, T>(keys, base, n, d, ld, kf);
 #pragma unroll
     for (int t = 0; t < T; ++t) {
         best[t] = -__builtin_inff();
         row0[t] = 0;
     }
     for (int tile = wv; tile < ntiles; tile += W) {
-        // Normalise or scale, and split.  Rows past the last centroid become
-        // NaN: their scores are never the best.
-        f16x8 hi[KS], lo[KS];
-        float f[4] = {};
+        // Normalise, and split.  Rows past the last centroid become NaN: their
+        // scores are never the best.
         const bool real = tile * 16 + col < nlist;
-        float mul = 0.0f;                          // cosine: 2^14 / norm
-        int sh = 0;
+        float mul = 1.0f;
         if constexpr (COS) {
             float cn = 0.0f;
 #pragma unroll
@@ -478,39 +467,27 @@ __global__ __launch_bounds__(512) void assign_split_kernel(
             }
             cn += __shfl_xor(cn, 16, 64);
             cn += __shfl_xor(cn, 32, 64);
-            mul = (cn > 0.0f) ? 0x1p14f / __builtin_sqrtf(cn) : 0.0f;
-        } else {
-            float big = 0.0f;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const float v = __builtin_fabsf(raw[ks][j]);
-                    big = __builtin_fmaxf(
-                        big, (v < __builtin_inff() && 8 * grp + 32 * ks < d) ? v : 0.0f);
-                }
-            big = __builtin_fmaxf(big, __shfl_xor(big, 16, 64));
-            big = __builtin_fmaxf(big, __shfl_xor(big, 32, 64));
-            sh = shift_to_14(big);
-            const float inv = __builtin_ldexpf(1.0f, -sh);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) f[i] = __shfl(inv, 4 * grp + i, 64);
+            mul = (cn > 0.0f) ? 1.0f / __builtin_sqrtf(cn) : 0.0f;
         }
+        u32x4 a[kParts][KS];
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
             const bool in = 8 * grp + 32 * ks < d;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                float v = in ? raw[ks][j] : 0.0f;
-                v = COS ? v * mul : __builtin_ldexpf(v, sh);
-                _Float16 h, l;
-                two_parts(real ? v : __builtin_nanf(""), h, l);
-                hi[ks][j] = h;
-                lo[ks][j] = l;
+            for (int j = 0; j < 4; ++j) {
+                uint32_t part[2][kParts];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    float v = in ? raw[ks][2 * j + h] : 0.0f;
+                    if constexpr (COS) v = v * mul;
+                    three_parts(real ? v : __builtin_nanf(""), part[h]);
+                }
+#pragma unroll
+                for (int q = 0; q < kParts; ++q) a[q][ks][j] = upper_halves(part[0][q], part[1][q]);
             }
         }
         if (tile + W < ntiles) request(tile + W);
-        tile_products<KS, T, COS>(tile * 16, hi, lo, f, kf, unscale, best, row0);
+        tile_products<KT, KS, T>(tile * 16, a, kf, best, row0);
     }
 #pragma unroll
     for (int t = 0; t < T; ++t) {
@@ -656,12 +633,13 @@ hipError_t assign_shape(const void* keys, int64_t n, int d, int64_t ld, const fl
 }
 
 // The shape with the least time, from its blocks per compute unit.  Measured
-// at 64 dims and 4096 centroids (us): split with 4 tiles 43 at 16384 keys, 153
-// at 65536; staged with 2 tiles 115 at 16384, 122 at 65536, 186 at 131072;
-// staged with 4 tiles 169 at 131072, 291 at 262144.  Fewer centroids and other
-// dims scale all three alike (50000 x 64 x 512: 38, 29, 44; 100000 x 32 x
-// 1000: 51, 37, 38).  Eight tiles per wave are no faster than four (287 at
-// 262144): two waves a SIMD are then all that fit.
+// at 64 dims and 4096 centroids, bf16 keys (us): split with 4 tiles 42 at 16384
+// keys, 76 at 32768, 146 at 65536; staged with 2 tiles 136 at 16384, 139 at
+// 65536, 206 at 98304, 221 at 131072; staged with 4 tiles 187 at 98304, 196 at
+// 131072, 338 at 262144 (432 with 2).  fp16 keys: split 53, 103, 203; 2 tiles
+// 174, 186, 279, 307; 4 tiles 277, 295, 586 (599).  Fewer centroids and other
+// dims scale all three alike (50000 x 32 x 1024: 27, 26, 37; 131072 x 128 x 1024:
+// 206, 132, 136).
 template <int KT, int KD>
 hipError_t assign_dim(const void* keys, int64_t n, int d, int64_t ld, const float* centroids,
                       int nlist, int cosine, int32_t* out_list, hipStream_t stream) {

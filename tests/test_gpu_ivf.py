@@ -424,16 +424,22 @@ def _special_keys(n, d, dt, g, cen):
 
 
 @pytest.mark.parametrize("metric", ["cosine", "ip"])
+@pytest.mark.parametrize("inf_centroid", [False, True])
 @pytest.mark.parametrize("n,d,nlist,kdt", [(2_000, 64, 130, "bf16"), (2_000, 8, 70, "f16"),
                                            (300_001, 32, 65, "bf16"), (80_001, 128, 100, "f16")])
-def test_assign_rows_without_an_ordinary_norm(n, d, nlist, kdt, metric):
+def test_assign_rows_without_an_ordinary_norm(n, d, nlist, kdt, inf_centroid, metric):
     """The list of a key is the first centroid whose fp32 score no other exceeds;
-    list 0 where no score is a number above -inf."""
-    print(f"[ivf-assign-special] n={n} d={d} nlist={nlist} {kdt} {metric}", flush=True)
+    list 0 where no score is a number above -inf.  With infinite centroid elements
+    (of both signs) the infinite scores of ordinary keys count."""
+    print(f"[ivf-assign-special] n={n} d={d} nlist={nlist} {kdt} {metric} {inf_centroid}",
+          flush=True)
     g = torch.Generator(device=DEV)
     g.manual_seed(n + d)
     cen = torch.randn(nlist, d, generator=g, device=DEV)
-    keys, kind = _special_keys(n, d, {"bf16": torch.bfloat16, "f16": torch.float16}[kdt], g, cen)
+    clean = cen.clone()
+    if inf_centroid:
+        cen[20, 3], cen[41, 6], cen[0, 2] = float("inf"), float("-inf"), float("nan")
+    keys, kind = _special_keys(n, d, {"bf16": torch.bfloat16, "f16": torch.float16}[kdt], g, clean)
     got = sense.sense_ivf_assign(keys, cen, metric).cpu().long()
     rows = torch.nonzero(kind < 10).view(-1).cpu()
     x, c = keys[rows.to(DEV)].float().cpu(), cen.cpu()
@@ -441,7 +447,7 @@ def test_assign_rows_without_an_ordinary_norm(n, d, nlist, kdt, metric):
     for i in range(0, len(rows), 512):
         s[i:i + 512] = (x[i:i + 512, None, :] * c[None]).sum(dim=2)
     wide = x.double() @ c.double().T
-    plain = torch.isfinite(s) & torch.isfinite(wide)
+    plain = torch.isfinite(x).all(dim=1)[:, None] & (torch.isfinite(wide) == torch.isfinite(s))
     if metric == "cosine":
         xn = (x * x).sum(dim=1)
         s = s * (1.0 / c.norm(dim=1)) * torch.where(xn > 0, 1.0 / xn.sqrt(), torch.zeros(()))[:, None]
@@ -451,10 +457,10 @@ def test_assign_rows_without_an_ordinary_norm(n, d, nlist, kdt, metric):
     mine = best.gather(1, got[rows][:, None])[:, 0]
     # Ordinary scores may change places within the sums' rounding (see
     # test_build_kernel_edges); the others are exact.
-    exact = ~(plain.all(dim=1) & (top != 0))
+    exact = ~(plain.all(dim=1) & (top != 0) & torch.isfinite(top))
     assert torch.equal(got[rows][exact], want[exact])
     near = top - mine <= 2 * (d + 8) * 2.0 ** -23 * (
-        (x.norm(dim=1) * c.norm(dim=1).max()) if metric == "ip" else torch.ones(len(rows)))
+        (x.norm(dim=1) * clean.cpu().norm(dim=1).max()) if metric == "ip" else torch.ones(len(rows)))
     assert bool((near | exact).all())
 
 
@@ -481,3 +487,37 @@ def test_assign_time_with_zero_keys():
             best[name] = min(best.get(name, 1e9), a.elapsed_time(b))
     print(f"[ivf-assign-zeros] {best['plain']:.3f} ms, {best['zeros']:.3f} with zero keys", flush=True)
     assert best["zeros"] < 3 * best["plain"]
+
+
+@pytest.mark.parametrize("metric", ["cosine", "ip"])
+@pytest.mark.parametrize("kdt", ["bf16", "f16"])
+@pytest.mark.parametrize("small", [2.0 ** -12, 2.0 ** -30])
+def test_assign_keys_in_small_coordinates(small, kdt, metric):
+    """Centroids with one large coordinate, keys that are zero there: the choice
+    rests on coordinates far below the centroids' largest, which count with all
+    their bits.  The list's 64-bit score is the best one but for the rounding of
+    fp32 sums, d + 8 roundings of the terms' magnitudes for either side (norm,
+    scale and sum)."""
+    for n in (3_000, 140_000):                         # both ways to share the centroids
+        d, nlist = 64, 2048
+        print(f"[ivf-assign-small] n={n} small={small:.1e} {kdt} {metric}", flush=True)
+        g = torch.Generator(device=DEV)
+        g.manual_seed(n)
+        cen = small * torch.randn(nlist, d, generator=g, device=DEV)
+        cen[:, 5] = 1.0
+        keys = torch.randn(n, d, generator=g, device=DEV)
+        keys[:, 5] = 0.0
+        keys = keys.to({"bf16": torch.bfloat16, "f16": torch.float16}[kdt])
+        got = sense.sense_ivf_assign(keys, cen, metric).long()
+        torch.cuda.synchronize()
+        c = cen.double() / (cen.double().norm(dim=1, keepdim=True) if metric == "cosine" else 1.0)
+        off = 0
+        for i in range(0, n, 1 << 14):
+            x = keys[i:i + (1 << 14)].double()
+            s, terms = x @ c.T, x.abs() @ c.abs().T
+            best = s.argmax(dim=1, keepdim=True)
+            mine = got[i:i + (1 << 14), None]
+            off += int((best != mine).sum())
+            bound = (d + 8) * 2.0 ** -24 * (terms.gather(1, best) + terms.gather(1, mine))
+            assert bool((s.gather(1, mine) >= s.gather(1, best) - bound).all())
+        print(f"[ivf-assign-small] {off} of {n} lists are not the 64-bit choice", flush=True)
