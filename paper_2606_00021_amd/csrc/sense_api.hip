@@ -93,12 +93,30 @@ struct RetrieveLayout {
     size_t q_off, m_off, s_off, t_off, total;
 };
 
-// Batched queries over short keys: the matrix-core short-key scan, by groups of
-// rows when the store is large.
-// Up to this many rows: plain scores + top-k, with two launches fewer (64
-// queries x 64 dims: 32768 rows 37.6 us so and 42.3 by groups, 65539 rows 48.6
-// and 44.5).
-constexpr int64_t kShortDirectMax = 32768;
+// Batched queries over short keys: the matrix-core short-key scan, either every
+// score and a top-k over them, or by groups of rows.
+// Groups read and select a sixteenth of the scores, and cost two launches and
+// the rescore of k groups: they pay where a pass's score matrix (ng queries by n
+// rows) is large and k is not.  Measured over 64-dim bf16 rows, fp32 queries, us
+// a search of one pass, every score / groups:
+//   k = 64      2 queries   16       33          64
+//     33000     26 / 29     29 / 32  31 / 34     38 / 35
+//     50000     21 / 31     29 / 31  33 / 34     39 / 35
+//     65536     21 / 31     24 / 31  29 / 34     36 / 36
+//     90000     24 / 31     28 / 32  36 / 35     44 / 37
+//     131072    24 / 32     30 / 32  40 / 35     50 / 39
+//   k = 4       64 queries: 33000 35 / 34, 50000 30 / 35, 65536 32 / 35, 90000
+//               41 / 36; 33 queries: 90000 33 / 35, 131072 37 / 36
+//   k = 256     64 queries: 65536 44 / 65, 131072 61 / 70
+// Up to kShortDirectMax rows every score always (32768 x 64 queries, k = 64: 29
+// and 35 us); beyond kShortGroupsMin rows groups always.
+constexpr int64_t kShortDirectMax = 32768, kShortGroupsMin = 131072;
+bool short_by_groups(int64_t n, int ng, int k) {
+    if (n <= kShortDirectMax) return false;
+    if (n > kShortGroupsMin) return true;
+    const int64_t scores = (int64_t)ng * n, unit = (int64_t)1 << 20;
+    return k <= 128 && scores > (k < 32 ? 4 * unit : (n < 65536 ? 2 : 3) * unit);
+}
 constexpr int64_t kShortSample = 32768;     // scores per query of the sample area
 
 bool short_batched(const sense_index* ix, int nq) {
@@ -442,9 +460,9 @@ SENSE_EXPORT sense_status_t sense_retrieve_workspace_size(const sense_index_t* i
     return ok();
 }
 
-// Short keys, query batch: per 64 queries either plain scores + top-k (small
-// stores), or the best score of every group of rows, the k best groups, the
-// scores of their rows and the top k of those.
+// Short keys, query batch: per 64 queries either plain scores + top-k, or the
+// best score of every group of rows, the k best groups, the scores of their rows
+// and the top k of those (short_by_groups).
 static hipError_t retrieve_short(const sense_index* ix, const void* queries, int q_dtype, int nq,
                                  int k, bool split, int64_t* out_ids, float* out_scores,
                                  int32_t* out_drafts, int32_t* out_draft_len, char* ws,
@@ -458,7 +476,6 @@ static hipError_t retrieve_short(const sense_index* ix, const void* queries, int
                                        ws + L.m_off, st)) != hipSuccess)
         return e;
     const sense::QuerySplit qs = sense::query_split_parts(ws + L.m_off, nq, ix->d);
-    const bool direct = n <= kShortDirectMax;
     const int group_rows = sense::short_group_rows(n);
     const int64_t n_groups = (n + group_rows - 1) / group_rows;
     const int n_hits = (int)(k < n_groups ? k : n_groups);
@@ -486,7 +503,7 @@ static hipError_t retrieve_short(const sense_index* ix, const void* queries, int
         float* gsc = out_scores ? out_scores + (int64_t)g0 * k : nullptr;
         int32_t* gdr = out_drafts ? out_drafts + (int64_t)g0 * k * ix->max_span : nullptr;
         int32_t* gdl = out_draft_len ? out_draft_len + (int64_t)g0 * k : nullptr;
-        if (direct) {
+        if (!short_by_groups(n, ng, k)) {
             S.scores = (float*)(ws + L.cand_off);
             if ((e = sense::launch_scan_short(S, st)) != hipSuccess) return e;
             if ((e = sense::launch_topk_gather(S.scores, n, ng, k, ix->spans, ix->span_len,

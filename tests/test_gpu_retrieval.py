@@ -311,7 +311,7 @@ def test_dynamic_cache_batched_sampled(metric):
     cache.close()
 
 
-@pytest.mark.parametrize("d,nq,n", [(64, 3, 40_000), (24, 20, 140_011)])
+@pytest.mark.parametrize("d,nq,n", [(64, 3, 140_003), (24, 50, 60_011)])
 def test_short_batch_norm_beyond_fp32(d, nq, n):
     """Cosine scores of a query whose squared norm overflows fp32 are 0 for a row
     whose product is finite and NaN for one whose product overflows.  A row of
@@ -627,6 +627,16 @@ def test_full_size_batched(name, full_queries):
     (300_007, 24, 5, 1024),
     (140_009, 64, 70, 16),        # two query groups
     (1_048_577, 16, 16, 40),      # groups of 64 rows; more than one block's of them
+    # either side of where groups pay (scores of a pass, k)
+    (131_073, 64, 2, 1),          # groups always: one row in the last group
+    (131_073, 56, 49, 129),       # ... more hit rows than the single-launch tail takes
+    (32_800, 64, 64, 32),         # groups: just over 2^21 scores
+    (32_800, 32, 63, 32),         # every score: just under
+    (65_535, 24, 64, 31),         # every score: fewer than 2^22 with k < 32
+    (65_537, 48, 64, 31),         # groups
+    (65_537, 40, 48, 128),        # groups: just over 3 * 2^20
+    (65_537, 16, 47, 128),        # every score
+    (60_001, 64, 70, 64),         # one pass by groups, the second of six queries not
 ])
 def test_short_groups_are_exact_with_ties(n, d, nq, k, dt):
     """The best groups of rows hold the best rows.  Small whole numbers, so that
@@ -673,3 +683,49 @@ def test_16_bit_queries_of_either_type(n, d, nq, kt, qt):
         assert torch.equal(ids[i].cpu(), order), f"query {i}"
         assert torch.equal(scores[i].cpu().double(), want[i][order])
     index.close()
+
+
+def _replay_us(fn, calls=20):
+    """Device time of a call, from replays of a captured run of them."""
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        fn()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        for _ in range(calls):
+            fn()
+    best = 1e9
+    for _ in range(6):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        graph.replay()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / calls)
+    return best
+
+
+@pytest.mark.parametrize("nq,k", [(2, 4), (16, 1024), (64, 1024)])
+def test_short_batch_time_past_the_plain_scan(nq, k):
+    """A batch over half as many rows again as the plain scan's 32768 takes about
+    as much longer: a search by groups, whose launches and rescore cost more than
+    the scores they save here, took 1.6 to 2.4 times as long."""
+    us = {}
+    for n in (32_768, 50_000):
+        g = torch.Generator(device=DEV)
+        g.manual_seed(n)
+        keys = torch.randn((n, 64), generator=g, device=DEV).to(torch.bfloat16)
+        spans = torch.zeros((n, 4), dtype=torch.int32, device=DEV)
+        q = torch.randn((nq, 64), generator=g, device=DEV)
+        index = sense.sense_build_index(keys, spans, None, metric="cosine")
+        ws = torch.empty(sense.sense_retrieve_workspace_size(index, nq, k), dtype=torch.uint8,
+                         device=DEV)
+        out = tuple(torch.empty(s, dtype=t, device=DEV) for s, t in (
+            ((nq, k), torch.int64), ((nq, k), torch.float32), ((nq, k, 4), torch.int32),
+            ((nq, k), torch.int32)))
+        us[n] = _replay_us(lambda: sense.sense_retrieve(index, q, k, workspace=ws, out=out))
+        index.close()
+    print(f"[short-time] nq={nq} k={k}: {us[32_768]:.1f} us at 32768 rows, {us[50_000]:.1f} at "
+          f"50000", flush=True)
+    assert us[50_000] < 1.45 * us[32_768]
