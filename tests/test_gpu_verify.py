@@ -246,3 +246,76 @@ def test_rows_at_every_alignment_and_step_edge(dtype, v):
     ref = oracle.soft_gate_verify(host_bits(logits.contiguous()), dtype, drafts.numpy(), lens,
                                   n_groups=2)
     check_verify(out, ref, 0.05, lens)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("c,v", [(80, 41_003), (512, 20_001)])
+def test_masked_rows_over_several_steps(dtype, c, v):
+    """Slices of two to six steps of a block: rows masked from their first word
+    on, only behind the first step, only in the last words, at a single logit,
+    and but for the judged token or but for another one."""
+    logits, drafts = structured(47, c, 8, v, dtype=dtype)
+    inf = -float("inf")
+    logits[1, :, 1::3] = inf
+    logits[2, :, v // 2:] = inf
+    logits[3, :, v - 5:] = inf
+    logits[4, :, v // 3] = inf
+    logits[5] = inf
+    logits[5].scatter_(1, drafts[5, :, None].long(), 2.0)
+    logits[6].scatter_(1, drafts[6, :, None].long(), inf)
+    logits[7] = inf
+    logits[7, :, v - 1] = 1.0
+    logits[8, :, : v // 2] = inf
+    logits[9, :, 9000] = float("nan")                  # counts as no logit
+    clean = logits.clone()
+    clean[9, :, 9000] = inf
+    out = sense.sense_soft_gate_verify(logits.to(DEV), drafts.to(DEV), None, n_groups=2)
+    torch.cuda.synchronize()
+    ref = oracle.soft_gate_verify(host_bits(clean.contiguous()), dtype, drafts.numpy(),
+                                  np.full(c, 8, dtype=np.int32), n_groups=2)
+    check_verify(out, ref, 0.05, None)
+
+
+def _verify_us(logits, drafts, n_groups=1, calls=10):
+    """Device time of a call, from replays of a captured run of them."""
+    n, m, v = logits.shape
+    ws = torch.empty(sense.sense_soft_gate_verify_workspace_size(n, m, v), dtype=torch.uint8,
+                     device=DEV)
+    out = sense.sense_soft_gate_verify(logits, drafts, None, n_groups=n_groups, workspace=ws)
+
+    def call():
+        sense.sense_soft_gate_verify(logits, drafts, None, n_groups=n_groups, workspace=ws,
+                                     out=out)
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        for _ in range(calls):
+            call()
+    best = 1e9
+    for _ in range(6):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        graph.replay()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / calls)
+    return best
+
+
+def test_masked_vocabulary_costs_no_second_pass():
+    """A third of the vocabulary at -inf (a grammar's mask): the sums are formed
+    once, as for rows without (both forms one after the other took 1.32 times
+    as long)."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(3)
+    v = 152_064
+    logits = (2.0 * torch.randn((64, 8, v), generator=g, device=DEV)).to(torch.bfloat16)
+    drafts = torch.randint(0, v, (64, 8), generator=g, device=DEV, dtype=torch.int32)
+    plain = _verify_us(logits, drafts)
+    logits.masked_fill_(torch.rand(v, generator=g, device=DEV) < 0.33, -float("inf"))
+    masked = _verify_us(logits, drafts)
+    print(f"[verify-masked] {plain:.1f} us, masked {masked:.1f}", flush=True)
+    assert masked < 1.18 * plain
