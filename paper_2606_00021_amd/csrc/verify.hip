@@ -335,7 +335,11 @@ __device__ __forceinline__ void add_up(u32x4 (&buf)[U], int live, float base,
 // nodes + u, token tree_tokens[item]; it is judged when u < tree_len[group]
 // and its parent is a node of the group (or none), and its logits row is
 // 1 + parent within the group's 1 + nodes rows.
-template <int LT, bool TREE>
+// ONE: a slice is one step, and the kernel requests no other (requests for the
+// two steps behind it, all lanes on the last word, cost as much as the rows:
+// 8192 rows of 1000 bf16 40.0 us with them, 18.6 without; of 8192 bf16 32.6 and
+// 28.0; one row of 500 6.9 and 6.1).
+template <int LT, bool TREE, bool ONE>
 __global__ __launch_bounds__(kRowThreads, 5) void verify_rows_kernel(
     const void* __restrict__ logits, int64_t row_stride, const int32_t* __restrict__ drafts,
     const int32_t* __restrict__ draft_len, int max_len, int vocab, int slice_vecs, int n_slices,
@@ -466,14 +470,18 @@ __global__ __launch_bounds__(kRowThreads, 5) void verify_rows_kernel(
         st.s += s1;
         st.t2 += t1;
     };
-    // Loads past the last step all fall on the share's last word.
-    for (int s = 0; s < steps; s += 2) {
-        load(bb, s + 1);
-        __builtin_amdgcn_sched_barrier(0);
-        absorb(ba, s);
-        load(ba, s + 2);
-        __builtin_amdgcn_sched_barrier(0);
-        if (s + 1 < steps) absorb(bb, s + 1);
+    if constexpr (ONE) {
+        absorb(ba, 0);
+    } else {
+        // Loads past the last step all fall on the share's last word.
+        for (int s = 0; s < steps; s += 2) {
+            load(bb, s + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            absorb(ba, s);
+            load(ba, s + 2);
+            __builtin_amdgcn_sched_barrier(0);
+            if (s + 1 < steps) absorb(bb, s + 1);
+        }
     }
 
     int cnt = 0;
@@ -823,9 +831,11 @@ hipError_t launch_rows_t(const void* logits, int64_t row_stride, const int32_t* 
                          const Plan& pl, Partial* part, const int32_t* tree_parent,
                          const int32_t* tree_len, int nodes, hipStream_t stream) {
     const dim3 grid((unsigned)n_items, (unsigned)pl.n_slices);
-    hipLaunchKernelGGL((verify_rows_kernel<LT, TREE>), grid, dim3(kRowThreads), 0, stream, logits,
-                       row_stride, tokens, draft_len, max_len, vocab, pl.slice_vecs, pl.n_slices,
-                       n_items, part, tree_parent, tree_len, nodes);
+    auto kern = pl.slice_vecs == kStepVecs ? verify_rows_kernel<LT, TREE, true>
+                                           : verify_rows_kernel<LT, TREE, false>;
+    hipLaunchKernelGGL(kern, grid, dim3(kRowThreads), 0, stream, logits, row_stride, tokens,
+                       draft_len, max_len, vocab, pl.slice_vecs, pl.n_slices, n_items, part,
+                       tree_parent, tree_len, nodes);
     return hipGetLastError();
 }
 

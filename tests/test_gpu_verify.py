@@ -319,3 +319,18 @@ def test_masked_vocabulary_costs_no_second_pass():
     masked = _verify_us(logits, drafts)
     print(f"[verify-masked] {plain:.1f} us, masked {masked:.1f}", flush=True)
     assert masked < 1.18 * plain
+
+
+def test_short_rows_are_cheaper_than_long_ones():
+    """Rows of 1000 logits take less than rows of 8192 (both one step of a block):
+    with requests and sums for the words a short row does not have they took
+    longer, 40 us against 33."""
+    us = {}
+    for v in (1000, 8192):
+        g = torch.Generator(device=DEV)
+        g.manual_seed(v)
+        logits = (2.0 * torch.randn((1024, 8, v), generator=g, device=DEV)).to(torch.bfloat16)
+        drafts = torch.randint(0, v, (1024, 8), generator=g, device=DEV, dtype=torch.int32)
+        us[v] = _verify_us(logits, drafts, n_groups=16)
+    print(f"[verify-short] {us}", flush=True)
+    assert us[1000] < us[8192]
