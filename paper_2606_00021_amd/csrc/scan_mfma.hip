@@ -579,48 +579,48 @@ hipError_t launch_tile(const MfmaScan& s, hipStream_t stream) {
     return hipGetLastError();
 }
 
-// WRITE passes over few rows (a strided sample, a small store) with the hi
-// half alone: blocks of 128 keys, so that every compute unit gets one (a
-// block of 256 keys per unit would leave half of them idle on a 32768-row
-// sample, and one unit streams a block at a fraction of the chip's rate).
-template <int KT>
-hipError_t launch_group_narrow(const MfmaScan& s, hipStream_t stream) {
+template <int KT, int T, int P, bool SPLIT>
+hipError_t launch_group_t(const MfmaScan& s, hipStream_t stream) {
     switch ((s.nq + 15) / 16) {
-        case 1: return launch_tile<KT, 1, 1, 4, false>(s, stream);
-        case 2: return launch_tile<KT, 2, 1, 4, false>(s, stream);
-        case 3: return launch_tile<KT, 3, 1, 4, false>(s, stream);
-        default: return launch_tile<KT, 4, 1, 4, false>(s, stream);
+        case 1: return launch_tile<KT, 1, T, P, SPLIT>(s, stream);
+        case 2: return launch_tile<KT, 2, T, P, SPLIT>(s, stream);
+        case 3: return launch_tile<KT, 3, T, P, SPLIT>(s, stream);
+        default: return launch_tile<KT, 4, T, P, SPLIT>(s, stream);
     }
 }
 
-template <int KT, int T, int P>
-hipError_t launch_group_split(const MfmaScan& s, hipStream_t stream) {
-    switch ((s.nq + 15) / 16) {
-        case 1: return launch_tile<KT, 1, T, P, true>(s, stream);
-        case 2: return launch_tile<KT, 2, T, P, true>(s, stream);
-        case 3: return launch_tile<KT, 3, T, P, true>(s, stream);
-        default: return launch_tile<KT, 4, T, P, true>(s, stream);
-    }
-}
-
+// The rows of a block (16 kWaves T) by the rows that a compute unit has; passes
+// that store every score or project.
+//   Up to 128 of them (a strided sample, a small store): blocks of 128 in four
+//   stages, so that every unit gets one and a stage of fewer rows keeps more of
+//   them in flight.
+//   With the hi half alone, up to 192: one block of 256 and not two of 128.
+//   Beyond, four query tiles take 256, which halves the reads of the query
+//   fragments; for up to 48 queries either is ahead by the key dimension and
+//   where the store lies in memory (256 at d = 2048, 13 queries: 0.82 to 1.15
+//   times the time of 128), and 128 stays.
+// us a search in blocks of 128 / 256, 32768, 36000, 49152, 65536, 100003, 131072
+// rows:
+//   64 queries, d 3584   64 / 71  95 / 75  98 / 84  120 / 100  197 / 161  221 / 193
+//               d 4096            105 / 82  120 / 110  141 / 144  245 / 219  241 / 208
+//               d 1024            45 / 40  47 / 43  51 / 49  79 / 71  86 / 83
+//   13 queries, d 3584   54 / 57  79 / 60  82 / 72  90 / 89  138 / 130  167 / 165
+//               d 4096            93 / 70  105 / 102  126 / 137  161 / 165  194 / 196
+//               d 1024            37 / 31  38 / 34  41 / 43  55 / 52  66 / 66
 template <int KT, bool SPLIT>
 hipError_t launch_group(const MfmaScan& s, hipStream_t stream) {
-    if constexpr (!SPLIT)
-        if (s.cand == nullptr && filter_groups(s.n_rows, device_cus()) < (int64_t)device_cus())
-            return launch_group_narrow<KT>(s, stream);
+    const int64_t rows = (s.n_rows + device_cus() - 1) / device_cus();
+    const bool narrow = rows <= 16 * kWaves || (!SPLIT && rows > 24 * kWaves && s.nq <= 48);
+    if (s.cand == nullptr && narrow) return launch_group_t<KT, 1, 4, SPLIT>(s, stream);
     if constexpr (SPLIT) {
         // The query fragments, hi and lo, are read again for every block of
         // rows: as much as half the keys' bytes at 256 rows and 64 queries.
         // Blocks of 512 rows in two stages halve that where a compute unit has
         // the rows (262144 x 4096 onto 64 outputs 443 -> 380 us, 100001 x 1024
-        // 62.3 -> 58.5); where it has not, a stage of fewer rows and more of
-        // them (30000 x 8192 269 us in blocks of 512, 181 of 256, 141 of 128;
-        // 2000 x 4096 120, 79, 57).
-        const int64_t rows = (s.n_rows + device_cus() - 1) / device_cus();
-        if (s.cand == nullptr && rows <= 16 * kWaves)
-            return launch_group_split<KT, 1, 4>(s, stream);
+        // 62.3 -> 58.5); where it has not, smaller ones (30000 x 8192 269 us in
+        // blocks of 512, 181 of 256, 141 of 128; 2000 x 4096 120, 79, 57).
         if (s.cand == nullptr && rows > 32 * kWaves)
-            return launch_group_split<KT, 4, 2>(s, stream);
+            return launch_group_t<KT, 4, 2, SPLIT>(s, stream);
     }
     switch ((s.nq + 15) / 16) {
         case 1: return launch_tile<KT, 1, 2, 4, SPLIT>(s, stream);

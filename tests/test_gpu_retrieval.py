@@ -664,7 +664,10 @@ def test_short_groups_are_exact_with_ties(n, d, nq, k, dt):
 
 @pytest.mark.parametrize("kt,qt", [("bf16", "f16"), ("f16", "bf16"), ("f16", "f16")])
 @pytest.mark.parametrize("n,d,nq", [(5000, 64, 3), (40_001, 24, 20), (6000, 136, 5),
-                                    (140_007, 72, 18)])
+                                    (140_007, 72, 18),
+                                    # either side of the lines between block sizes
+                                    (32_768, 72, 33), (32_769, 136, 13), (49_152, 72, 3),
+                                    (49_153, 72, 48), (49_153, 72, 49)])
 def test_16_bit_queries_of_either_type(n, d, nq, kt, qt):
     """Queries in a 16-bit type, that of the keys or the other one, from a row
     start of any alignment.  Small whole numbers: every score is exact."""
@@ -729,3 +732,27 @@ def test_short_batch_time_past_the_plain_scan(nq, k):
     print(f"[short-time] nq={nq} k={k}: {us[32_768]:.1f} us at 32768 rows, {us[50_000]:.1f} at "
           f"50000", flush=True)
     assert us[50_000] < 1.45 * us[32_768]
+
+
+def test_batch_time_between_block_sizes():
+    """64 queries over 65000 rows take about as long as over 65400: both have the
+    better block size (a line by the blocks of another grid gave it to 65281 ..
+    65536 rows alone, and 65000 took 1.19 times as long)."""
+    us = {}
+    d, nq, k = 3584, 64, 16
+    for n in (65_000, 65_400):
+        g = torch.Generator(device=DEV)
+        g.manual_seed(n)
+        keys = torch.randn((n, d), generator=g, device=DEV).to(torch.bfloat16)
+        spans = torch.zeros((n, 4), dtype=torch.int32, device=DEV)
+        q = torch.randn((nq, d), generator=g, device=DEV).to(torch.bfloat16)
+        index = sense.sense_build_index(keys, spans, None, metric="cosine")
+        ws = torch.empty(sense.sense_retrieve_workspace_size(index, nq, k), dtype=torch.uint8,
+                         device=DEV)
+        out = tuple(torch.empty(s, dtype=t, device=DEV) for s, t in (
+            ((nq, k), torch.int64), ((nq, k), torch.float32), ((nq, k, 4), torch.int32),
+            ((nq, k), torch.int32)))
+        us[n] = _replay_us(lambda: sense.sense_retrieve(index, q, k, workspace=ws, out=out))
+        index.close()
+    print(f"[batch-time] {us}", flush=True)
+    assert us[65_000] < 1.1 * us[65_400]
