@@ -112,12 +112,10 @@ hipError_t launch_key_norms(const void* keys, int key_dtype, int64_t n, int d, i
 // single query runs the GEMV, whose fp32 query needs no hi/lo split.
 constexpr int kMfmaMinQueries = 2;
 
-// scores[q * n + i] = similarity of query q and row i for q in [0, nq).
-// queries: nq x d fp32 (already converted).  inv_norm NULL for IP.  split and
-// scratch are those of launch_scan_mfma, which batches take.
+// scores[i] = similarity of one fp32 query and row i.  inv_norm NULL for IP.
 hipError_t launch_scan(const void* keys, int key_dtype, int64_t n, int d, int64_t ld,
-                       const float* queries, int nq, bool split, const float* inv_norm,
-                       float* scores, void* scratch, hipStream_t stream);
+                       const float* query, const float* inv_norm, float* scores,
+                       hipStream_t stream);
 size_t scan_mfma_scratch_bytes(int nq, int d);
 // One query group (<= 64 queries, already split) of the batched scan over
 // rows 0, row_step, 2 row_step, ... (n_rows of them) of a store of row
@@ -170,13 +168,6 @@ struct QueryBatch {
 hipError_t launch_scan_mfma(const void* keys, int key_dtype, int64_t n, int64_t ld,
                             const QueryBatch& b, bool split, const float* inv_norm,
                             float* scores, void* scratch, hipStream_t stream);
-inline hipError_t launch_scan_mfma(const void* keys, int key_dtype, int64_t n, int d, int64_t ld,
-                                   const float* queries, int nq, bool split,
-                                   const float* inv_norm, float* scores, void* scratch,
-                                   hipStream_t stream) {
-    const QueryBatch b{queries, DT_F32, nq, d, nullptr, nullptr, nullptr};
-    return launch_scan_mfma(keys, key_dtype, n, ld, b, split, inv_norm, scores, scratch, stream);
-}
 
 // Single-query scans of keys with d <= kSmallDim (several rows per load
 // instruction), one launch per query.

@@ -538,7 +538,8 @@ constexpr int resident(int lds) { return 160 * 1024 / lds < 1 ? 1 : 160 * 1024 /
 template <int KT, int MT, int T, int P, bool SPLIT>
 hipError_t launch_tile(const MfmaScan& s, hipStream_t stream) {
     if (s.cand) {
-        if constexpr (16 * kWaves * T == kFilterRows) {
+        // Filtered passes take the hi half alone.
+        if constexpr (!SPLIT && 16 * kWaves * T == kFilterRows) {
             // Whole blocks, one workgroup per compute unit (the ring's LDS
             // allows one): the lists' slots are those of this grid.
             const int64_t nblk = (s.n_rows + kFilterRows - 1) / kFilterRows;
@@ -619,8 +620,7 @@ hipError_t launch_group(const MfmaScan& s, hipStream_t stream) {
         // the rows (262144 x 4096 onto 64 outputs 443 -> 380 us, 100001 x 1024
         // 62.3 -> 58.5); where it has not, smaller ones (30000 x 8192 269 us in
         // blocks of 512, 181 of 256, 141 of 128; 2000 x 4096 120, 79, 57).
-        if (s.cand == nullptr && rows > 32 * kWaves)
-            return launch_group_t<KT, 4, 2, SPLIT>(s, stream);
+        if (rows > 32 * kWaves) return launch_group_t<KT, 4, 2, SPLIT>(s, stream);
     }
     switch ((s.nq + 15) / 16) {
         case 1: return launch_tile<KT, 1, 2, 4, SPLIT>(s, stream);

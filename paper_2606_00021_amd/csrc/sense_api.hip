@@ -87,10 +87,9 @@ int elem_size(int dt) { return dt == SENSE_F32 ? 4 : 2; }
 
 bool dtype_ok(int dt) { return dt == SENSE_F32 || dt == SENSE_F16 || dt == SENSE_BF16; }
 
-// Retrieval workspace layout:
-// [fp32 queries | split queries (MFMA path) | scores | top-k buffers].
+// Retrieval workspace layout of one query: [fp32 query | scores | top-k buffers].
 struct RetrieveLayout {
-    size_t q_off, m_off, s_off, t_off, total;
+    size_t q_off, s_off, t_off, total;
 };
 
 // Batched queries over short keys: the matrix-core short-key scan, either every
@@ -181,16 +180,13 @@ RetrieveLayout retrieve_layout(const sense_index* ix, int nq, int k) {
     if (short_batched(ix, nq) || long_batched(ix, nq)) {
         const ShortLayout sl = short_layout(ix, nq, k);
         l.q_off = sl.q_off;
-        l.m_off = sl.m_off;
         l.s_off = sl.cand_off;
         l.t_off = sl.fws_off;
         l.total = sl.total;
         return l;
     }
     l.q_off = 0;
-    l.m_off = round_up((size_t)nq * ix->d * sizeof(float), 256);
-    const size_t mfma = nq >= sense::kMfmaMinQueries ? sense::scan_mfma_scratch_bytes(nq, ix->d) : 0;
-    l.s_off = l.m_off + round_up(mfma, 256);
+    l.s_off = round_up((size_t)nq * ix->d * sizeof(float), 256);
     // A dynamic cache is sized for its capacity, so one workspace serves
     // every later row count.
     const int64_t rows = ix->capacity > 0 ? ix->capacity : ix->n;
@@ -711,8 +707,8 @@ SENSE_EXPORT sense_status_t sense_retrieve(const sense_index_t* ix, const void* 
         e = sense::launch_scan_small(ix->keys, ix->key_dtype, ix->n, ix->d, ix->ld, qptr, nq,
                                      ix->inv_norm, scores, st);
     else
-        e = sense::launch_scan(ix->keys, ix->key_dtype, ix->n, ix->d, ix->ld, qptr, nq, split,
-                               ix->inv_norm, scores, ws + L.m_off, st);
+        e = sense::launch_scan(ix->keys, ix->key_dtype, ix->n, ix->d, ix->ld, qptr, ix->inv_norm,
+                               scores, st);
     if (e != hipSuccess) return hip_fail(e, "similarity scan");
     if ((e = timer_mark(SENSE_TIMER_SCAN, 1, st)) != hipSuccess) return hip_fail(e, "timer");
     if ((e = timer_mark(SENSE_TIMER_TOPK, 0, st)) != hipSuccess) return hip_fail(e, "timer");
