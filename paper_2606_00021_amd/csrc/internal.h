@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "filter_lists.h"
+#include "short_groups.h"
 
 namespace sense {
 
@@ -306,10 +307,6 @@ struct ShortScan {
     int64_t n_groups;
     float* gmax;              // gmax[q * n_groups + g]
 };
-constexpr int kMaxGroupRows = 64;
-int short_group_rows(int64_t n_rows);
-// Rows the sizing of a short-key candidate list counts beside the store's.
-int64_t short_list_slots(int64_t n_rows);
 hipError_t launch_scan_short(const ShortScan& s, hipStream_t stream);
 hipError_t launch_scan_groups(const ShortScan& s, hipStream_t stream);
 // What follows the group maxima, in one launch where it fits (best_groups_fit).

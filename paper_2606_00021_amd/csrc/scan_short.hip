@@ -1,7 +1,6 @@
 // Batched similarity scan of short keys (d <= 64, e.g. the 64-dim PCA keys)
-// on the matrix cores, with an optional filter that keeps only rows able to
-// enter a query's top k (Sec. 3.2 Eq. 8 for a batch of queries; the top-N'
-// retrieval of Eq. 7).
+// on the matrix cores, every score or the best of each group of rows (Sec. 3.2
+// Eq. 8 for a batch of queries; the top-N' retrieval of Eq. 7).
 //
 // A 64-dim key is 128 bytes, so the long-key MFMA design (a ring of key
 // stages walking d) has nothing to pipeline across.  Here every wave keeps
@@ -532,7 +531,7 @@ __global__ __launch_bounds__(kShortThreads) void score_groups_kernel(
 // k = 100 (1600 rows) 48.4 us so and 55.0 in three launches; over 1M, k = 64
 // (4096 rows) 79.3 so and 75.7 in three.
 constexpr int kTailThreads = 1024;
-constexpr int kTailGroups = 16384;
+constexpr int kTailGroups = (int)kSelectGroups;
 constexpr int kTailRows = 2048;
 
 template <int KT, bool SPLIT>
@@ -755,18 +754,6 @@ static hipError_t launch_groups_t(const ShortScan& s, hipStream_t stream) {
         case 3: return launch_groups<KT, 3>(s, stream);
         default: return launch_groups<KT, 4>(s, stream);
     }
-}
-
-// Rows per group: at most 16384 groups (one block's selection) up to a million
-// rows; groups of 64 beyond (one wave's rescore).
-int short_group_rows(int64_t n_rows) {
-    const int64_t g = 16 * ((n_rows + 16 * 16384 - 1) / (16 * 16384));
-    return (int)(g < kMaxGroupRows ? g : kMaxGroupRows);
-}
-
-int64_t short_list_slots(int64_t n_rows) {
-    const int64_t rpw = short_rows_per_wave(n_rows);
-    return (n_rows + rpw - 1) / rpw * 4;
 }
 
 hipError_t launch_scan_groups(const ShortScan& s, hipStream_t stream) {

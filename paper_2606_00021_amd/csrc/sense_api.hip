@@ -87,36 +87,8 @@ int elem_size(int dt) { return dt == SENSE_F32 ? 4 : 2; }
 
 bool dtype_ok(int dt) { return dt == SENSE_F32 || dt == SENSE_F16 || dt == SENSE_BF16; }
 
-// Retrieval workspace layout of one query: [fp32 query | scores | top-k buffers].
-struct RetrieveLayout {
-    size_t q_off, s_off, t_off, total;
-};
-
-// Batched queries over short keys: the matrix-core short-key scan, either every
-// score and a top-k over them, or by groups of rows.
-// Groups read and select a sixteenth of the scores, and cost two launches and
-// the rescore of k groups: they pay where a pass's score matrix (ng queries by n
-// rows) is large and k is not.  Measured over 64-dim bf16 rows, fp32 queries, us
-// a search of one pass, every score / groups:
-//   k = 64      2 queries   16       33          64
-//     33000     26 / 29     29 / 32  31 / 34     38 / 35
-//     50000     21 / 31     29 / 31  33 / 34     39 / 35
-//     65536     21 / 31     24 / 31  29 / 34     36 / 36
-//     90000     24 / 31     28 / 32  36 / 35     44 / 37
-//     131072    24 / 32     30 / 32  40 / 35     50 / 39
-//   k = 4       64 queries: 33000 35 / 34, 50000 30 / 35, 65536 32 / 35, 90000
-//               41 / 36; 33 queries: 90000 33 / 35, 131072 37 / 36
-//   k = 256     64 queries: 65536 44 / 65, 131072 61 / 70
-// Up to kShortDirectMax rows every score always (32768 x 64 queries, k = 64: 29
-// and 35 us); beyond kShortGroupsMin rows groups always.
-constexpr int64_t kShortDirectMax = 32768, kShortGroupsMin = 131072;
-bool short_by_groups(int64_t n, int ng, int k) {
-    if (n <= kShortDirectMax) return false;
-    if (n > kShortGroupsMin) return true;
-    const int64_t scores = (int64_t)ng * n, unit = (int64_t)1 << 20;
-    return k <= 128 && scores > (k < 32 ? 4 * unit : (n < 65536 ? 2 : 3) * unit);
-}
-constexpr int64_t kShortSample = 32768;     // scores per query of the sample area
+// Most rows of a store of short keys that batches search.
+constexpr int64_t kShortBatchRows = (int64_t)INT32_MAX - 8192;
 
 bool short_batched(const sense_index* ix, int nq) {
     return ix->d <= sense::kSmallDim && nq >= sense::kMfmaMinQueries;
@@ -133,66 +105,90 @@ bool long_batched(const sense_index* ix, int nq) {
     return ix->d > sense::kSmallDim && nq >= sense::kMfmaMinQueries;
 }
 
+// Offsets taken one after the other, 256-byte aligned.
+struct Arena {
+    size_t at = 0;
+    size_t take(size_t bytes) {
+        const size_t o = at;
+        at = round_up(at + bytes, 256);
+        return o;
+    }
+};
+
+// Workspace of a batch over short keys: query split, hit groups, the area of
+// scores or of group maxima and hit rows, top-k buffers.  Sized for the row
+// count or, of a growing store, for every one up to its capacity.
 struct ShortLayout {
+    size_t m_off, hit_off, area_off, t_off, total;
+};
+
+ShortLayout short_layout(const sense_index* ix, int nq, int k) {
+    ShortLayout l;
+    const int g = nq < 64 ? nq : 64;
+    const bool grows = ix->capacity > 0;
+    const int64_t rows = grows ? ix->capacity : ix->n;
+    const int64_t groups = grows ? sense::short_groups_most(rows) : sense::short_groups(rows);
+    const int64_t direct = rows < sense::kShortGroupsMin ? rows : sense::kShortGroupsMin;
+    Arena a;
+    l.m_off = a.take(sense::scan_mfma_scratch_bytes(nq, ix->d));
+    l.hit_off = a.take((size_t)g * k * sizeof(int64_t));
+    l.area_off = a.take(grows ? sense::short_area_most(rows, g, k)
+                              : sense::short_area_bytes(rows, g, k));
+    l.t_off = a.take(sense::topk_workspace_bytes(groups > direct ? groups : direct, g, k));
+    l.total = a.at;
+    return l;
+}
+
+// Workspace of a batch over long keys: query split, sample scores and top-k,
+// thresholds and counts, the candidate lists (a workgroup's slots, then an
+// overflow list of up to every row) or, for a store searched directly, the plain
+// score matrix in the same area.
+struct BatchLayout {
     size_t q_off, m_off, ss_off, sid_off, ssc_off, sws_off, tau_off, cnt_off, cand_off, fws_off,
         total;
     int64_t cap;    // entries of one query's candidate list
 };
 
-// Workspace of the batched retrieval (short keys, or long keys in
-// batches): query split, sample scores and top-k, thresholds and counts, the
-// candidate lists (wave slots + an overflow list of up to every row) or, for
-// a store searched directly, the plain score matrix in the same area.
-ShortLayout short_layout(const sense_index* ix, int nq, int k) {
-    ShortLayout l;
-    const bool long_keys = ix->d > sense::kSmallDim;
-    const int64_t sample = long_keys ? kBatchSample : kShortSample;
-    const int64_t rows = ix->capacity > 0 ? ix->capacity : ix->n;
+BatchLayout batch_layout(const sense_index* ix, int nq, int k) {
+    BatchLayout l;
     const int g = nq < 64 ? nq : 64;
-    size_t at = 0;
-    auto take = [&](size_t bytes) {
-        const size_t o = at;
-        at = round_up(at + bytes, 256);
-        return o;
-    };
-    l.q_off = take((size_t)nq * ix->d * sizeof(float));
-    l.m_off = take(sense::scan_mfma_scratch_bytes(nq, ix->d));
-    l.ss_off = take((size_t)g * sample * sizeof(float));
-    l.sid_off = take((size_t)g * k * sizeof(int64_t));
-    l.ssc_off = take((size_t)g * k * sizeof(float));
-    l.sws_off = take(sense::topk_workspace_bytes(sample, g, k));
-    l.tau_off = take((size_t)g * sizeof(uint64_t));
-    l.cnt_off = take((size_t)g * sizeof(int32_t));
-    // candidates per query: the wave slots, then an overflow list of up to
-    // every row; also the plain score matrix of small stores
-    const int64_t cap = long_keys
-                            ? sense::filter_list_entries(ix->n, ix->capacity, sense::device_cus())
-                            : sense::short_list_slots(rows) + rows;
-    l.cap = cap;
-    l.cand_off = take((size_t)g * cap * sizeof(uint64_t));
-    l.fws_off = take(sense::topk_workspace_bytes(cap, g, k));
-    l.total = at;
+    Arena a;
+    l.q_off = a.take((size_t)nq * ix->d * sizeof(float));
+    l.m_off = a.take(sense::scan_mfma_scratch_bytes(nq, ix->d));
+    l.ss_off = a.take((size_t)g * kBatchSample * sizeof(float));
+    l.sid_off = a.take((size_t)g * k * sizeof(int64_t));
+    l.ssc_off = a.take((size_t)g * k * sizeof(float));
+    l.sws_off = a.take(sense::topk_workspace_bytes(kBatchSample, g, k));
+    l.tau_off = a.take((size_t)g * sizeof(uint64_t));
+    l.cnt_off = a.take((size_t)g * sizeof(int32_t));
+    l.cap = sense::filter_list_entries(ix->n, ix->capacity, sense::device_cus());
+    l.cand_off = a.take((size_t)g * l.cap * sizeof(uint64_t));
+    l.fws_off = a.take(sense::topk_workspace_bytes(l.cap, g, k));
+    l.total = a.at;
     return l;
 }
 
-RetrieveLayout retrieve_layout(const sense_index* ix, int nq, int k) {
-    RetrieveLayout l;
-    if (short_batched(ix, nq) || long_batched(ix, nq)) {
-        const ShortLayout sl = short_layout(ix, nq, k);
-        l.q_off = sl.q_off;
-        l.s_off = sl.cand_off;
-        l.t_off = sl.fws_off;
-        l.total = sl.total;
-        return l;
-    }
-    l.q_off = 0;
-    l.s_off = round_up((size_t)nq * ix->d * sizeof(float), 256);
-    // A dynamic cache is sized for its capacity, so one workspace serves
-    // every later row count.
+// Workspace of one query: [fp32 query | scores | top-k buffers].
+struct SingleLayout {
+    size_t q_off, s_off, t_off, total;
+};
+
+SingleLayout single_layout(const sense_index* ix, int k) {
+    SingleLayout l;
+    // A growing store is sized for its capacity, so one workspace serves every
+    // later row count.
     const int64_t rows = ix->capacity > 0 ? ix->capacity : ix->n;
-    l.t_off = l.s_off + round_up((size_t)nq * (size_t)rows * sizeof(float), 256);
-    l.total = l.t_off + sense::topk_workspace_bytes(rows, nq, k);
+    l.q_off = 0;
+    l.s_off = round_up((size_t)ix->d * sizeof(float), 256);
+    l.t_off = l.s_off + round_up((size_t)rows * sizeof(float), 256);
+    l.total = l.t_off + sense::topk_workspace_bytes(rows, 1, k);
     return l;
+}
+
+size_t retrieve_bytes(const sense_index* ix, int nq, int k) {
+    if (short_batched(ix, nq)) return short_layout(ix, nq, k).total;
+    if (long_batched(ix, nq)) return batch_layout(ix, nq, k).total;
+    return single_layout(ix, k).total;
 }
 
 }  // namespace
@@ -434,15 +430,19 @@ static sense_status_t check_retrieve_sizes(const sense_index_t* ix, int32_t nq, 
     if ((int64_t)k > ix->n)
         return fail(SENSE_ERR_INVALID_ARGUMENT, "k = %d exceeds the %lld stored rows", k,
                     (long long)ix->n);
-    // Batches keep per-query candidate lists (wave slots, then up to every
-    // row) whose positions are 32-bit.
-    if (short_batched(ix, nq) || long_batched(ix, nq)) {
-        const ShortLayout L = short_layout(ix, nq, k);
-        if (L.cap > (int64_t)INT32_MAX)
+    const long long rows = (long long)(ix->capacity > 0 ? ix->capacity : ix->n);
+    if (short_batched(ix, nq) && rows > kShortBatchRows)
+        return fail(SENSE_ERR_UNSUPPORTED,
+                    "a batch over %lld rows (at most %lld): search it one query at a time", rows,
+                    (long long)kShortBatchRows);
+    // Batches over long keys keep per-query candidate lists (slots, then up to
+    // every row) whose positions are 32-bit.
+    if (long_batched(ix, nq)) {
+        const int64_t cap = sense::filter_list_entries(ix->n, ix->capacity, sense::device_cus());
+        if (cap > (int64_t)INT32_MAX)
             return fail(SENSE_ERR_UNSUPPORTED,
                         "a batch over %lld rows needs candidate lists of %lld entries (at most "
-                        "2^31 - 1): search it one query at a time",
-                        (long long)(ix->capacity > 0 ? ix->capacity : ix->n), (long long)L.cap);
+                        "2^31 - 1): search it one query at a time", rows, (long long)cap);
     }
     return SENSE_OK;
 }
@@ -452,7 +452,7 @@ SENSE_EXPORT sense_status_t sense_retrieve_workspace_size(const sense_index_t* i
     if (!bytes) return fail(SENSE_ERR_INVALID_ARGUMENT, "bytes is NULL");
     const sense_status_t s = check_retrieve_sizes(ix, nq, k);
     if (s != SENSE_OK) return s;
-    *bytes = retrieve_layout(ix, nq, k).total;
+    *bytes = retrieve_bytes(ix, nq, k);
     return ok();
 }
 
@@ -473,14 +473,11 @@ static hipError_t retrieve_short(const sense_index* ix, const void* queries, int
         return e;
     const sense::QuerySplit qs = sense::query_split_parts(ws + L.m_off, nq, ix->d);
     const int group_rows = sense::short_group_rows(n);
-    const int64_t n_groups = (n + group_rows - 1) / group_rows;
+    const int64_t n_groups = sense::short_groups(n);
     const int n_hits = (int)(k < n_groups ? k : n_groups);
-    // The candidate area (per query at least n entries of 8 bytes) holds the
-    // group maxima, then the keys of the hit groups' rows: for n > 32768 and
-    // k <= 1024 less than n / 2 + 8 K bytes and 8 n_hits * group_rows.
-    float* gmax = (float*)(ws + L.cand_off);
-    uint64_t* cand = (uint64_t*)(ws + L.cand_off +
-                                 round_up((size_t)(nq < 64 ? nq : 64) * n_groups * 4, 256));
+    float* gmax = (float*)(ws + L.area_off);
+    uint64_t* cand =
+        (uint64_t*)(ws + L.area_off + sense::short_keys_offset(n_groups, nq < 64 ? nq : 64));
     for (int g0 = 0; g0 < nq; g0 += 64) {
         const int ng = nq - g0 < 64 ? nq - g0 : 64;
         sense::ShortScan S{};
@@ -499,12 +496,12 @@ static hipError_t retrieve_short(const sense_index* ix, const void* queries, int
         float* gsc = out_scores ? out_scores + (int64_t)g0 * k : nullptr;
         int32_t* gdr = out_drafts ? out_drafts + (int64_t)g0 * k * ix->max_span : nullptr;
         int32_t* gdl = out_draft_len ? out_draft_len + (int64_t)g0 * k : nullptr;
-        if (!short_by_groups(n, ng, k)) {
-            S.scores = (float*)(ws + L.cand_off);
+        if (!sense::short_by_groups(n, ng, k)) {
+            S.scores = (float*)(ws + L.area_off);
             if ((e = sense::launch_scan_short(S, st)) != hipSuccess) return e;
             if ((e = sense::launch_topk_gather(S.scores, n, ng, k, ix->spans, ix->span_len,
                                                ix->max_span, ix->span_stride, gid, gsc, gdr,
-                                               gdl, ws + L.fws_off, st)) != hipSuccess)
+                                               gdl, ws + L.t_off, st)) != hipSuccess)
                 return e;
             continue;
         }
@@ -518,9 +515,9 @@ static hipError_t retrieve_short(const sense_index* ix, const void* queries, int
             if ((e = sense::launch_best_groups(S, n_hits, O, st)) != hipSuccess) return e;
             continue;
         }
-        int64_t* hit = (int64_t*)(ws + L.sid_off);
+        int64_t* hit = (int64_t*)(ws + L.hit_off);
         if ((e = sense::launch_topk_gather(gmax, n_groups, ng, n_hits, nullptr, nullptr, 1, 1,
-                                           hit, nullptr, nullptr, nullptr, ws + L.fws_off,
+                                           hit, nullptr, nullptr, nullptr, ws + L.t_off,
                                            st)) != hipSuccess)
             return e;
         if ((e = sense::launch_score_groups(S, hit, n_hits, n_hits, cand, st)) != hipSuccess)
@@ -559,7 +556,7 @@ static hipError_t retrieve_batched(const sense_index* ix, const void* queries, i
                                    int nq, int k, bool split, int64_t* out_ids, float* out_scores,
                                    int32_t* out_drafts, int32_t* out_draft_len, char* ws,
                                    hipStream_t st) {
-    const ShortLayout L = short_layout(ix, nq, k);
+    const BatchLayout L = batch_layout(ix, nq, k);
     const int64_t n = ix->n;
     hipError_t e;
     if ((e = timer_mark(SENSE_TIMER_SCAN, 0, st)) != hipSuccess) return e;
@@ -672,16 +669,14 @@ SENSE_EXPORT sense_status_t sense_retrieve(const sense_index_t* ix, const void* 
     if (!dtype_ok(q_dtype)) return fail(SENSE_ERR_INVALID_ARGUMENT, "unknown q_dtype %d", (int)q_dtype);
     if (!aligned(queries, q_dtype == SENSE_F32 ? 16 : 2))
         return fail(SENSE_ERR_MISALIGNED, "fp32 queries must be 16-byte aligned");
-    const RetrieveLayout L = retrieve_layout(ix, nq, k);
-    if (!workspace || workspace_bytes < L.total)
-        return fail(SENSE_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", L.total,
+    const size_t need = retrieve_bytes(ix, nq, k);
+    if (!workspace || workspace_bytes < need)
+        return fail(SENSE_ERR_WORKSPACE, "workspace of %zu bytes needed, %zu given", need,
                     workspace ? workspace_bytes : (size_t)0);
     if (!aligned(workspace, 256)) return fail(SENSE_ERR_MISALIGNED, "workspace must be 256-byte aligned");
 
     hipStream_t st = (hipStream_t)stream;
     char* ws = (char*)workspace;
-    float* qf = (float*)(ws + L.q_off);
-    float* scores = (float*)(ws + L.s_off);
     hipError_t e;
     const bool split = q_dtype != ix->key_dtype;  // key-typed queries need no lo half
     if (short_batched(ix, nq)) {
@@ -696,6 +691,9 @@ SENSE_EXPORT sense_status_t sense_retrieve(const sense_index_t* ix, const void* 
             return hip_fail(e, "batched retrieval");
         return ok();
     }
+    const SingleLayout L = single_layout(ix, k);
+    float* qf = (float*)(ws + L.q_off);
+    float* scores = (float*)(ws + L.s_off);
     const float* qptr = (const float*)queries;
     if (q_dtype != SENSE_F32) {
         if ((e = sense::launch_query_to_f32(queries, q_dtype, nq, ix->d, qf, st)) != hipSuccess)
@@ -761,7 +759,7 @@ SENSE_EXPORT sense_status_t sense_retrieve_noalloc(const sense_index_t* ix, cons
                                                    void* stream) {
     sense_status_t s = check_retrieve_sizes(ix, nq, k);
     if (s != SENSE_OK) return s;
-    const size_t need = retrieve_layout(ix, nq, k).total;
+    const size_t need = retrieve_bytes(ix, nq, k);
     if (need > kNoAllocScratchBytes)
         return fail(SENSE_ERR_UNSUPPORTED,
                     "this retrieval needs %zu bytes of scratch; the static scratch holds %zu "

@@ -375,6 +375,38 @@ def test_growing_cache_between_grid_steps():
     cache.close()
 
 
+@pytest.mark.parametrize("n,capacity,nq,k", [
+    (262_144, 300_000, 70, 40),      # most groups: 16384, of 16 rows; two passes
+    (270_000, 300_000, 16, 1024),    # groups of 32, hit rows in launches of their own
+    (131_072, 300_000, 3, 200),      # every score, the most rows that take it
+    (33_000, 34_000, 65, 100),       # one pass by groups, the other not
+    (20_000, 20_000, 64, 1024),
+])
+def test_short_batch_stays_in_its_workspace(n, capacity, nq, k):
+    """A growing store of short keys: the hits are the oracle's, and nothing is
+    written behind the workspace that its capacity asks for."""
+    d, m = 64, 2
+    print(f"[case] short cache of {capacity} rows holding {n} Q={nq} k={k}", flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n)
+    rows = torch.randn((n, d), generator=g, device=DEV).to(torch.bfloat16)
+    tok = torch.randint(0, 32000, (n,), generator=g, device=DEV, dtype=torch.int32)
+    q = torch.randn((nq, d), generator=g, device=DEV)
+    cache = sense.sense_build_dynamic_index(d, capacity, m, key_dtype=torch.bfloat16)
+    sense.sense_index_append(cache, rows, tok)
+    need, guard = sense.sense_retrieve_workspace_size(cache, nq, k), 1 << 22
+    buf = torch.full((need + guard,), 0xA5, dtype=torch.uint8, device=DEV)
+    ids, scores, _, _ = sense.sense_retrieve(cache, q, k, workspace=buf[:need])
+    torch.cuda.synchronize()
+    assert (buf[need:] == 0xA5).all(), "written past the workspace"
+    kb, qh = host_bits(rows), q.cpu().numpy()
+    o_s = oracle.scores(kb, "bf16", qh, "f32")
+    bounds = query_bounds(kb, "bf16", qh, "cosine")
+    for qi in range(nq):
+        check_topk(ids[qi].cpu().numpy(), scores[qi].cpu().numpy(), o_s[qi], k, bounds[qi])
+    cache.close()
+
+
 @pytest.mark.parametrize("metric", ["cosine", "ip"])
 def test_batched_sampled_all_rows_tie(metric):
     """Every stored row the same key: every row reaches the sampled threshold
