@@ -24,9 +24,10 @@
 //   Rows may start at any element: the elements before the first 16-byte word
 //   of memory and behind the last go to single lanes.
 //
-//   Bound: the read of the rows; per 16-bit logit 6.5 vector instructions
-//   (half of one for the maximum, unpack, fma, exp2 at half rate, add, fma),
-//   one more where a logit of the wave reaches the judged one and one more
+//   Bound: the read of the rows; per 16-bit logit 6.5 vector issues (half of one
+//   for the maximum, unpack, fma, exp2 at half rate, add, fma; 10.1 instructions
+//   counted at 64 x 8 rows of 152064, the count of the judged logit, the state's
+//   changes, prologue and reduction with them), one more where a logit of the wave reaches the judged one and one more
 //   where a masked (-inf) one is among them.  64 x 8 of 152064 bf16 with a third
 //   of the vocabulary masked: 31.4 us clamped throughout, 41.4 where every step
 //   first forms the sums without the clamp, 31.6 so.
