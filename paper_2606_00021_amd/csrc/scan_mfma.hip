@@ -63,6 +63,12 @@ __device__ __forceinline__ float from_key_bits(uint16_t b) {
     }
 }
 
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x),
+                                                                 CTRL, 0xF, 0xF, false));
+}
+
 // Pads the query batch to qpad rows and splits each fp32 value into hi + lo
 // in the key type; inv_qn[q] = 1/||q|| (cosine), 1 (inner product), 0 for
 // padding rows.  margin[q] is twice a bound on the difference between a
@@ -77,28 +83,31 @@ __device__ __forceinline__ float from_key_bits(uint16_t b) {
 // doubled for safety and the split term raised by 1 % (its own fp32
 // evaluation is good to ~d * 2^-24).  An overflowing split (an f16 hi half
 // of |x| > 65504) or an infinite key gives an infinite or NaN margin: every
-// row then passes.  One block (256 threads) per padded query row.
+// row then passes.  One block of W waves per padded query row.
 //
 // The queries come in fp32 or either 16-bit type (QT); with f32 they are also
 // stored in fp32, and with mean (a projection's basis as the queries)
 // centre[row] = mean . row.
-// Bound: latency; a thread's loads of up to 4096 dims go out together (64 rows
-// of 8192 fp32 14.3 -> 7.0 us, of 4096 with the mean 30 in two launches -> 6.7).
-template <int KT, int QT>
-__global__ __launch_bounds__(256) void query_split_kernel(
+// Bound: latency; a thread's U loads of four dims go out together, for up to
+// 4096 dims (64 rows of 8192 fp32 14.3 -> 7.0 us, of 4096 with the mean 30 in two
+// launches -> 6.7), and its sums' steps side by side.  Rows of up to 256 dims are
+// one wave's, one load a thread and no barrier (a search of 2 queries over 64 x 64
+// 16.4 us in four waves, 15.5 so).
+template <int KT, int QT, int W, int U>
+__global__ __launch_bounds__(64 * W) void query_split_kernel(
     const void* __restrict__ q, int nq, int d, bool cosine, uint16_t* __restrict__ qhi,
     uint16_t* __restrict__ qlo, float* __restrict__ inv_qn,
     const float* __restrict__ key_norm_max, float* __restrict__ margin, float* __restrict__ f32,
     const float* __restrict__ mean, float* __restrict__ centre) {
-    constexpr int U = 4;
+    constexpr int kStep = 256 * W;                // dims of a block's loads
     const int row = blockIdx.x, tid = threadIdx.x;
     const int64_t src = (int64_t)(row < nq ? row : 0) * d;
     float part[3] = {0.0f, 0.0f, 0.0f};           // x x, lo lo, mean x
-    for (int t0 = 0; t0 < d; t0 += 1024 * U) {
+    for (int t0 = 0; t0 < d; t0 += kStep * U) {
         float v[U][4], mv[U][4];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int t = t0 + 1024 * u + 4 * tid;
+            const int t = t0 + kStep * u + 4 * tid;
             const int tc = t < d ? t : 0;
             if constexpr (QT != DT_F32) {
                 u32x2 w;                              // rows at any element
@@ -113,7 +122,7 @@ __global__ __launch_bounds__(256) void query_split_kernel(
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const int t = t0 + 1024 * u + 4 * tid;
+            const int t = t0 + kStep * u + 4 * tid;
             if (t >= d) continue;
             uint32_t hb[4], lb[4];
 #pragma unroll
@@ -132,17 +141,30 @@ __global__ __launch_bounds__(256) void query_split_kernel(
             if (f32 && row < nq) *(f32x4*)(f32 + at) = f32x4{v[u][0], v[u][1], v[u][2], v[u][3]};
         }
     }
-    __shared__ float s_part[3][4];
+    // Over the wave; the first steps by DPP (quads, half rows, rows).
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < 3; ++i) part[i] += dpp_f<0xB1>(part[i]);
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) part[i] += __shfl_xor(part[i], off, 64);
-        if ((tid & 63) == 0) s_part[i][tid >> 6] = part[i];
+    for (int i = 0; i < 3; ++i) part[i] += dpp_f<0x4E>(part[i]);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) part[i] += dpp_f<0x141>(part[i]);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) part[i] += dpp_f<0x140>(part[i]);
+#pragma unroll
+    for (int off = 16; off < 64; off <<= 1)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) part[i] += __shfl_xor(part[i], off, 64);
+    [[maybe_unused]] __shared__ float s_part[3][W];
+    if constexpr (W > 1) {
+        if ((tid & 63) == 0)
+#pragma unroll
+            for (int i = 0; i < 3; ++i) s_part[i][tid >> 6] = part[i];
+        __syncthreads();
     }
-    __syncthreads();
     if (tid == 0) {
         auto total = [&](int i) {
-            return (s_part[i][0] + s_part[i][1]) + (s_part[i][2] + s_part[i][3]);
+            if constexpr (W == 1) return part[i];
+            else return (s_part[i][0] + s_part[i][1]) + (s_part[i][2] + s_part[i][3]);
         };
         if (mean && row < nq) centre[row] = total(2);
         const float s = total(0);
@@ -805,11 +827,18 @@ QuerySplit query_split_parts(void* scratch, int nq, int d) {
 template <int KT>
 static void launch_query_split_t(const QueryBatch& b, bool cosine, const float* key_norm_max,
                                  const QuerySplit& p, hipStream_t stream) {
-    auto kern = b.dtype == DT_F32   ? query_split_kernel<KT, DT_F32>
-                : b.dtype == DT_F16 ? query_split_kernel<KT, DT_F16>
-                                    : query_split_kernel<KT, DT_BF16>;
-    hipLaunchKernelGGL(kern, dim3(p.qpad), dim3(256), 0, stream, b.q, b.nq, b.d, cosine, p.hi,
-                       p.lo, p.inv_qn, key_norm_max, p.margin, b.f32, b.mean, b.centre);
+    auto go = [&](auto kern, int threads) {
+        hipLaunchKernelGGL(kern, dim3(p.qpad), dim3(threads), 0, stream, b.q, b.nq, b.d, cosine,
+                           p.hi, p.lo, p.inv_qn, key_norm_max, p.margin, b.f32, b.mean, b.centre);
+    };
+    if (b.d <= 256)
+        go(b.dtype == DT_F32   ? query_split_kernel<KT, DT_F32, 1, 1>
+           : b.dtype == DT_F16 ? query_split_kernel<KT, DT_F16, 1, 1>
+                               : query_split_kernel<KT, DT_BF16, 1, 1>, 64);
+    else
+        go(b.dtype == DT_F32   ? query_split_kernel<KT, DT_F32, 4, 4>
+           : b.dtype == DT_F16 ? query_split_kernel<KT, DT_F16, 4, 4>
+                               : query_split_kernel<KT, DT_BF16, 4, 4>, 256);
 }
 
 hipError_t launch_query_split(const QueryBatch& b, int key_dtype, bool cosine,

@@ -699,7 +699,9 @@ def test_short_groups_are_exact_with_ties(n, d, nq, k, dt):
                                     (140_007, 72, 18),
                                     # either side of the lines between block sizes
                                     (32_768, 72, 33), (32_769, 136, 13), (49_152, 72, 3),
-                                    (49_153, 72, 48), (49_153, 72, 49)])
+                                    (49_153, 72, 48), (49_153, 72, 49),
+                                    # ... and between one wave's query rows and a block's
+                                    (6000, 256, 17), (6000, 264, 17)])
 def test_16_bit_queries_of_either_type(n, d, nq, kt, qt):
     """Queries in a 16-bit type, that of the keys or the other one, from a row
     start of any alignment.  Small whole numbers: every score is exact."""
