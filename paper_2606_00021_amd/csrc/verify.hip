@@ -170,21 +170,24 @@ __device__ __forceinline__ void raise_to(State& a, float m2) {
     a.m2 = m2;
 }
 
-// Merges N partials into (a, c): to the largest maximum at once, so that no
-// factor waits for another.
+// Merges the first n (uniform) of N partials into (a, c): to the largest maximum
+// at once, so that no factor waits for another.
 template <int N>
-__device__ __forceinline__ void merge_all(State& a, int& c, const Partial (&q)[N]) {
+__device__ __forceinline__ void merge_all(State& a, int& c, const Partial (&q)[N], int n = N) {
     float m2 = a.m2;
 #pragma unroll
-    for (int u = 0; u < N; ++u) m2 = __builtin_fmaxf(m2, q[u].m2);
+    for (int u = 0; u < N; ++u)
+        if (u < n) m2 = __builtin_fmaxf(m2, q[u].m2);
     raise_to(a, m2);
 #pragma unroll
     for (int u = 0; u < N; ++u) {
-        State b{q[u].m2, q[u].s, q[u].t2};
-        raise_to(b, m2);
-        a.s += b.s;
-        a.t2 += b.t2;
-        c += q[u].cnt;
+        if (u < n) {
+            State b{q[u].m2, q[u].s, q[u].t2};
+            raise_to(b, m2);
+            a.s += b.s;
+            a.t2 += b.t2;
+            c += q[u].cnt;
+        }
     }
 }
 
@@ -525,11 +528,19 @@ __device__ __forceinline__ uint64_t bits_upto(int x) {  // bits 0..x set (x may 
 
 // Merge of an item's slice partials in slice order.  Loads go out in
 // batches of kMergeBatch (clamped indices, no branch around a load, so none
-// waits for the one before it).
+// waits for the one before it); partials past the last take no part (merged as
+// empty ones they cost the finalize of 256 x 8 rows of one slice 8.5 us against
+// 5.8).
 constexpr int kMergeBatch = 8;
 
 __device__ __forceinline__ void merge_partials(const Partial* p, int64_t n_items, int n_slices,
                                                State* st, int* cnt) {
+    if (n_slices == 1) {
+        const Partial q = *p;
+        *st = State{q.m2, q.s, q.t2};
+        *cnt = q.cnt;
+        return;
+    }
     State a;
     int c = 0;
     for (int s0 = 0; s0 < n_slices; s0 += kMergeBatch) {
@@ -537,10 +548,7 @@ __device__ __forceinline__ void merge_partials(const Partial* p, int64_t n_items
 #pragma unroll
         for (int u = 0; u < kMergeBatch; ++u)
             q[u] = p[((s0 + u < n_slices) ? s0 + u : n_slices - 1) * n_items];
-#pragma unroll
-        for (int u = 1; u < kMergeBatch; ++u)
-            if (s0 + u >= n_slices) q[u] = Partial{-__builtin_inff(), 0.0f, 0.0f, 0};
-        merge_all(a, c, q);
+        merge_all(a, c, q, n_slices - s0);
     }
     *st = a;
     *cnt = c;

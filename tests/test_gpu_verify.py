@@ -334,3 +334,29 @@ def test_short_rows_are_cheaper_than_long_ones():
         us[v] = _verify_us(logits, drafts, n_groups=16)
     print(f"[verify-short] {us}", flush=True)
     assert us[1000] < us[8192]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("slices", [1, 2, 7, 8, 9, 16, 17])
+def test_slices_of_a_row(slices, dtype):
+    """A few rows are cut into as many slices as they have steps of 8192 logits;
+    their partials are merged eight at a time, fewer at the end, and a single one
+    is taken as it is."""
+    logits, drafts = structured(61 + slices, 3, 2, 8192 * slices - 5, dtype=dtype)
+    logits[1, :, : 4096 * slices] = -float("inf")     # empty slices before the others
+    logits[1, 0, drafts[1, 0]] = 1.0
+    run(logits, drafts)
+
+
+def test_finalize_time_by_rows():
+    """Rows of one slice have nothing to merge: four times the rows take 1.6 times
+    as long (1.82 when every row also merged seven empty partials)."""
+    us = {}
+    for c in (64, 256):
+        g = torch.Generator(device=DEV)
+        g.manual_seed(c)
+        logits = 2.0 * torch.randn((c, 8, 100), generator=g, device=DEV)
+        drafts = torch.randint(0, 100, (c, 8), generator=g, device=DEV, dtype=torch.int32)
+        us[c] = _verify_us(logits, drafts)
+    print(f"[verify-finalize] {us}", flush=True)
+    assert us[256] < 1.72 * us[64]
