@@ -641,8 +641,14 @@ hipError_t launch_group(const MfmaScan& s, hipStream_t stream) {
         // Blocks of 512 rows in two stages halve that where a compute unit has
         // the rows (262144 x 4096 onto 64 outputs 443 -> 380 us, 100001 x 1024
         // 62.3 -> 58.5); where it has not, smaller ones (30000 x 8192 269 us in
-        // blocks of 512, 181 of 256, 141 of 128; 2000 x 4096 120, 79, 57).
-        if (rows > 32 * kWaves) return launch_group_t<KT, 4, 2, SPLIT>(s, stream);
+        // blocks of 512, 181 of 256, 141 of 128; 2000 x 4096 120, 79, 57), and
+        // where its last block of 512 would be near empty (513 to 768 rows, three
+        // blocks of 256): 150000 rows x 512, 1024, 2048 and 4096 onto 16 outputs 42,
+        // 72, 163 and 269 us in blocks of 512, 35, 60, 159 and 218 of 256, onto 64
+        // outputs 60, 97, 196 and 336, 52, 87, 194 and 305.
+        auto whole = [&](int64_t block) { return (rows + block - 1) / block * block; };
+        if (rows > 32 * kWaves && 4 * whole(64 * kWaves) <= 5 * whole(32 * kWaves))
+            return launch_group_t<KT, 4, 2, SPLIT>(s, stream);
     }
     switch ((s.nq + 15) / 16) {
         case 1: return launch_tile<KT, 1, 2, 4, SPLIT>(s, stream);

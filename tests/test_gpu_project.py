@@ -264,7 +264,7 @@ def test_full_size_store_projection():
 def test_full_size_short_key_retrieval(nq):
     """Retrieval over a projected-shape store at the bench's size: 1M x 64
     bf16 keys, k = 64; one query takes the short-key scan, 64 the batched
-    path with the sampled threshold.  Every query against the oracle's
+    path by groups of rows.  Every query against the oracle's
     scores of all rows."""
     n, d, k = 1 << 20, 64, 64
     print(f"[short-scan] full size n={n} d={d} Q={nq} k={k}", flush=True)
@@ -288,7 +288,8 @@ def test_full_size_short_key_retrieval(nq):
 @pytest.mark.parametrize("n,d_in,d_out", [
     (32_769, 72, 64), (33_001, 1000, 33),            # 129 rows a compute unit: blocks of 256
     (65_537, 136, 17), (70_003, 64, 96),             # 257 rows: blocks of 512, the last part full
-    (131_073, 40, 5),                                # two blocks of 512, the second of few rows
+    (131_073, 40, 5), (140_001, 64, 33),             # 513 rows: three blocks of 256
+    (196_609, 64, 20),                               # 769 rows: two of 512
     (513, 4104, 48),                                 # one block of 128 rows for some, none for most
 ])
 @pytest.mark.parametrize("dt", [torch.bfloat16, torch.float16])
@@ -306,3 +307,35 @@ def test_block_shapes_of_a_store_projection(n, d_in, d_out, dt):
     want = (x.double() - mean.double()) @ basis.double().T
     want = want / want.norm(dim=1, keepdim=True)
     assert (out.double() - want).abs().max().item() < 2.0 ** -12
+
+
+def test_projection_time_past_a_whole_block():
+    """An eighth more rows than fill one block of 512 per compute unit take about
+    an eighth longer (a second, near empty block of 512 made it 1.35 times)."""
+    g = torch.Generator(device="cuda").manual_seed(1)
+    d_in, d_out, us = 1024, 16, {}
+    basis = torch.randn((d_out, d_in), generator=g, device="cuda") / d_in ** 0.5
+    mean = torch.randn((d_in,), generator=g, device="cuda")
+    for n in (131_072, 150_000):
+        x = torch.randn((n, d_in), generator=g, device="cuda").to(torch.bfloat16)
+        out = torch.empty((n, d_out), dtype=torch.bfloat16, device="cuda")
+        ws = torch.empty(sense.sense_project_workspace_size(basis, x.dtype, n, mean),
+                         dtype=torch.uint8, device="cuda")
+        side = torch.cuda.Stream()
+        with torch.cuda.stream(side):
+            sense.sense_project(x, basis, mean, out=out, workspace=ws)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            for _ in range(5):
+                sense.sense_project(x, basis, mean, out=out, workspace=ws)
+        us[n] = 1e9
+        for _ in range(8):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            graph.replay()
+            b.record()
+            b.synchronize()
+            us[n] = min(us[n], a.elapsed_time(b) * 1e3 / 5)
+    print(f"[project-time] {us}", flush=True)
+    assert us[150_000] < 1.26 * us[131_072]
