@@ -811,8 +811,12 @@ constexpr int kStepVecs = kRowThreads * kNV;
 // of a trie may be dead (64 + 16 drafts of 8, 152064 bf16, 7 tenths judged:
 // 24.8 us with 4 slices a row, 21.8 with 7, 23.4 with 10), and to one step each
 // only up to 512 of them (16 x 6 ragged rows of 128256 bf16: 7.8 us in slices
-// of one step, 7.3 of two).
-constexpr int64_t kSliceSteps = 8, kFillBlocks = 4096, kFillSingle = 512;
+// of one step, 7.3 of two).  Rows shorter than 8 steps are cut to 2048 slices
+// only, since each costs a start and an end (256 x 8 rows whole and in two slices,
+// dense / ragged: 20000 bf16 24.9 / 19.7 us and 28.2 / 22.4, 32000 30.4 / 24.1 and
+// 33.5 / 26.4, 50257 42.9 / 30.2 and 45.2 / 32.1; 64 x 14 rows of 32000 18.2 / 16.8
+// and 18.9 / 15.6).
+constexpr int64_t kSliceSteps = 8, kFillBlocks = 4096, kFillShort = 2048, kFillSingle = 512;
 
 // The most slices of a row, whatever the logits' type: one step of 16-bit
 // logits each.  The workspace holds one partial for each of them.
@@ -823,7 +827,8 @@ Plan make_plan(int logits_dtype, int64_t n_items, int vocab) {
     const int64_t steps = ((int64_t)vocab + (int64_t)vw * kStepVecs - 1) / ((int64_t)vw * kStepVecs);
     const int64_t by_size = (steps + kSliceSteps - 1) / kSliceSteps;
     const int64_t pairs = (steps + 1) / 2;
-    const int64_t fill = (kFillBlocks + n_items - 1) / n_items;
+    const int64_t blocks = steps < kSliceSteps ? kFillShort : kFillBlocks;
+    const int64_t fill = (blocks + n_items - 1) / n_items;
     const int64_t single = (kFillSingle + n_items - 1) / n_items;
     int64_t n = fill < pairs ? fill : pairs;
     n = n > by_size ? n : by_size;

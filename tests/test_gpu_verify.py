@@ -360,3 +360,23 @@ def test_finalize_time_by_rows():
         us[c] = _verify_us(logits, drafts)
     print(f"[verify-finalize] {us}", flush=True)
     assert us[256] < 1.72 * us[64]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("c,v", [(1024, 12_005), (1023, 12_005), (120, 57_344), (128, 57_345)])
+def test_rows_whole_or_in_slices(c, v, dtype):
+    """Either side of the rule that cuts short rows (2048 rows of fewer than eight
+    steps stay whole, 2046 are cut; seven steps of 16-bit logits are 57344)."""
+    x, drafts = structured(5, 8, 2, v, dtype=dtype)
+    logits = x.repeat(c // 8 + 1, 1, 1)[:c].contiguous()
+    drafts = drafts.repeat(c // 8 + 1, 1)[:c].contiguous()
+    out = sense.sense_soft_gate_verify(logits.to(DEV), drafts.to(DEV), None)
+    torch.cuda.synchronize()
+    ref = oracle.soft_gate_verify(host_bits(x), dtype, drafts[:8].numpy(),
+                                  np.full(8, 2, dtype=np.int32))
+    first = {k: (w if k == "best" else w[:8]) for k, w in out.items()}
+    check_verify(first, ref, 0.05, None)
+    for name in ("gate_score", "masks", "rank", "accept_len"):
+        for i in range(8, c, 8):
+            n = min(8, c - i)
+            assert torch.equal(out[name][i:i + n], out[name][:n]), name
