@@ -632,22 +632,31 @@ hipError_t assign_shape(const void* keys, int64_t n, int d, int64_t ld, const fl
                       : go(assign_split_kernel<KT, KD, T, false>);
 }
 
-// The shape with the least time, from its blocks per compute unit.  Measured
-// at 64 dims and 4096 centroids, bf16 keys (us): split with 4 tiles 42 at 16384
-// keys, 76 at 32768, 146 at 65536; staged with 2 tiles 136 at 16384, 139 at
-// 65536, 206 at 98304, 221 at 131072; staged with 4 tiles 187 at 98304, 196 at
-// 131072, 338 at 262144 (432 with 2).  fp16 keys: split 53, 103, 203; 2 tiles
-// 174, 186, 279, 307; 4 tiles 277, 295, 586 (599).  Fewer centroids and other
-// dims scale all three alike (50000 x 32 x 1024: 27, 26, 37; 131072 x 128 x 1024:
-// 206, 132, 136).
+// The shape with the least time, from its rounds of one block per compute unit,
+// in tenths of a round of the split shape with 4 tiles (which has to be ahead by a
+// twentieth: it loses by more where the centroids are few).  Where the registers
+// leave room for a second block on a unit, its round costs less than the first.
+// Measured (us at 4096 centroids; split a round, then 1, 2, 3 and 4 rounds of two
+// tiles and 1 and 2 of four):
+//   bf16  d  32   20 | 81 112 160 218 | 113 170      64   35 | 137 210 326 425 | 190 298
+//        128   69 | 264 410 630 823 | 397 781
+//   fp16  32   25 | 96 150 220 303 | 150 245      64   49 | 174 285 445 593 | 276 557
+//        128   90 | 355 710 1065 1422 | 530 1070
+// 70000 keys, against blocks by the shapes' former costs: 64 dims bf16 189 -> 175,
+// fp16 276 -> 243; 165000: fp16 556 -> 439, 128 dims bf16 782 -> 625.  Fewer
+// centroids scale all alike down to about a thousand; below, two tiles gain (256 x
+// 64 dims fp16, 100000 keys: 38 against 44).
 template <int KT, int KD>
 hipError_t assign_dim(const void* keys, int64_t n, int d, int64_t ld, const float* centroids,
                       int nlist, int cosine, int32_t* out_list, hipStream_t stream) {
     const int64_t cus = device_cus();
     auto rounds = [&](int64_t per) { return (n + per * cus - 1) / (per * cus); };
-    const int64_t split4 = 6 + 37 * rounds(64), stage2 = 30 + 90 * rounds(256),
-                  stage4 = 45 + 123 * rounds(512);
-    if (split4 <= stage2 && split4 <= stage4)
+    constexpr int kFrags = kKeyParts<KT> * (KD / 32);    // of a key tile
+    const int64_t split4 = 10 * rounds(64);
+    const int64_t r2 = rounds(256), r4 = rounds(512);
+    const int64_t stage2 = kFrags > 4 ? 39 * r2 : r2 == 1 ? 39 : r2 / 2 * 59 + r2 % 2 * 32;
+    const int64_t stage4 = KT == DT_BF16 && kFrags <= 2 ? r4 / 2 * 90 + r4 % 2 * 57 : 57 * r4;
+    if (21 * split4 <= 20 * stage2 && 21 * split4 <= 20 * stage4)
         return assign_shape<KT, KD, 4, false>(keys, n, d, ld, centroids, nlist, cosine, out_list, stream);
     if (stage2 < stage4)
         return assign_shape<KT, KD, 2, true>(keys, n, d, ld, centroids, nlist, cosine, out_list, stream);

@@ -332,6 +332,12 @@ BUILD_CASES = [
     (70_001, 24, "f16", 64, "cosine", 8, 256, 24, 1.0),
     (140_003, 64, "bf16", 97, "cosine", 16, 256, 64, 1.0),
     (270_001, 32, "bf16", 63, "ip", 4, 200, 40, 1e-4),
+    # the shapes that share the centroids, by rounds of blocks
+    (77_001, 64, "f16", 97, "ip", 8, 16, 64, 1.0),
+    (100_001, 64, "f16", 97, "cosine", 8, 16, 64, 1.0),
+    (140_001, 64, "f16", 66, "cosine", 8, 16, 64, 1.0),
+    (150_001, 128, "f16", 70, "ip", 8, 16, 128, 1.0),
+    (180_001, 128, "bf16", 70, "cosine", 8, 16, 128, 1.0),
 ]
 
 
@@ -521,3 +527,26 @@ def test_assign_keys_in_small_coordinates(small, kdt, metric):
             bound = (d + 8) * 2.0 ** -24 * (terms.gather(1, best) + terms.gather(1, mine))
             assert bool((s.gather(1, mine) >= s.gather(1, best) - bound).all())
         print(f"[ivf-assign-small] {off} of {n} lists are not the 64-bit choice", flush=True)
+
+
+def test_assign_time_past_a_round():
+    """A fourteenth more fp16 keys than fill a round of four-tile blocks take 1.45
+    times as long (a second, near empty round of them made it 1.9 times)."""
+    d, nlist, us = 64, 4096, {}
+    for n in (131_072, 140_000):
+        g = torch.Generator(device=DEV)
+        g.manual_seed(n)
+        cen = torch.randn(nlist, d, generator=g, device=DEV)
+        keys = torch.randn(n, d, generator=g, device=DEV).to(torch.float16)
+        out = torch.empty(n, dtype=torch.int32, device=DEV)
+        us[n] = 1e9
+        for _ in range(8):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(4):
+                sense.sense_ivf_assign(keys, cen, "cosine", out=out)
+            b.record()
+            b.synchronize()
+            us[n] = min(us[n], a.elapsed_time(b) * 250)
+    print(f"[ivf-assign-time] {us}", flush=True)
+    assert us[140_000] < 1.7 * us[131_072]
